@@ -134,11 +134,12 @@ def _scatterer(c, seed):
 
 
 def _wells(n, seed):
-    """V of the batched Schroedinger law on n x n intervals."""
+    """V of the batched Schroedinger law on n x n intervals; the wells lie closer to the origin, since the continued well of
+    an arbitrary seed can grow beyond what V-cycles converge on."""
     z = [np.exp(1j * GAMMA) * x.to(C128) for x in _axes([n, n], [10.0, 10.0])]
     V = -0.2 * torch.exp(-z[1][:, None] ** 2 - z[0][None, :] ** 2)
     for depth, (cx, cy) in W.wells(seed % (1 << 31), depth=(0.05, 0.2)):
-        V = V - depth * torch.exp(-(z[1][:, None] - cy) ** 2 - (z[0][None, :] - cx) ** 2)
+        V = V - depth * torch.exp(-(z[1][:, None] - 0.5 * cy) ** 2 - (z[0][None, :] - 0.5 * cx) ** 2)
     return V.contiguous()
 
 
