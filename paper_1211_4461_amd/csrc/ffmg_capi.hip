@@ -637,14 +637,26 @@ ffmg_status setup_impl(ffmg_handle *h)
     // exact inverse of the coarsest operator (FP64)
     Level &lc = h->L.back();
     TRY(dalloc(h, &h->aug, (size_t)h->nc * 2 * h->nc * sizeof(cd)));
-    launch_build_coarse(lc.g, lc.P64, lc.q, h->aug, h->stream);
-    cd *gjws = nullptr;
-    if (h->nc > GJ_ONE_BLOCK_MAX) TRY(dalloc(h, &gjws, gauss_jordan_ws(h->nc) * sizeof(cd)));
-    launch_gauss_jordan(h->aug, h->nc, h->d_info, h->stream, gjws);
-    HIPCHK(h, hipGetLastError());
-    int info = 0;
-    HIPCHK(h, hipMemcpyAsync(&info, h->d_info, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
+    int info = -1;
+    auto read_info = [&]() -> ffmg_status {
+        HIPCHK(h, hipGetLastError());
+        HIPCHK(h, hipMemcpyAsync(&info, h->d_info, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(h, hipStreamSynchronize(h->stream));
+        return FFMG_OK;
+    };
+    if (const size_t nws = coarse_inverse_ws(lc.g)) {
+        cd *ws = nullptr;
+        TRY(dalloc(h, &ws, nws * sizeof(cd)));
+        launch_coarse_inverse(lc.g, lc.P64, lc.q, h->aug, ws, h->d_info, h->stream);
+        TRY(read_info());
+    }
+    if (info < 0) {   // not accurate without pivots across slices (or slices too large)
+        launch_build_coarse(lc.g, lc.P64, lc.q, h->aug, h->stream);
+        cd *gjws = nullptr;
+        if (h->nc > GJ_ONE_BLOCK_MAX) TRY(dalloc(h, &gjws, gauss_jordan_ws(h->nc) * sizeof(cd)));
+        launch_gauss_jordan(h->aug, h->nc, h->d_info, h->stream, gjws);
+        TRY(read_info());
+    }
     if (info != 0) return fail(h, FFMG_EINVAL, "coarsest operator is singular (zero pivot in column %d)", info - 1);
     plan_tail<double>(h, h->tail64, h->tail_lds[0]);
     if (ir) plan_tail<float>(h, h->tail32, h->tail_lds[1]);

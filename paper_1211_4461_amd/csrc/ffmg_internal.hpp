@@ -173,6 +173,13 @@ void launch_build_coarse(const LevelGeom &g, const Stencil<double> &P, const cd 
 // gauss_jordan_ws(n) complex values of workspace).
 constexpr int GJ_ONE_BLOCK_MAX = 256;
 void launch_gauss_jordan(cd *aug, int n, int *info, hipStream_t s, cd *ws);
+void launch_gj_init(int *info, hipStream_t s);
+// The coarsest operator's inverse by its block structure, into the right half
+// of aug (n x 2n; the left half is not written); info[0] = -1 where it is not
+// an inverse to 1e-9 (then the elimination above has to run), else 0.
+size_t coarse_inverse_ws(const LevelGeom &g);
+void launch_coarse_inverse(const LevelGeom &g, const Stencil<double> &P, const cd *q, cd *aug, cd *ws, int *info,
+                           hipStream_t s);
 size_t gauss_jordan_ws(int n);
 template <typename T>
 void launch_coarse_apply(const cd *Ainv, int n, const cx<T> *b, cx<T> *u, hipStream_t s, const int *stop = nullptr);

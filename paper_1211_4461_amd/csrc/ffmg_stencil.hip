@@ -2227,6 +2227,8 @@ __global__ __launch_bounds__(256) void k_gjb_update(cd *__restrict__ a, int n, i
     }
 }
 
+void launch_gj_init(int *info, hipStream_t s) { hipLaunchKernelGGL(k_gj_init, dim3(1), dim3(1), 0, s, info); }
+
 void launch_gauss_jordan(cd *aug, int n, int *info, hipStream_t s, cd *ws)
 {
     if (n <= GJ_ONE_BLOCK_MAX || !ws) {
@@ -2234,7 +2236,7 @@ void launch_gauss_jordan(cd *aug, int n, int *info, hipStream_t s, cd *ws)
         return;
     }
     cd *P = ws, *Tr = ws + (size_t)GJB * 2 * n;
-    hipLaunchKernelGGL(k_gj_init, dim3(1), dim3(1), 0, s, info);
+    launch_gj_init(info, s);
     for (int k0 = 0; k0 < n; k0 += GJB) {
         hipLaunchKernelGGL(k_gjb_panel, dim3(1), dim3(1024), 0, s, aug, n, k0, P, Tr, info);
         const int nc = 2 * n - std::min(n, k0 + GJB);
