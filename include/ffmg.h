@@ -462,9 +462,10 @@ ffmg_status mg_profile_durations(ffmg_handle *h, int kernel, double *ms, int64_t
  * directions.  FFMG_TUNE_FF_GEMM: the split-BF16 far-field GEMM (row tiles x
  * column tiles per wave, or a block tile staged in LDS and shared by its four
  * waves); with ff_precision FP64 it has one variant.
- * FFMG_TUNE_TAIL: the largest coarse level (4096, 1024 or 256 interior
- * points for variants 0, 1, 2) run inside the one-workgroup LDS tail of the
- * fused 2D cycle; the levels above it run as grid-wide launches.  It has one
+ * FFMG_TUNE_TAIL: the largest level (4096, 1024 or 256 interior points for
+ * variants 0, 1, 2; in FP64 cycles 1024 at most; the finest level too where it
+ * is that small) run inside the one-workgroup LDS tail of the fused 2D cycle;
+ * the levels above it run as grid-wide launches.  It has one
  * variant for handles without the LDS tail (3D, tile_config != 0) and for the
  * learned smoother.  FFMG_TUNE_SMOOTH: the tile height of the fused 2D
  * smoothing kernel on the finest level (8, 16 or 4 rows of 64 points for

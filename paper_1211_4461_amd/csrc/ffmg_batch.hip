@@ -32,6 +32,7 @@ namespace ffmg {
 struct BatchInst {
     ffmg_handle *op = nullptr;
     int D = 0;                            // levels above the tail (tail starts at level D)
+    TailParams<float> tail{};
     cd *t = nullptr;                      // the other buffer of the FP64 iterate
     cd *f = nullptr;                      // the plane wave's per-axis factors (b = q u_in is never stored)
     std::vector<cf *> u32, b32, t32, r32; // FP32 cycle: levels 0..D (t32, r32: 0..D-1)
@@ -297,7 +298,7 @@ void build_cycle(Plan &pl, std::vector<LaunchRec> &out, Batch &B, bool first, in
             ++r.ntiles;
             BatchInst &I = B.inst[i];
             TailJob<float> j;
-            j.tp = I.op->tail32;
+            j.tp = I.tail;
             j.b_top = I.b32[I.D];
             j.u_top = I.u32[I.D];
             j.stop = &I.ctl->done;
@@ -398,7 +399,7 @@ void build_fmg(Plan &pl, Batch &B, int k)
     for (int i = 0; i < n; ++i) {
         BatchInst &I = B.inst[i];
         TailJob<float> j;
-        j.tp = I.op->tail32;
+        j.tp = I.tail;
         j.b_top = I.b32[I.D];
         j.u_top = I.u32[I.D];
         j.stop = &I.ctl->done;
@@ -447,7 +448,7 @@ void enqueue_cycle(const Batch &B, const std::vector<LaunchRec> &recs, const Dev
         if (r.kind == 4)
             launch_xfer_batch(r.ns, d.xj + r.job_off, r.ntiles, r.max_n, B.stream);
         else if (r.kind == 5)
-            launch_tail2d_fmg_batch<float>(d.tfj + r.job_off, r.ntiles, r.ns, B.tail_lds, B.stream);
+            launch_tail2d_fmg_batch<float>(B.inst[0].tail, d.tfj + r.job_off, r.ntiles, r.ns, B.tail_lds, B.stream);
         else if (r.kind == 3)
             launch_smooth_rr2d_batch<float>(r.zero, srj + r.job_off, tile_job + r.tj_off, r.ntiles, B.stream,
                                             B.th_srr);
@@ -457,7 +458,7 @@ void enqueue_cycle(const Batch &B, const std::vector<LaunchRec> &recs, const Dev
         else if (r.kind == 1)
             launch_resid_restrict2d_batch<float>(rj + r.job_off, tile_job + r.tj_off, r.ntiles, B.stream);
         else
-            launch_tail2d_batch<float>(tj + r.job_off, r.ntiles, B.tail_lds, B.stream);
+            launch_tail2d_batch<float>(B.inst[0].tail, tj + r.job_off, r.ntiles, B.tail_lds, B.stream);
     }
 }
 
@@ -494,20 +495,33 @@ ffmg_status build_batch(ffmg_handle *const *hs, int count, Batch **out)
             (o.inner_cycles > 0 ? o.inner_cycles : DEFAULT_INNER_CYCLES) != B.inner || o.smoother != FFMG_SMOOTH_JACOBI)
             return bail(fail(h0, FFMG_EINVAL, "instance %d: every operator needs the same nu1, nu2 >= 1 and inner "
                                               "cycles", i));
-        const TailParams<float> &tp = h->tail32, &t0 = h0->tail32;
-        if (tp.nt < 2 || tp.nt != t0.nt || h->nc != h0->nc || h->tail_lds[1] != h0->tail_lds[1])
-            return bail(fail(h0, FFMG_EINVAL, "instance %d: the coarse ends of the operators differ", i));
-        for (int k = 0; k < tp.nt; ++k)
-            if (tp.lv[k].mx != t0.lv[k].mx || tp.lv[k].my != t0.lv[k].my)
-                return bail(fail(h0, FFMG_EINVAL, "instance %d: the coarse ends of the operators differ", i));
+        const int nt = tail_count32(h), nl = (int)h->L.size();
+        bool same = nt >= 2 && nt == tail_count32(h0) && h->nc == h0->nc;
+        for (int k = 1; k <= nt && same; ++k)
+            for (int a = 0; a < 2; ++a) same &= h->L[nl - k].g.m[a] == h0->L[h0->L.size() - k].g.m[a];
+        if (!same) return bail(fail(h0, FFMG_EINVAL, "instance %d: the coarse ends of the operators differ", i));
         BatchInst I;
         I.op = h;
-        I.D = (int)h->L.size() - tp.nt;
-        if (I.D < 1) return bail(fail(h0, FFMG_EINVAL, "instance %d: grid too small for a batched solve", i));
-        B.Dmax = std::max(B.Dmax, I.D);
         B.inst.push_back(I);
     }
-    B.tail_lds = h0->tail_lds[1];
+    // the tail: as many levels as every instance has below its finest one and
+    // the kernel holds, the same shapes for all
+    int max_nt = TAIL_MAX_LEVELS;
+    for (const BatchInst &I : B.inst) {
+        TailParams<float> tp;
+        size_t lds;
+        plan_tail32(I.op, tp, lds, max_nt);
+        max_nt = tp.nt;
+    }
+    if (max_nt < 2) return bail(fail(h0, FFMG_EINVAL, "the coarse ends of the operators do not fit one workgroup"));
+    for (int i = 0; i < count; ++i) {
+        BatchInst &I = B.inst[i];
+        plan_tail32(I.op, I.tail, B.tail_lds, max_nt);
+        I.D = (int)I.op->L.size() - I.tail.nt;
+        if (I.D < 1 || I.tail.nt != max_nt)
+            return bail(fail(h0, FFMG_EINVAL, "instance %d: grid too small for a batched solve", i));
+        B.Dmax = std::max(B.Dmax, I.D);
+    }
     // workspaces
     for (BatchInst &I : B.inst) {
         const LevelGeom &g0 = I.op->L[0].g;
@@ -583,8 +597,8 @@ ffmg_status build_batch(ffmg_handle *const *hs, int count, Batch **out)
     BCHK(hipHostMalloc((void **)&B.h_ctls, count * sizeof(SolveCtl), hipHostMallocDefault));
     BCHK(hipStreamCreateWithFlags(&B.stream, hipStreamNonBlocking));
     // the tail kernels' LDS limit must be raised before capture
-    launch_tail2d_batch<float>(nullptr, 0, 0, B.stream);
-    launch_tail2d_fmg_batch<float>(nullptr, 0, 0, 0, B.stream);
+    launch_tail2d_batch<float>(B.inst[0].tail, nullptr, 0, 0, B.stream);
+    launch_tail2d_fmg_batch<float>(B.inst[0].tail, nullptr, 0, 0, 0, B.stream);
     // the graph: two refinement steps (u -> t, t -> u) and the count of
     // finished instances
     BCHK(hipStreamBeginCapture(B.stream, hipStreamCaptureModeThreadLocal));

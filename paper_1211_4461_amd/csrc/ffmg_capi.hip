@@ -347,8 +347,8 @@ void smooth_chain2d(ffmg_handle *h, Level &lv, const cx<T> *b, const cx<T> *src,
 }
 
 // One V(nu1, nu2) cycle with the fused 2D kernels: pre-smoothing u -> t,
-// residual + restriction from t, coarse correction (the LDS tail kernel once
-// the levels are small), then interpolation fused into post-smoothing t -> u.
+// residual + restriction from t, coarse correction, then interpolation fused
+// into post-smoothing t -> u.
 template <typename T>
 void vcycle_fused2d(ffmg_handle *h, int l, const cx<T> *b, cx<T> *u, bool zero_guess, const int *stop)
 {
@@ -381,11 +381,7 @@ void vcycle_fused2d(ffmg_handle *h, int l, const cx<T> *b, cx<T> *u, bool zero_g
         }
         launch_resid_restrict2d<T>(lv.g, LP::P(lv), cur, b, LP::q(lv), LP::b(lc), h->stream, stop);
     }
-    const TailParams<T> &tp = LP::tail(h);
-    if (h->opt.tile_config == TILE_FUSED && tp.nt > 0 && l + 1 == (int)h->L.size() - tp.nt)
-        launch_tail2d<T>(tp, LP::tail_lds(h), LP::b(lc), LP::u(lc), h->stream, stop);
-    else
-        vcycle<T>(h, l + 1, LP::b(lc), LP::u(lc), true, stop);
+    vcycle<T>(h, l + 1, LP::b(lc), LP::u(lc), true, stop);
     if (nu2 > 0) {
         smooth_chain2d<T>(h, lv, b, cur, u, scratch, nu2, false, LP::u(lc), PROF_POST, stop);
     } else {
@@ -458,49 +454,88 @@ uint64_t next_handle_serial()
 constexpr int TAIL_POINTS[] = {4096, 1024, 256};
 constexpr int TAIL_VARIANTS = (int)(sizeof(TAIL_POINTS) / sizeof(TAIL_POINTS[0]));
 
-// Coarse levels handled by the one-workgroup LDS tail (2D): the longest
-// run of levels l >= 1 ending at the coarsest level whose b, u, t, q fit in LDS
-// and that hold at most TAIL_POINTS[tail_variant] points each.
+// The number of tail levels counted from level 1 by their points and by the
+// bytes of four arrays with a border, at most 144 KB.  Which levels the learned
+// smoother leaves to Jacobi and which operators a batch takes together go by
+// this count, whatever the tail kernel itself can hold.
 template <typename T>
-void plan_tail(ffmg_handle *h, TailParams<T> &tp, size_t &lds)
+int tail_count(const ffmg_handle *h)
 {
-    const size_t max_points = (size_t)TAIL_POINTS[h->tail_variant];
-    tp = TailParams<T>{};
-    lds = 0;
+    const size_t max_points = (size_t)TAIL_POINTS[h->tail_variant], budget = 144 * 1024;
     const int nl = (int)h->L.size();
-    if (h->prob.dim != 2 || h->opt.tile_config != TILE_FUSED || nl < 3 || h->opt.smoother == FFMG_SMOOTH_GMRES ||
-        h->opt.smoother == FFMG_SMOOTH_RBGS)
-        return;
-    const size_t budget = 144 * 1024;
     size_t bytes = 0;
-    int top = nl;   // first tail level
+    int top = nl;
     for (int l = nl - 1; l >= 1; --l) {
-        const Level &lv = h->L[l];
-        // b, u, t and a copy of q, each with a one-point zero border
-        size_t add = 4 * (size_t)(lv.g.m[0] + 2) * (lv.g.m[1] + 2) * sizeof(cx<T>);
-        if (lv.g.N() > max_points || bytes + add > budget || nl - l > TAIL_MAX_LEVELS) break;
+        const LevelGeom &g = h->L[l].g;
+        const size_t add = 4 * (size_t)(g.m[0] + 2) * (g.m[1] + 2) * sizeof(cx<T>);
+        if (g.N() > max_points || bytes + add > budget || nl - l > TAIL_MAX_LEVELS) break;
         bytes += add;
         top = l;
     }
-    int nt = nl - top;
-    if (nt < 2) return;   // the coarsest level alone is one matrix-vector product
-    tp.nt = nt;
-    tp.nu1 = nu_pre(h, 1);     // tail levels are coarse levels
-    tp.nu2 = nu_post(h, 1);
+    return nl - top;
+}
+
+// The tail of at most max_nt levels, from level min_level on at the earliest:
+// the longest run of levels ending at the coarsest that fit the kernel and its
+// LDS and hold at most TAIL_POINTS[tail_variant] points each.
+template <typename T>
+void plan_tail_levels(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level, int max_nt)
+{
+    tp = TailParams<T>{};
+    lds = 0;
+    const size_t max_points = (size_t)TAIL_POINTS[h->tail_variant];
+    const int nl = (int)h->L.size();
+    size_t later = 0;       // elements of the levels below, none of them the first
+    int top = nl;
+    for (int l = nl - 1; l >= min_level; --l) {
+        const LevelGeom &g = h->L[l].g;
+        if (g.N() > max_points || nl - l > max_nt || !tail_level_fits(g.m[0], g.m[1], true, sizeof(T) == 4) ||
+            (later + tail_level_elems(g.m[0], g.m[1], true)) * sizeof(cx<T>) > TAIL_LDS_BUDGET)
+            break;
+        top = l;
+        if (!tail_level_fits(g.m[0], g.m[1], false, sizeof(T) == 4)) break;
+        later += tail_level_elems(g.m[0], g.m[1], false);
+    }
+    if (nl - top < 2) return;   // the coarsest level alone is one matrix-vector product
+    tp.nt = nl - top;
+    tp.nu1 = nu_pre(h, top);    // (levels above them only when every level has the same count)
+    tp.nu2 = nu_post(h, top);
     tp.aug = h->aug;
     tp.nc = h->nc;
-    int off = 0;
-    for (int i = 0; i < nt; ++i) {
-        Level &lv = h->L[top + i];
-        TailLevel<T> &t = tp.lv[i];
-        t.mx = lv.g.m[0];
-        t.my = lv.g.m[1];
-        t.off = off;
-        t.P = LvlPtr<T>::P(lv);
-        t.q = LvlPtr<T>::q(lv);
-        off += 4 * (t.mx + 2) * (t.my + 2);
+    for (int i = 0; i < tp.nt; ++i) {
+        const Level &lv = h->L[top + i];
+        tp.lv[i].mx = lv.g.m[0];
+        tp.lv[i].my = lv.g.m[1];
+        if constexpr (sizeof(T) == 4) {
+            tp.lv[i].P = lv.P32;
+            tp.lv[i].q = lv.q32;
+        } else {
+            tp.lv[i].P = lv.P64;
+            tp.lv[i].q = lv.q;
+        }
     }
-    lds = bytes;
+    lds = tail_layout(tp);
+}
+
+// The tail of a handle's own cycles.  The finest level joins it where the grid
+// is small enough (and its sweep counts are those of the other levels).  A
+// coarsest level of more than 256 unknowns stays with the grid-wide kernels:
+// one workgroup takes longer to read its inverse than the launches it saves.
+template <typename T>
+void plan_tail(ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level = 0)
+{
+    tp = TailParams<T>{};
+    lds = 0;
+    if (h->prob.dim != 2 || h->opt.tile_config != TILE_FUSED || h->opt.smoother == FFMG_SMOOTH_GMRES ||
+        h->opt.smoother == FFMG_SMOOTH_RBGS || h->nc > 256)
+        return;
+    if (nu_pre(h, 0) != nu_pre(h, 1) || nu_post(h, 0) != nu_post(h, 1)) min_level = std::max(min_level, 1);
+    int max_nt = TAIL_MAX_LEVELS;
+    if (h->opt.smoother == FFMG_SMOOTH_LEARNED) {
+        min_level = std::max(min_level, 1);
+        max_nt = tail_count<T>(h);
+    }
+    plan_tail_levels<T>(h, tp, lds, min_level, max_nt);
 }
 
 // The learned smoother: weight fragments, kappa h^2 on the finest level, and
@@ -715,10 +750,18 @@ bool learned_level(const ffmg_handle *h, int l)
 {
     if (h->opt.smoother != FFMG_SMOOTH_LEARNED) return false;
     const int nl = (int)h->L.size();
-    const int first_tail = (h->opt.tile_config == TILE_FUSED && h->tail64.nt > 0) ? nl - h->tail64.nt : nl - 1;
+    const int nt = h->opt.tile_config == TILE_FUSED ? tail_count<double>(h) : 0;
+    const int first_tail = nt >= 2 ? nl - nt : nl - 1;
     if (l >= first_tail) return false;
     const int mask = h->opt.learned_levels ? h->opt.learned_levels : 1;
     return l < 31 && ((mask >> l) & 1);
+}
+
+int tail_count32(const ffmg_handle *h) { return tail_count<float>(h); }
+
+void plan_tail32(const ffmg_handle *h, TailParams<float> &tp, size_t &lds, int max_nt)
+{
+    plan_tail_levels<float>(h, tp, lds, 1, max_nt);
 }
 
 // One learned smoothing step on level l: r = b - A u (FP64), then
@@ -746,11 +789,7 @@ static void vcycle_learned(ffmg_handle *h, int l, const cd *b, cd *u, bool zero_
     if (zero_guess) launch_zero<double>(u, lv.g.N(), h->stream, stop);
     for (int s = 0; s < nu_pre(h, l); ++s) learned_step(h, l, b, u, stop);
     launch_resid_restrict2d<double>(lv.g, lv.P64, u, b, lv.q, lc.b, h->stream, stop);
-    const TailParams<double> &tp = h->tail64;
-    if (h->opt.tile_config == TILE_FUSED && tp.nt > 0 && l + 1 == (int)h->L.size() - tp.nt)
-        launch_tail2d<double>(tp, h->tail_lds[0], lc.b, lc.u, h->stream, stop);
-    else
-        vcycle<double>(h, l + 1, lc.b, lc.u, true, stop);
+    vcycle<double>(h, l + 1, lc.b, lc.u, true, stop);
     launch_prolong_add<double>(lv.g, lc.u, u, h->stream, stop);
     for (int s = 0; s < nu_post(h, l); ++s) learned_step(h, l, b, u, stop);
 }
@@ -815,6 +854,10 @@ void vcycle(ffmg_handle *h, int l, const cx<T> *b, cx<T> *u, bool zero_guess, co
             vcycle_learned(h, l, b, u, zero_guess, stop);
             return;
         }
+    }
+    if (LP::tail(h).nt > 0 && l == last + 1 - LP::tail(h).nt) {
+        launch_tail2d<T>(LP::tail(h), LP::tail_lds(h), b, u, zero_guess, h->stream, stop);
+        return;
     }
     if (lv.g.dim == 2 && h->opt.tile_config != TILE_REFERENCE) {
         vcycle_fused2d<T>(h, l, b, u, zero_guess, stop);
@@ -892,17 +935,16 @@ void fmg_start(ffmg_handle *h, const cd *b, cd *u, int k, const double *bnorm2, 
         launch_coarse_apply<double>(h->aug, h->nc, b, u, h->stream, nullptr);
         return;
     }
-    const TailParams<T> &tp = LP::tail(h);
-    const bool tail = (l0.g.dim == 2 && h->opt.tile_config == TILE_FUSED && tp.nt >= 2);
-    const int t0 = tail ? last + 1 - tp.nt : last + 1;   // first tail level
-    const int s0 = (t0 == 0) ? 1 : 0;                      // its first level the start runs on
-    const int top = tail ? t0 + s0 : last;                 // right-hand sides injected down to here
-    const bool tail_fmg = tail && top < last;
+    TailParams<T> tp = LP::tail(h);
+    size_t tail_lds = LP::tail_lds(h);
+    if (tp.nt == last + 1) plan_tail<T>(h, tp, tail_lds, 1);   // no cycle on the finest level
+    const bool tail_fmg = tp.nt >= 2;
+    const int top = tail_fmg ? last + 1 - tp.nt : last;        // right-hand sides injected down to here
     launch_inject_rhs<T>(l0.g, b, LP::b(h->L[1]), bnorm2, h->stream, l0.q, h->pw_f);
     for (int l = 1; l < top; ++l) launch_inject<T>(h->L[l].g, LP::b(h->L[l]), LP::b(h->L[l + 1]), h->stream);
     int from;
     if (tail_fmg) {
-        launch_tail2d_fmg<T>(tp, LP::tail_lds(h), LP::b(h->L[top]), LP::u(h->L[top]), s0, k, h->stream);
+        launch_tail2d_fmg<T>(tp, tail_lds, LP::b(h->L[top]), LP::u(h->L[top]), k, h->stream);
         from = top - 1;
     } else {
         for (int l = top; l < last; ++l) launch_inject<T>(h->L[l].g, LP::b(h->L[l]), LP::b(h->L[l + 1]), h->stream);

@@ -18,13 +18,9 @@
 //       s d (FP64 update of the FP32 correction), r = b - A u' in FP64,
 //       written as FP32 r / s' (the next scaled right-hand side) with the
 //       FP64 sum |r|^2 per block.
-//   k_tail2d  the coarse end of the cycle (all levels small enough for LDS and
-//       the exact coarsest solve) in one 1024-thread workgroup: on those
-//       levels a launch per operation would cost far more than the work.
 //
 // Per point the arithmetic is the same as the one-operation kernels in
-// ffmg_stencil.hip (same operation order, same reduction order in the
-// coarsest solve), so the fused path reproduces them bit for bit.
+// ffmg_stencil.hip (same operation order), so the fused path reproduces them bit for bit.
 #include <algorithm>
 
 #include "ffmg_internal.hpp"
@@ -36,27 +32,6 @@ constexpr int FTX = 64;     // tile width (one wavefront of x)
 constexpr int FTY = 16;     // tile height
 constexpr int RCX = 32;     // resid_restrict: coarse tile 32 x 8 (one point per thread)
 constexpr int RCY = 8;
-
-// Interpolated coarse correction at fine interior point (ix, iy) (0-based):
-// coarse nodes floor(f/2), ceil(f/2) of fine node f = i + 1, weights 1 or 1/2,
-// summed y-outer / x-inner as in the one-operation kernel.  The coarse field
-// is read from ec[(ay - oy) * ld + (ax - ox)] (a tile of it, or all of it).
-template <typename T>
-__device__ __forceinline__ cx<T> interp2d(const cx<T> *ec, int ld, int ox, int oy, int mxc, int myc, int ix, int iy)
-{
-    int fx = ix + 1, fy = iy + 1;
-    cx<T> acc = {T(0), T(0)};
-    for (int Cy = fy / 2; Cy <= (fy + 1) / 2; ++Cy)
-        for (int Cx = fx / 2; Cx <= (fx + 1) / 2; ++Cx) {
-            int dx = fx - 2 * Cx, dy = fy - 2 * Cy;
-            T wx = dx == 0 ? T(1) : T(0.5), wy = dy == 0 ? T(1) : T(0.5);
-            T wgt = wx * wy * T(1);
-            int ax = Cx - 1, ay = Cy - 1;
-            if (ax < 0 || ay < 0 || ax >= mxc || ay >= myc) continue;
-            acc = acc + wgt * ec[(ay - oy) * ld + (ax - ox)];
-        }
-    return acc;
-}
 
 // Tile heights of the smoothing kernel (rows of 64 points): a tunable of the
 // handle (FFMG_TUNE_SMOOTH); the batched path its own (FFMG_TUNE_BATCH).  Every
@@ -537,274 +512,6 @@ __global__ __launch_bounds__(256) void k_refine2d(const cd *__restrict__ u, cons
 }
 
 // ---------------------------------------------------------------------------
-// The coarse end of the V-cycle in one workgroup.  Every tail level keeps
-// b, u, t and a copy of q in LDS, each as a (mx + 2) x (my + 2) array whose
-// one-point border stays zero (the Dirichlet values), so stencil reads need
-// no bounds tests.  Level 0 of the tail starts from a zero guess with b read
-// from b_top; its correction is written to u_top.  Steps are separated by
-// workgroup barriers.
-template <typename T>
-struct TailView {
-    cx<T> *b, *u, *t, *q;
-    int mx, my, W, N;
-    float inv_mx;
-    // padded index of interior point (x, y)
-    __device__ __forceinline__ int at(int x, int y) const { return (y + 1) * W + x + 1; }
-    // (x, y) of the j-th interior point, j < 2^16 (the float quotient is
-    // exact there: its distance to the next integer is >= 0.5 / mx)
-    __device__ __forceinline__ void xy(int j, int &x, int &y) const
-    {
-        y = (int)(((float)j + 0.5f) * inv_mx);
-        x = j - y * mx;
-    }
-};
-
-template <typename T>
-__device__ __forceinline__ TailView<T> tail_view(cx<T> *lds, const TailLevel<T> &L)
-{
-    TailView<T> v;
-    v.mx = L.mx;
-    v.my = L.my;
-    v.W = L.mx + 2;
-    v.N = L.mx * L.my;
-    v.inv_mx = 1.f / (float)L.mx;
-    const int np = (L.mx + 2) * (L.my + 2);
-    v.b = lds + L.off;
-    v.u = v.b + np;
-    v.t = v.u + np;
-    v.q = v.t + np;
-    return v;
-}
-
-// nu sweeps on one tail level into v.u; zero: the incoming u is 0.
-template <typename T>
-__device__ void tail_smooth(const TailView<T> &v, const TailLevel<T> &L, int nu, bool zero)
-{
-    cx<T> *src = v.u, *dst = v.t;
-    for (int s = 0; s < nu; ++s) {
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            const int k = v.at(x, y);
-            cx<T> bj = v.b[k], qj = v.q[k];
-            if (s == 0 && zero) {
-                dst[k] = jacobi0_w(bj, jweight(L.P, qj));
-            } else {
-                dst[k] = jacobi_point<T>(L.P, src[k], src[k - 1], src[k + 1], src[k - v.W], src[k + v.W], bj,
-                                         jweight(L.P, qj));
-            }
-        }
-        __syncthreads();
-        cx<T> *tmp = src;
-        src = dst;
-        dst = tmp;
-    }
-    if (src != v.u) {
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            v.u[v.at(x, y)] = src[v.at(x, y)];
-        }
-        __syncthreads();
-    }
-    if (nu == 0 && zero) {
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            v.u[v.at(x, y)] = cx<T>{T(0), T(0)};
-        }
-        __syncthreads();
-    }
-}
-
-// Zero every array (borders included), then b of tail level s0 from b_top
-// and q of all levels.
-template <typename T>
-__device__ __forceinline__ void tail_load(const TailParams<T> &tp, const cx<T> *__restrict__ b_top, cx<T> *lds,
-                                          int s0)
-{
-    const int nt = tp.nt;
-    const TailLevel<T> &last = tp.lv[nt - 1];
-    const int total = last.off + 4 * (last.mx + 2) * (last.my + 2);
-    for (int j = threadIdx.x; j < total; j += blockDim.x) lds[j] = cx<T>{T(0), T(0)};
-    __syncthreads();
-    TailView<T> v0 = tail_view(lds, tp.lv[s0]);
-    for (int j = threadIdx.x; j < v0.N; j += blockDim.x) {
-        int x, y;
-        v0.xy(j, x, y);
-        v0.b[v0.at(x, y)] = b_top[j];
-    }
-    for (int i = 0; i < nt; ++i) {
-        TailView<T> v = tail_view(lds, tp.lv[i]);
-        const cx<T> *qs = tp.lv[i].q;
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            v.q[v.at(x, y)] = qs[j];
-        }
-    }
-    __syncthreads();
-}
-
-// Coarsest tail level: u = A^{-1} b in FP64, one wave per row, lane-strided
-// sums then a shuffle tree (the order of the one-operation kernel).
-template <typename T>
-__device__ __forceinline__ void tail_coarsest(const TailParams<T> &tp, cx<T> *lds)
-{
-    TailView<T> c = tail_view(lds, tp.lv[tp.nt - 1]);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int n = tp.nc;
-    for (int row = wave; row < n; row += nw) {
-        const cd *ar = tp.aug + (size_t)row * 2 * n + n;
-        double re = 0.0, im = 0.0;
-        for (int k = lane; k < n; k += 64) {
-            cd a = ar[k];
-            int x, y;
-            c.xy(k, x, y);
-            cx<T> bk = c.b[c.at(x, y)];
-            double br = (double)bk.re, bi = (double)bk.im;
-            re += a.re * br - a.im * bi;
-            im += a.re * bi + a.im * br;
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-            re += __shfl_down(re, off, 64);
-            im += __shfl_down(im, off, 64);
-        }
-        if (lane == 0) {
-            int x, y;
-            c.xy(row, x, y);
-            c.u[c.at(x, y)] = cx<T>{T(re), T(im)};
-        }
-    }
-    __syncthreads();
-}
-
-// One V-cycle from tail level i0 (its b and u in LDS; zero_top: its u is
-// taken as 0): pre-smoothing, residual and restriction down to the coarsest
-// level (every coarser level from a zero guess), exact solve, then
-// interpolation of the correction and post-smoothing back up to i0.
-template <typename T>
-__device__ __forceinline__ void tail_vcycle(const TailParams<T> &tp, cx<T> *lds, int i0, bool zero_top)
-{
-    const int nt = tp.nt;
-    for (int i = i0; i + 1 < nt; ++i) {
-        const TailLevel<T> &L = tp.lv[i];
-        TailView<T> v = tail_view(lds, L);
-        tail_smooth<T>(v, L, tp.nu1, zero_top || i > i0);
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            const int k = v.at(x, y);
-            v.t[k] = resid_point<T>(L.P, v.u[k], v.u[k - 1], v.u[k + 1], v.u[k - v.W], v.u[k + v.W], v.b[k], v.q[k]);
-        }
-        __syncthreads();
-        TailView<T> c = tail_view(lds, tp.lv[i + 1]);
-        const T w[3] = {T(0.25), T(0.5), T(0.25)};
-        for (int J = threadIdx.x; J < c.N; J += blockDim.x) {
-            int I, K;
-            c.xy(J, I, K);
-            const int fk = v.at(2 * I + 1, 2 * K + 1);
-            cx<T> acc = {T(0), T(0)};
-            for (int dy = -1; dy <= 1; ++dy)
-                for (int dx = -1; dx <= 1; ++dx) {
-                    T wgt = (w[dx + 1] * w[dy + 1]) * T(1);
-                    acc = acc + wgt * v.t[fk + dy * v.W + dx];
-                }
-            c.b[c.at(I, K)] = acc;
-        }
-        __syncthreads();
-    }
-    tail_coarsest<T>(tp, lds);
-    for (int i = nt - 2; i >= i0; --i) {
-        const TailLevel<T> &L = tp.lv[i];
-        TailView<T> v = tail_view(lds, L);
-        TailView<T> c = tail_view(lds, tp.lv[i + 1]);
-        const cx<T> *cu = c.u + c.W + 1;   // interior (0, 0) of the coarse correction, row stride c.W
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            const int k = v.at(x, y);
-            v.u[k] = v.u[k] + interp2d<T>(cu, c.W, 0, 0, c.mx, c.my, x, y);
-        }
-        __syncthreads();
-        tail_smooth<T>(v, L, tp.nu2, false);
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void tail_store(const TailParams<T> &tp, cx<T> *lds, int s0, cx<T> *__restrict__ u_top)
-{
-    TailView<T> v0 = tail_view(lds, tp.lv[s0]);
-    for (int j = threadIdx.x; j < v0.N; j += blockDim.x) {
-        int x, y;
-        v0.xy(j, x, y);
-        u_top[j] = v0.u[v0.at(x, y)];
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void tail2d_body(const TailParams<T> &tp, const cx<T> *__restrict__ b_top,
-                                            cx<T> *__restrict__ u_top, cx<T> *lds)
-{
-    tail_load<T>(tp, b_top, lds, 0);
-    tail_vcycle<T>(tp, lds, 0, true);
-    tail_store<T>(tp, lds, 0, u_top);
-}
-
-// Full multigrid start on the tail levels s0 .. nt - 1 in one workgroup: b of
-// level s0 from b_top, injected level by level down to the coarsest, exact
-// solve there, then on each level up to s0 the interpolated coarser solution
-// as the guess and k V-cycles; u_top receives level s0's solution.
-template <typename T>
-__device__ __forceinline__ void tail2d_fmg_body(const TailParams<T> &tp, const cx<T> *__restrict__ b_top,
-                                                cx<T> *__restrict__ u_top, int s0, int k, cx<T> *lds)
-{
-    const int nt = tp.nt;
-    tail_load<T>(tp, b_top, lds, s0);
-    for (int i = s0; i + 1 < nt; ++i) {
-        TailView<T> v = tail_view(lds, tp.lv[i]);
-        TailView<T> c = tail_view(lds, tp.lv[i + 1]);
-        for (int J = threadIdx.x; J < c.N; J += blockDim.x) {
-            int I, K;
-            c.xy(J, I, K);
-            c.b[c.at(I, K)] = v.b[v.at(2 * I + 1, 2 * K + 1)];
-        }
-        __syncthreads();
-    }
-    tail_coarsest<T>(tp, lds);
-    for (int i = nt - 2; i >= s0; --i) {
-        TailView<T> v = tail_view(lds, tp.lv[i]);
-        TailView<T> c = tail_view(lds, tp.lv[i + 1]);
-        const cx<T> *cu = c.u + c.W + 1;
-        for (int j = threadIdx.x; j < v.N; j += blockDim.x) {
-            int x, y;
-            v.xy(j, x, y);
-            v.u[v.at(x, y)] = interp2d<T>(cu, c.W, 0, 0, c.mx, c.my, x, y);
-        }
-        __syncthreads();
-        for (int c2 = 0; c2 < k; ++c2) tail_vcycle<T>(tp, lds, i, false);
-    }
-    tail_store<T>(tp, lds, s0, u_top);
-}
-
-template <typename T>
-__global__ __launch_bounds__(1024) void k_tail2d_fmg(TailParams<T> tp, const cx<T> *__restrict__ b_top,
-                                                     cx<T> *__restrict__ u_top, int s0, int k)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char tail_lds_f[];
-    tail2d_fmg_body<T>(tp, b_top, u_top, s0, k, reinterpret_cast<cx<T> *>(tail_lds_f));
-}
-
-template <typename T>
-__global__ __launch_bounds__(1024) void k_tail2d(TailParams<T> tp, const cx<T> *__restrict__ b_top,
-                                                 cx<T> *__restrict__ u_top, const int *__restrict__ stop)
-{
-    if (stop && *stop) return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char tail_lds[];
-    tail2d_body<T>(tp, b_top, u_top, reinterpret_cast<cx<T> *>(tail_lds));
-}
-
-// ---------------------------------------------------------------------------
 static int tiles2d(const LevelGeom &g, int &tx)
 {
     tx = (g.m[0] + FTX - 1) / FTX;
@@ -921,45 +628,6 @@ void launch_refine2d(const LevelGeom &g, const Stencil<double> &P, const cd *u, 
                        pwf);
 }
 
-template <typename T>
-size_t tail2d_lds_bytes(const int *mx, const int *my, int nt)
-{
-    size_t n = 0;
-    for (int i = 0; i < nt; ++i) n += 3 * (size_t)mx[i] * my[i];
-    return n * sizeof(cx<T>);
-}
-template size_t tail2d_lds_bytes<double>(const int *, const int *, int);
-template size_t tail2d_lds_bytes<float>(const int *, const int *, int);
-
-template <typename T>
-void launch_tail2d(const TailParams<T> &tp, size_t lds_bytes, const cx<T> *b_top, cx<T> *u_top, hipStream_t s,
-                   const int *stop)
-{
-    // once per instantiation (a thread-safe static initialisation)
-    static const bool attr_set = [] {
-        (void)hipFuncSetAttribute((const void *)k_tail2d<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        return true;
-    }();
-    (void)attr_set;
-    hipLaunchKernelGGL((k_tail2d<T>), dim3(1), dim3(1024), lds_bytes, s, tp, b_top, u_top, stop);
-}
-template <typename T>
-void launch_tail2d_fmg(const TailParams<T> &tp, size_t lds_bytes, const cx<T> *b_top, cx<T> *u_top, int s0, int k,
-                       hipStream_t s)
-{
-    // once per instantiation (a thread-safe static initialisation)
-    static const bool attr_set = [] {
-        (void)hipFuncSetAttribute((const void *)k_tail2d_fmg<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        return true;
-    }();
-    (void)attr_set;
-    hipLaunchKernelGGL((k_tail2d_fmg<T>), dim3(1), dim3(1024), lds_bytes, s, tp, b_top, u_top, s0, k);
-}
-template void launch_tail2d_fmg<double>(const TailParams<double> &, size_t, const cd *, cd *, int, int, hipStream_t);
-template void launch_tail2d_fmg<float>(const TailParams<float> &, size_t, const cf *, cf *, int, int, hipStream_t);
-template void launch_tail2d<double>(const TailParams<double> &, size_t, const cd *, cd *, hipStream_t, const int *);
-template void launch_tail2d<float>(const TailParams<float> &, size_t, const cf *, cf *, hipStream_t, const int *);
-
 // ---------------------------------------------------------------------------
 // Batched launches.  The flat block index is mapped XCD-contiguously onto the
 // concatenated tiles of all jobs; within a job the tile and the slot of its
@@ -1005,26 +673,6 @@ __global__ __launch_bounds__(256) void k_refine2d_batch(const RefineJob *__restr
     const int tile = t - J.tile0;
     refine2d_body(J.u, J.d, J.b, J.q, J.u_out, J.r32, J.ctl, J.P, J.tiles_x, tile,
                   J.partial + xcd_tile_inv(tile, J.ntiles), J.f);
-}
-
-template <typename T>
-__global__ __launch_bounds__(1024) void k_tail2d_batch(const TailJob<T> *__restrict__ jobs)
-{
-    const TailJob<T> &J = jobs[blockIdx.x];
-    if (J.stop && *J.stop) return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char tail_lds_b[];
-    tail2d_body<T>(J.tp, J.b_top, J.u_top, reinterpret_cast<cx<T> *>(tail_lds_b));
-}
-
-// The full multigrid start of every tail in one launch (one workgroup per
-// job, from the first tail level).
-template <typename T>
-__global__ __launch_bounds__(1024) void k_tail2d_fmg_batch(const TailJob<T> *__restrict__ jobs, int k)
-{
-    const TailJob<T> &J = jobs[blockIdx.x];
-    if (J.stop && *J.stop) return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char tail_lds_fb[];
-    tail2d_fmg_body<T>(J.tp, J.b_top, J.u_top, 0, k, reinterpret_cast<cx<T> *>(tail_lds_fb));
 }
 
 void batch_tiles(int variant, int *th_smooth, int *th_srr)
@@ -1124,34 +772,5 @@ void launch_refine2d_batch(const RefineJob *jobs, const int *tile_job, int ntile
     if (ntiles <= 0) return;
     hipLaunchKernelGGL(k_refine2d_batch, dim3(ntiles), dim3(256), 0, s, jobs, tile_job);
 }
-
-template <typename T>
-void launch_tail2d_batch(const TailJob<T> *jobs, int njobs, size_t lds_bytes, hipStream_t s)
-{
-    // once per instantiation (a thread-safe static initialisation)
-    static const bool attr_set = [] {
-        (void)hipFuncSetAttribute((const void *)k_tail2d_batch<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        return true;
-    }();
-    (void)attr_set;
-    if (njobs <= 0) return;
-    hipLaunchKernelGGL((k_tail2d_batch<T>), dim3(njobs), dim3(1024), lds_bytes, s, jobs);
-}
-template <typename T>
-void launch_tail2d_fmg_batch(const TailJob<T> *jobs, int njobs, int k, size_t lds_bytes, hipStream_t s)
-{
-    // once per instantiation (a thread-safe static initialisation)
-    static const bool attr_set = [] {
-        (void)hipFuncSetAttribute((const void *)k_tail2d_fmg_batch<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  160 * 1024);
-        return true;
-    }();
-    (void)attr_set;
-    if (njobs <= 0) return;
-    hipLaunchKernelGGL((k_tail2d_fmg_batch<T>), dim3(njobs), dim3(1024), lds_bytes, s, jobs, k);
-}
-template void launch_tail2d_fmg_batch<float>(const TailJob<float> *, int, int, size_t, hipStream_t);
-template void launch_tail2d_batch<float>(const TailJob<float> *, int, size_t, hipStream_t);
-template void launch_tail2d_batch<double>(const TailJob<double> *, int, size_t, hipStream_t);
 
 }  // namespace ffmg

@@ -152,6 +152,10 @@ void batch_destroy(Batch *b);
 // one learned smoothing step on level l, in place on u
 void learned_step(ffmg_handle *h, int l, const cd *b, cd *u, const int *stop);
 bool learned_level(const ffmg_handle *h, int l);
+// The FP32 tail of a batched instance: how many levels count for taking
+// operators together, and the tail of at most max_nt coarse levels.
+int tail_count32(const ffmg_handle *h);
+void plan_tail32(const ffmg_handle *h, ffmg::TailParams<float> &tp, size_t &lds, int max_nt);
 
 }  // namespace ffmg
 

@@ -256,13 +256,14 @@ void launch_refine2d(const LevelGeom &g, const Stencil<double> &P, const cd *u, 
                      const cd *q, cd *u_out, cf *r32, const SolveCtl *ctl, double *partial, hipStream_t st,
                      const int *stop, const cd *pwf = nullptr);
 
-// The coarse end of a 2D V-cycle in one workgroup, all fields in LDS: the
-// levels lt .. L-1 of the hierarchy (small enough for LDS) and the exact
-// coarsest solve.  Reads b of level lt, writes its correction u (zero guess).
+// The coarse end of a 2D V-cycle in one workgroup (ffmg_tail2d.hip): the levels
+// lt .. L-1 of the hierarchy and the exact coarsest solve.
 constexpr int TAIL_MAX_LEVELS = 6;
+constexpr size_t TAIL_LDS_BUDGET = 160 * 1024;
 template <typename T>
 struct TailLevel {
     int mx, my;
+    int lp;                // log2(mx + 1)
     int off;               // element offset of this level's fields in LDS
     Stencil<T> P;
     const cx<T> *q;
@@ -273,18 +274,25 @@ struct TailParams {
     int nu1, nu2;
     const cd *aug;         // [A | A^{-1}] of the coarsest level, row stride 2 nc
     int nc;
+    int inv_off;           // element offset of the coarsest inverse in LDS
     TailLevel<T> lv[TAIL_MAX_LEVELS];
 };
-// LDS bytes the tail needs for the given levels (0 if it does not fit).
+// Whether a level fits the tail (as its first level or a later one), and the
+// elements of LDS it takes there.
+bool tail_level_fits(int mx, int my, bool first, bool fp32);
+size_t tail_level_elems(int mx, int my, bool first);
+// Fills lp and off of the levels from mx, my; returns the bytes of LDS.
 template <typename T>
-size_t tail2d_lds_bytes(const int *mx, const int *my, int nt);
+size_t tail_layout(TailParams<T> &tp);
+// One V-cycle on the tail's first level: b_top its right-hand side, u_top its
+// correction (zero: from a zero guess).
 template <typename T>
-void launch_tail2d(const TailParams<T> &tp, size_t lds_bytes, const cx<T> *b_top, cx<T> *u_top, hipStream_t s,
-                   const int *stop);
-// Full multigrid start on tail levels s0 .. nt - 1 (b_top: level s0's
+void launch_tail2d(const TailParams<T> &tp, size_t lds_bytes, const cx<T> *b_top, cx<T> *u_top, bool zero,
+                   hipStream_t s, const int *stop);
+// Full multigrid start on the tail's levels (b_top: the first level's
 // right-hand side; u_top: its solution after k V-cycles there).
 template <typename T>
-void launch_tail2d_fmg(const TailParams<T> &tp, size_t lds_bytes, const cx<T> *b_top, cx<T> *u_top, int s0, int k,
+void launch_tail2d_fmg(const TailParams<T> &tp, size_t lds_bytes, const cx<T> *b_top, cx<T> *u_top, int k,
                        hipStream_t s);
 
 // Batched fused 2D kernels (one launch for many instances).  Each job is one
@@ -355,11 +363,12 @@ template <typename T>
 void launch_resid_restrict2d_batch(const RRJob<T> *jobs, const int *tile_job, int ntiles, hipStream_t s);
 void launch_refine2d_batch(const RefineJob *jobs, const int *tile_job, int ntiles, hipStream_t s);
 template <typename T>
-void launch_tail2d_batch(const TailJob<T> *jobs, int njobs, size_t lds_bytes, hipStream_t s);
+void launch_tail2d_batch(const TailParams<T> &tp, const TailJob<T> *jobs, int njobs, size_t lds_bytes, hipStream_t s);
 // the full multigrid start of each job's tail (from its first level), k
 // V-cycles per level
 template <typename T>
-void launch_tail2d_fmg_batch(const TailJob<T> *jobs, int njobs, int k, size_t lds_bytes, hipStream_t s);
+void launch_tail2d_fmg_batch(const TailParams<T> &tp, const TailJob<T> *jobs, int njobs, int k, size_t lds_bytes,
+                             hipStream_t s);
 
 // Per-instance setup of a batched solve (ffmg_stencil.hip): the plane wave's
 // factors, zero guess, ||b||^2, control init and the initial scaled FP32
