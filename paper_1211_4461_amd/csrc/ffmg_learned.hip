@@ -39,6 +39,15 @@
 namespace ffmg {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+
+// Hardware round-to-nearest-even pair FP32 -> BF16 (v_cvt_pk_bf16_f32).
+typedef float fv2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bv2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi)
+{
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(fv2{lo, hi}, bv2));
+}
 
 // ---------------------------------------------------------------------------
 // BF16 helpers: round-to-nearest-even of a finite FP32, and complex values
@@ -59,13 +68,6 @@ __device__ __forceinline__ float2 unpack_c(unsigned v)
     return make_float2(__builtin_bit_cast(float, v << 16), __builtin_bit_cast(float, v & 0xFFFF0000u));
 }
 
-__device__ __forceinline__ void cmac(float2 &acc, float2 w, float2 x)
-{
-    acc.x = fmaf(w.x, x.x, acc.x);
-    acc.x = fmaf(-w.y, x.y, acc.x);
-    acc.y = fmaf(w.x, x.y, acc.y);
-    acc.y = fmaf(w.y, x.x, acc.y);
-}
 // acc += conj(w) x
 __device__ __forceinline__ void cmac_cw(float2 &acc, float2 w, float2 x)
 {
@@ -74,355 +76,552 @@ __device__ __forceinline__ void cmac_cw(float2 &acc, float2 w, float2 x)
     acc.y = fmaf(w.x, x.y, acc.y);
     acc.y = fmaf(-w.y, x.x, acc.y);
 }
-// acc += g conj(x)
-__device__ __forceinline__ void cmac_cx(float2 &acc, float2 g, float2 x)
-{
-    acc.x = fmaf(g.x, x.x, acc.x);
-    acc.x = fmaf(g.y, x.y, acc.x);
-    acc.y = fmaf(g.y, x.x, acc.y);
-    acc.y = fmaf(-g.x, x.y, acc.y);
-}
-
 __device__ __forceinline__ constexpr int tap_dy(int t) { return t / 3 - 1; }
 __device__ __forceinline__ constexpr int tap_dx(int t) { return t % 3 - 1; }
 
 // ---------------------------------------------------------------------------
-// Training: one 256-thread workgroup per 32 x 32 patch.
+// Training: one 1024-thread workgroup per 32 x 32 patch, a point per thread in
+// the point-wise steps.  Every product of two BF16 arrays (layers 1 to 3, the
+// gradients of x1 and of all weights) is a GEMM on v_mfma_f32_16x16x32_bf16
+// (operand layout as in the inference kernel below) with FP32 accumulators, so
+// the products are exact and the precision is that of FP32 sums; the gradient
+// g_N of the output is FP32 and enters the weight gradient of layer 3 as three
+// BF16 parts (24 bits).
+//   convolutions: rows = 16 points, K = the 16 complex channels of a tap as 32
+//     real slots (a packed activation is two of them), columns = 16 output
+//     channels, one product for the real and one for the imaginary parts;
+//   weight gradients sum_p g(p) conj(x(p + d)): K = 16 points x (re, im), the
+//     packed dwords of both operands as they are for the real part, g's as
+//     (im, -re) for the imaginary part.
+// A row of a point's 16 packed channels is 64 bytes in LDS; its four 16-byte
+// chunks are permuted by the point (chunk c of point p at c ^ (p / 4 % 4)), so
+// that the 16-point operand reads spread over all banks.  Points outside the
+// patch read row TPP, which is zero.
+// Bound by LDS latency and the vector unit between the GEMMs (which take about
+// 8 us at the matrix rate).  Measured, 256 patches: 77 us; with one FP32 vector
+// product per weight and point in 256-thread workgroups it took 879 us.
 constexpr float LOSS_ALPHA = 1.f;   // weight of the error-growth penalty
 constexpr int TP = 32;              // patch side
 constexpr int TPP = TP * TP;        // points per patch
-constexpr int TPT = TPP / 256;      // points per thread
+constexpr int TRAIN_SETS = 8;       // partial sums kept in LDS for a weight gradient
 
-struct TrainLds {
-    unsigned x0[TPP][2];            // inputs (r~, kappa~), BF16 complex
-    unsigned x1[TPP][16];           // layer-1 output, later its gradient
-    unsigned x2[TPP][16];           // layer-2 output, later its gradient
+struct alignas(16) TrainLds {
+    unsigned x1[(TPP + 1) * 16];    // layer-1 output, later its gradient, later that of a
+    unsigned x2[(TPP + 1) * 16];    // layer-2 output, later its gradient, later that of m
+    unsigned r0[TPP + 4], k0[TPP + 4];  // inputs r~, kappa~, BF16 complex
     float2 d[TPP];                  // e~ - N, later g_N
-    float2 z[TPP];                  // mask L5 (e~ - N)
+    union {
+        unsigned w2[9 * 256];       // packed W2
+        float2 z[TPP];              // mask L5 (e~ - N)
+        unsigned gp[3][TPP];        // g_N as three BF16 parts
+    };
+};
+static_assert(offsetof(TrainLds, z) == offsetof(TrainLds, d) + sizeof(float2) * TPP && sizeof(TrainLds) <= 160 * 1024,
+              "d and what follows it serve as one buffer of partial sums");
+static_assert(TRAIN_SETS * 288 * sizeof(float2) <= sizeof(float2) * TPP + 3 * sizeof(unsigned) * TPP, "partial sums");
+static_assert(TRAIN_SETS * 144 * sizeof(float2) <= 3 * sizeof(unsigned) * TPP, "partial sums");
+
+__device__ __forceinline__ bool in_patch(int y, int x) { return (unsigned)y < (unsigned)TP && (unsigned)x < (unsigned)TP; }
+__device__ __forceinline__ int point_or_zero(int y, int x) { return in_patch(y, x) ? y * TP + x : TPP; }
+// dword of channel c of point p, and the 16-byte chunk c of it
+__device__ __forceinline__ int act_at(int p, int c) { return p * 16 + (((c >> 2) ^ ((p >> 2) & 3)) << 2) + (c & 3); }
+__device__ __forceinline__ bf8 act_chunk(const unsigned *x, int p, int c)
+{
+    return __builtin_bit_cast(bf8, *reinterpret_cast<const uint4 *>(x + p * 16 + ((c ^ ((p >> 2) & 3)) << 2)));
+}
+__device__ __forceinline__ unsigned swap_halves(unsigned v) { return __builtin_amdgcn_alignbit(v, v, 16); }
+__device__ __forceinline__ bf8 as_bf8(unsigned a, unsigned b, unsigned c, unsigned d)
+{
+    return __builtin_bit_cast(bf8, make_uint4(a, b, c, d));
+}
+// BF16-rounded weights: the upper halves of their FP32 bits are exact
+__device__ __forceinline__ unsigned pack_weight(float2 w)
+{
+    return __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, w.y), __builtin_bit_cast(unsigned, w.x), 0x07060302u);
+}
+constexpr unsigned NEG_HI = 0x80000000u, NEG_LO = 0x8000u;
+
+// The four row tiles (16 points each: half a patch row) of a wave.
+struct TrainTile {
+    int py, px;     // of the lane's point as an operand row
+    int p0;         // of the tile's first point
+    __device__ __forceinline__ TrainTile(int wave, int q)
+    {
+        const int rt = wave * 4 + q;
+        py = rt >> 1;
+        px = 16 * (rt & 1) + (threadIdx.x & 15);
+        p0 = py * TP + 16 * (rt & 1);
+    }
 };
 
-static_assert(offsetof(TrainLds, z) == offsetof(TrainLds, d) + sizeof(float2) * TPP,
-              "d and z must be contiguous (used together as a partial-sum buffer)");
-
-__device__ __forceinline__ bool in_patch(int y, int x) { return y >= 0 && y < TP && x >= 0 && x < TP; }
-
-// a_o = sum_t W1[t][o][0] r~(p + d_t), m_o = sum_t W1[t][o][1] kappa~(p + d_t)
-__device__ __forceinline__ void layer1_point(const TrainLds &S, const float2 *__restrict__ W1, int p, float2 (&a)[16],
-                                             float2 (&m)[16])
+// acc[q] = the 3x3 convolution of x with W2 (16 -> 16 channels) at the wave's
+// tiles, real and imaginary parts; TR: with the conjugate transposed weights.
+template <bool TR>
+__device__ __forceinline__ void conv16(const unsigned *x, const unsigned *w2, int wave, f4 (&acc)[4][2])
 {
-    const int py = p / TP, px = p % TP;
-    float2 x[9][2];
+    const int j = threadIdx.x & 15, kq = (threadIdx.x & 63) >> 4;
 #pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q][0] = acc[q][1] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 3
     for (int t = 0; t < 9; ++t) {
-        const int yy = py + tap_dy(t), xx = px + tap_dx(t);
-        const bool in = in_patch(yy, xx);
-        const int q = in ? yy * TP + xx : 0;
+        const int dy = TR ? -tap_dy(t) : tap_dy(t), dx = TR ? -tap_dx(t) : tap_dx(t);
+        unsigned w[4];
+        if (TR) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) x[t][i] = in ? unpack_c(S.x0[q][i]) : make_float2(0.f, 0.f);
-    }
+            for (int e = 0; e < 4; ++e) w[e] = w2[(t * 16 + 4 * kq + e) * 16 + j];
+        } else {
+            const uint4 v = *reinterpret_cast<const uint4 *>(w2 + (t * 16 + j) * 16 + 4 * kq);
+            w[0] = v.x;
+            w[1] = v.y;
+            w[2] = v.z;
+            w[3] = v.w;
+        }
+        unsigned re[4], im[4];
 #pragma unroll
-    for (int o = 0; o < 16; ++o) {
-        a[o] = make_float2(0.f, 0.f);
-        m[o] = make_float2(0.f, 0.f);
+        for (int e = 0; e < 4; ++e) {
+            re[e] = TR ? w[e] : w[e] ^ NEG_HI;                              // (wr, wi) or (wr, -wi)
+            im[e] = TR ? swap_halves(w[e]) ^ NEG_LO : swap_halves(w[e]);    // (-wi, wr) or (wi, wr)
+        }
+        const bf8 bre = as_bf8(re[0], re[1], re[2], re[3]), bim = as_bf8(im[0], im[1], im[2], im[3]);
 #pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            cmac(a[o], W1[(t * 16 + o) * 2 + 0], x[t][0]);
-            cmac(m[o], W1[(t * 16 + o) * 2 + 1], x[t][1]);
+        for (int q = 0; q < 4; ++q) {
+            const TrainTile T(wave, q);
+            const bf8 a = act_chunk(x, point_or_zero(T.py + dy, T.px + dx), kq);
+            acc[q][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bre, acc[q][0], 0, 0, 0);
+            acc[q][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bim, acc[q][1], 0, 0, 0);
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_train_patch(const float2 *__restrict__ rt, const float2 *__restrict__ kt,
-                                                     const float2 *__restrict__ et,
-                                                     const float2 *__restrict__ W, float2 *__restrict__ dW_part,
-                                                     float *__restrict__ loss_part, int border)
+// Layer 1 at the wave's tile: a (from r~) and m (from kappa~), real and
+// imaginary parts; K = 9 taps x (re, im), lanes 16 kq.. the taps 4 kq .. + 3.
+struct Layer1 {
+    bf8 are, aim, mre, mim;
+    __device__ __forceinline__ explicit Layer1(const float2 *__restrict__ W1)
+    {
+        const int j = threadIdx.x & 15, kq = (threadIdx.x & 63) >> 4;
+        unsigned a[4], m[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = 4 * kq + e, s = min(t, 8);
+            const float4 w = *reinterpret_cast<const float4 *>(W1 + (s * 16 + j) * 2);
+            a[e] = t < 9 ? pack_weight(make_float2(w.x, w.y)) : 0u;
+            m[e] = t < 9 ? pack_weight(make_float2(w.z, w.w)) : 0u;
+        }
+        are = as_bf8(a[0] ^ NEG_HI, a[1] ^ NEG_HI, a[2] ^ NEG_HI, a[3] ^ NEG_HI);
+        aim = as_bf8(swap_halves(a[0]), swap_halves(a[1]), swap_halves(a[2]), swap_halves(a[3]));
+        mre = as_bf8(m[0] ^ NEG_HI, m[1] ^ NEG_HI, m[2] ^ NEG_HI, m[3] ^ NEG_HI);
+        mim = as_bf8(swap_halves(m[0]), swap_halves(m[1]), swap_halves(m[2]), swap_halves(m[3]));
+    }
+    __device__ __forceinline__ void at(const TrainLds &S, const TrainTile &T, f4 (&a)[2], f4 (&m)[2]) const
+    {
+        const int kq = (threadIdx.x & 63) >> 4;
+        unsigned r[4], k[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = 4 * kq + e, ty = t / 3;
+            const int p = t < 9 ? point_or_zero(T.py + ty - 1, T.px + t - 3 * ty - 1) : TPP;
+            r[e] = S.r0[p];
+            k[e] = S.k0[p];
+        }
+        const bf8 ar = as_bf8(r[0], r[1], r[2], r[3]), ak = as_bf8(k[0], k[1], k[2], k[3]);
+        const f4 z = {0.f, 0.f, 0.f, 0.f};
+        a[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar, are, z, 0, 0, 0);
+        a[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar, aim, z, 0, 0, 0);
+        m[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak, mre, z, 0, 0, 0);
+        m[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak, mim, z, 0, 0, 0);
+    }
+};
+
+// The 5-point Laplacian stencil of v at (y, x), zero outside the patch.
+__device__ __forceinline__ float2 lap5(const float2 *v, int y, int x)
+{
+    const float2 c = v[y * TP + x];
+    float2 s = make_float2(4.f * c.x, 4.f * c.y);
+    const int nb[4][2] = {{0, -1}, {0, 1}, {-1, 0}, {1, 0}};
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int yy = y + nb[m][0], xx = x + nb[m][1];
+        if (in_patch(yy, xx)) {
+            const float2 w = v[yy * TP + xx];
+            s.x -= w.x;
+            s.y -= w.y;
+        }
+    }
+    return s;
+}
+
+__device__ __forceinline__ void stage_w2(TrainLds &S, const float2 *__restrict__ W2)
+{
+    for (int k = threadIdx.x; k < 9 * 256; k += 1024) S.w2[k] = pack_weight(W2[k]);
+}
+
+__global__ __launch_bounds__(1024) void k_train_patch(const float2 *__restrict__ rt, const float2 *__restrict__ kt,
+                                                      const float2 *__restrict__ et, const float2 *__restrict__ W,
+                                                      float2 *__restrict__ dW_part, float *__restrict__ loss_part,
+                                                      int border)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     TrainLds &S = *reinterpret_cast<TrainLds *>(lds_raw);
     const float2 *W1 = W + NET_W1, *W2 = W + NET_W2, *W3 = W + NET_W3;
     const size_t base = (size_t)blockIdx.x * TPP;
-    const int tid = threadIdx.x;
-    // inputs, rounded to BF16
-    for (int p = tid; p < TPP; p += 256) {
-        float2 r = rt[base + p], k = kt[base + p];
-        S.x0[p][0] = pack_c(r.x, r.y);
-        S.x0[p][1] = pack_c(k.x, k.y);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, kq = lane >> 4;
+    const int py = tid / TP, px = tid % TP;
+    // inputs, rounded to BF16; the zero rows
+    {
+        const float2 r = rt[base + tid], k = kt[base + tid];
+        S.r0[tid] = pack_bf16(r.x, r.y);
+        S.k0[tid] = pack_bf16(k.x, k.y);
+        if (tid < 16) S.x1[TPP * 16 + tid] = S.x2[TPP * 16 + tid] = 0u;
+        if (tid == 0) S.r0[TPP] = S.k0[TPP] = 0u;
+        stage_w2(S, W2);
     }
+    const float2 e = et[base + tid];
     __syncthreads();
-    // layer 1: a (from r~) gated by 1 + m (from kappa~)
-    for (int k = 0; k < TPT; ++k) {
-        const int p = tid + 256 * k;
-        float2 a[16], m[16];
-        layer1_point(S, W1, p, a, m);
+    // layer 1: a gated by 1 + m
+    {
+        const Layer1 l1(W1);
 #pragma unroll
-        for (int o = 0; o < 16; ++o) {
-            const float cr = 1.f + m[o].x, ci = m[o].y;
-            S.x1[p][o] = pack_c(a[o].x * cr - a[o].y * ci, a[o].x * ci + a[o].y * cr);
+        for (int q = 0; q < 4; ++q) {
+            const TrainTile T(wave, q);
+            f4 a[2], m[2];
+            l1.at(S, T, a, m);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float cr = 1.f + m[0][r], ci = m[1][r];
+                S.x1[act_at(T.p0 + 4 * kq + r, j)] =
+                    pack_bf16(a[0][r] * cr - a[1][r] * ci, a[0][r] * ci + a[1][r] * cr);
+            }
         }
     }
     __syncthreads();
     // layer 2: 16 -> 16
     {
-        float2 acc[TPT][16];
+        f4 acc[4][2];
+        conv16<false>(S.x1, S.w2, wave, acc);
 #pragma unroll
-        for (int k = 0; k < TPT; ++k)
+        for (int q = 0; q < 4; ++q) {
+            const TrainTile T(wave, q);
 #pragma unroll
-            for (int o = 0; o < 16; ++o) acc[k][o] = make_float2(0.f, 0.f);
-        for (int t = 0; t < 9; ++t) {
-            float2 x[TPT][16];
-#pragma unroll
-            for (int k = 0; k < TPT; ++k) {
-                const int p = tid + 256 * k, py = p / TP + tap_dy(t), px = p % TP + tap_dx(t);
-                const bool in = in_patch(py, px);
-                const int q = in ? py * TP + px : 0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) x[k][i] = in ? unpack_c(S.x1[q][i]) : make_float2(0.f, 0.f);
-            }
-#pragma unroll
-            for (int o = 0; o < 16; ++o)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float2 w = W2[(t * 16 + o) * 16 + i];
-#pragma unroll
-                    for (int k = 0; k < TPT; ++k) cmac(acc[k][o], w, x[k][i]);
-                }
-        }
-#pragma unroll
-        for (int k = 0; k < TPT; ++k) {
-            const int p = tid + 256 * k;
-#pragma unroll
-            for (int o = 0; o < 16; ++o) S.x2[p][o] = pack_c(acc[k][o].x, acc[k][o].y);
+            for (int r = 0; r < 4; ++r)
+                S.x2[act_at(T.p0 + 4 * kq + r, j)] = pack_bf16(acc[q][0][r], acc[q][1][r]);
         }
     }
     __syncthreads();
-    // layer 3: 16 -> 1; d = e~ - N
-    for (int k = 0; k < TPT; ++k) {
-        const int p = tid + 256 * k, py = p / TP, px = p % TP;
-        float2 y = make_float2(0.f, 0.f);
-        for (int t = 0; t < 9; ++t) {
-            const int yy = py + tap_dy(t), xx = px + tap_dx(t);
-            if (!in_patch(yy, xx)) continue;
-            const int q = yy * TP + xx;
+    // layer 3: 16 -> 1 (columns 0 and 1: real and imaginary part); d = e~ - N
+    {
+        f4 acc[4];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) cmac(y, W3[t * 16 + i], unpack_c(S.x2[q][i]));
+        for (int q = 0; q < 4; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 3
+        for (int t = 0; t < 9; ++t) {
+            unsigned w[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const unsigned v = pack_weight(W3[t * 16 + 4 * kq + c]);
+                w[c] = j == 0 ? v ^ NEG_HI : j == 1 ? swap_halves(v) : 0u;
+            }
+            const bf8 b = as_bf8(w[0], w[1], w[2], w[3]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const TrainTile T(wave, q);
+                const bf8 a = act_chunk(S.x2, point_or_zero(T.py + tap_dy(t), T.px + tap_dx(t)), kq);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[q], 0, 0, 0);
+            }
         }
-        const float2 e = et[base + p];
-        S.d[p] = make_float2(e.x - y.x, e.y - y.y);
+        if (j < 2) {
+            float *d = reinterpret_cast<float *>(S.d);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const TrainTile T(wave, q);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) d[2 * (T.p0 + 4 * kq + r) + j] = acc[q][r];
+            }
+        }
     }
+    __syncthreads();
+    S.d[tid] = make_float2(e.x - S.d[tid].x, e.y - S.d[tid].y);
     __syncthreads();
     // z = mask L5 d; loss; patch sums of |e~|^2 and |d|^2 for the growth penalty
     const int lo = border, hi = TP - border;
     const float cnt = (float)((hi - lo) * (hi - lo));
-    float lsum = 0.f, esum = 0.f, dsum = 0.f;
-    for (int k = 0; k < TPT; ++k) {
-        const int p = tid + 256 * k, py = p / TP, px = p % TP;
-        float2 z = make_float2(0.f, 0.f);
-        if (py >= lo && py < hi && px >= lo && px < hi) {
-            float2 c = S.d[p];
-            z.x = 4.f * c.x;
-            z.y = 4.f * c.y;
-            const int nb[4][2] = {{0, -1}, {0, 1}, {-1, 0}, {1, 0}};
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const int yy = py + nb[m][0], xx = px + nb[m][1];
-                if (in_patch(yy, xx)) {
-                    float2 v = S.d[yy * TP + xx];
-                    z.x -= v.x;
-                    z.y -= v.y;
-                }
-            }
-            lsum += z.x * z.x + z.y * z.y;
-            const float2 e = et[base + p];
-            esum += e.x * e.x + e.y * e.y;
-            dsum += c.x * c.x + c.y * c.y;
-        }
-        S.z[p] = z;
-    }
-    __shared__ float red[3][4];
-    __shared__ float tot[3];
+    const bool inner = py >= lo && py < hi && px >= lo && px < hi;
+    const float2 dv = S.d[tid];
+    float v[3] = {0.f, 0.f, 0.f};
     {
-        float v[3] = {lsum, esum, dsum};
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_down(v[q], off, 64);
-            if ((tid & 63) == 0) red[q][tid >> 6] = v[q];
+        float2 z = make_float2(0.f, 0.f);
+        if (inner) {
+            z = lap5(S.d, py, px);
+            v[0] = z.x * z.x + z.y * z.y;
+            v[1] = e.x * e.x + e.y * e.y;
+            v[2] = dv.x * dv.x + dv.y * dv.y;
         }
-        __syncthreads();
-        if (tid < 3) tot[tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
-        __syncthreads();
+        S.z[tid] = z;
     }
+    __shared__ float red[3][16];
+    __shared__ float tot[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_down(v[q], off, 64);
+        if (lane == 0) red[q][wave] = v[q];
+    }
+    __syncthreads();
+    if (tid < 3) {
+        float s = 0.f;
+        for (int w = 0; w < 16; ++w) s += red[tid][w];
+        tot[tid] = s;
+    }
+    // g_N = -(2 / cnt) L5 z - (growth) 2 LOSS_ALPHA mask d / E  (into d)
+    const float2 lz = lap5(S.z, py, px);
+    __syncthreads();
     const float E = tot[1], D = tot[2];
     const bool grow = E > 0.f && D > E;
     if (tid == 0) loss_part[blockIdx.x] = tot[0] / cnt + (grow ? LOSS_ALPHA * (D / E - 1.f) : 0.f);
-    // g_N = -(2 / cnt) L5 z - (growth) 2 LOSS_ALPHA mask d / E  (into d)
-    for (int k = 0; k < TPT; ++k) {
-        const int p = tid + 256 * k, py = p / TP, px = p % TP;
-        float2 c = S.z[p];
-        float2 g = make_float2(4.f * c.x, 4.f * c.y);
-        const int nb[4][2] = {{0, -1}, {0, 1}, {-1, 0}, {1, 0}};
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int yy = py + nb[m][0], xx = px + nb[m][1];
-            if (in_patch(yy, xx)) {
-                float2 v = S.z[yy * TP + xx];
-                g.x -= v.x;
-                g.y -= v.y;
-            }
-        }
+    {
         const float sc = -2.f / cnt;
-        float2 gn = make_float2(sc * g.x, sc * g.y);
-        if (grow && py >= lo && py < hi && px >= lo && px < hi) {
-            const float2 dv = S.d[p];
+        float2 gn = make_float2(sc * lz.x, sc * lz.y);
+        if (grow && inner) {
             const float f = -2.f * LOSS_ALPHA / E;
             gn.x += f * dv.x;
             gn.y += f * dv.y;
         }
-        S.d[p] = gn;
+        S.d[tid] = gn;
+        // three parts of 8 bits (z is dead: every thread has read it)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const unsigned u = pack_bf16(gn.x, gn.y);
+            const float2 part = unpack_c(u);
+            S.gp[k][tid] = u;
+            gn.x -= part.x;
+            gn.y -= part.y;
+        }
     }
     __syncthreads();
     float2 *dW = dW_part + (size_t)blockIdx.x * NET_NW;
-    // dW3[t][i] = sum_p g_N(p) conj(x2_i(p + d_t))
-    if (tid < 144) {
-        const int t = tid / 16, i = tid % 16, dy = tap_dy(t), dx = tap_dx(t);
-        float2 acc = make_float2(0.f, 0.f);
-        for (int py = 0; py < TP; ++py) {
-            const int yy = py + dy;
-            if (yy < 0 || yy >= TP) continue;
-            for (int px = 0; px < TP; ++px) {
-                const int xx = px + dx;
-                if (xx < 0 || xx >= TP) continue;
-                cmac_cx(acc, S.d[py * TP + px], unpack_c(S.x2[yy * TP + xx][i]));
+    // dW3[t][i] = sum_p g_N(p) conj(x2_i(p + d_t)): rows 0..2 the parts of g_N
+    // for the real part, 3..5 for the imaginary part; each wave two patch rows
+    {
+        f4 acc[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+        const unsigned *g = S.gp[j < 3 ? j : j < 6 ? j - 3 : 0];
+#pragma unroll 1
+        for (int s = 0; s < 4; ++s) {
+            const int y = 2 * wave + (s >> 1), x0 = 16 * (s & 1) + kq;
+            unsigned a[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const unsigned u = g[y * TP + x0 + 4 * c];
+                a[c] = j < 3 ? u : j < 6 ? swap_halves(u) ^ NEG_HI : 0u;
+            }
+            const bf8 av = as_bf8(a[0], a[1], a[2], a[3]);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                unsigned b[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    b[c] = S.x2[act_at(point_or_zero(y + tap_dy(t), x0 + 4 * c + tap_dx(t)), j)];
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf8(b[0], b[1], b[2], b[3]), acc[t], 0, 0, 0);
             }
         }
-        dW[NET_W3 + tid] = acc;
+        // lanes 0..15 hold rows 0..3, lanes 16..31 rows 4 and 5
+        float2 part[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            part[t].x = (acc[t][2] + acc[t][1]) + acc[t][0];
+            part[t].y = __shfl_down(acc[t][1] + acc[t][0], 16, 64) + acc[t][3];
+        }
+        __syncthreads();    // gp is dead
+        float2 *sum = S.z;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (wave / TRAIN_SETS == half && lane < 16) {
+                float2 *at = sum + (wave % TRAIN_SETS) * 144 + lane;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    float2 s = part[t];
+                    if (half) {
+                        s.x += at[16 * t].x;
+                        s.y += at[16 * t].y;
+                    }
+                    at[16 * t] = s;
+                }
+            }
+            __syncthreads();
+        }
+        if (tid < 144) {
+            float2 s = make_float2(0.f, 0.f);
+            for (int k = 0; k < TRAIN_SETS; ++k) {
+                s.x += sum[k * 144 + tid].x;
+                s.y += sum[k * 144 + tid].y;
+            }
+            dW[NET_W3 + tid] = s;
+        }
     }
-    __syncthreads();
     // g_x2 = (conj(W3) * g_N, transposed), in place of x2
-    for (int k = 0; k < TPT; ++k) {
-        const int q = tid + 256 * k, qy = q / TP, qx = q % TP;
+    {
         float2 g[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) g[i] = make_float2(0.f, 0.f);
+#pragma unroll 1
         for (int t = 0; t < 9; ++t) {
-            const int py = qy - tap_dy(t), px = qx - tap_dx(t);
-            if (!in_patch(py, px)) continue;
-            const float2 gn = S.d[py * TP + px];
+            const int dy = t / 3 - 1, y = py - dy, x = px - (t - 3 * (dy + 1) - 1);
+            const bool in = in_patch(y, x);
+            float2 gn = S.d[in ? y * TP + x : 0];
+            gn = make_float2(in ? gn.x : 0.f, in ? gn.y : 0.f);
 #pragma unroll
             for (int i = 0; i < 16; ++i) cmac_cw(g[i], W3[t * 16 + i], gn);
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) S.x2[q][i] = pack_c(g[i].x, g[i].y);
+        for (int i = 0; i < 16; ++i) S.x2[act_at(tid, i)] = pack_bf16(g[i].x, g[i].y);
     }
     __syncthreads();
-    // dW2[t][o][i] = sum_p g_x2_o(p) conj(x1_i(p + d_t)); thread = (o, i)
-    {
-        const int o = tid / 16, i = tid % 16;
-        float2 acc[9];
+    // dW2[t][o][i] = sum_p g_x2_o(p) conj(x1_i(p + d_t)): a tap per wave
+    if (wave < 9) {
+        const int dy = wave / 3 - 1, dx = wave - 3 * (dy + 1) - 1;
+        f4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+        for (int y = max(0, -dy); y < TP - max(0, dy); ++y) {
 #pragma unroll
-        for (int t = 0; t < 9; ++t) acc[t] = make_float2(0.f, 0.f);
-        for (int py = 0; py < TP; ++py)
-            for (int px = 0; px < TP; ++px) {
-                const float2 g = unpack_c(S.x2[py * TP + px][o]);
+            for (int h = 0; h < 2; ++h) {
+                unsigned a[4], b[4];
 #pragma unroll
-                for (int t = 0; t < 9; ++t) {
-                    const int yy = py + tap_dy(t), xx = px + tap_dx(t);
-                    if (in_patch(yy, xx)) cmac_cx(acc[t], g, unpack_c(S.x1[yy * TP + xx][i]));
+                for (int c = 0; c < 4; ++c) {
+                    const int x = 16 * h + 4 * c + kq;
+                    a[c] = S.x2[act_at(y * TP + x, j)];
+                    b[c] = S.x1[act_at(point_or_zero(y + dy, x + dx), j)];
                 }
-            }
+                const bf8 bv = as_bf8(b[0], b[1], b[2], b[3]);
+                re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a[0], a[1], a[2], a[3]), bv, re, 0, 0, 0);
 #pragma unroll
-        for (int t = 0; t < 9; ++t) dW[NET_W2 + (t * 16 + o) * 16 + i] = acc[t];
+                for (int c = 0; c < 4; ++c) a[c] = swap_halves(a[c]) ^ NEG_HI;
+                im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a[0], a[1], a[2], a[3]), bv, im, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dW[NET_W2 + (wave * 16 + 4 * kq + r) * 16 + j] = make_float2(re[r], im[r]);
+    } else {
+        for (int k = tid - 9 * 64; k < 9 * 256; k += 7 * 64) S.w2[k] = pack_weight(W2[k]);   // (the sums are dead)
     }
     __syncthreads();
     // g_x1 = (conj(W2) * g_x2, transposed), in place of x1
-    for (int k = 0; k < TPT; ++k) {
-        const int q = tid + 256 * k, qy = q / TP, qx = q % TP;
-        float2 g[16];
+    {
+        f4 acc[4][2];
+        conv16<true>(S.x2, S.w2, wave, acc);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) g[i] = make_float2(0.f, 0.f);
-        for (int t = 0; t < 9; ++t) {
-            const int py = qy - tap_dy(t), px = qx - tap_dx(t);
-            if (!in_patch(py, px)) continue;
-            float2 ga[16];
+        for (int q = 0; q < 4; ++q) {
+            const TrainTile T(wave, q);
 #pragma unroll
-            for (int o = 0; o < 16; ++o) ga[o] = unpack_c(S.x2[py * TP + px][o]);
-#pragma unroll
-            for (int o = 0; o < 16; ++o)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) cmac_cw(g[i], W2[(t * 16 + o) * 16 + i], ga[o]);
+            for (int r = 0; r < 4; ++r)
+                S.x1[act_at(T.p0 + 4 * kq + r, j)] = pack_bf16(acc[q][0][r], acc[q][1][r]);
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) S.x1[q][i] = pack_c(g[i].x, g[i].y);
     }
     __syncthreads();
     // through the gate x1 = a c, c = 1 + m (a, m recomputed from the
     // inputs): g_a = conj(c) g_x1 into x1, g_m = conj(a) g_x1 into x2
-    for (int k = 0; k < TPT; ++k) {
-        const int p = tid + 256 * k;
-        float2 a[16], m[16];
-        layer1_point(S, W1, p, a, m);
+    {
+        const Layer1 l1(W1);
 #pragma unroll
-        for (int o = 0; o < 16; ++o) {
-            const float2 g = unpack_c(S.x1[p][o]);
-            const float2 c = make_float2(1.f + m[o].x, m[o].y);
-            float2 ga = make_float2(0.f, 0.f), gm = make_float2(0.f, 0.f);
-            cmac_cw(ga, c, g);
-            cmac_cw(gm, a[o], g);
-            S.x1[p][o] = pack_c(ga.x, ga.y);
-            S.x2[p][o] = pack_c(gm.x, gm.y);
+        for (int q = 0; q < 4; ++q) {
+            const TrainTile T(wave, q);
+            f4 a[2], m[2];
+            l1.at(S, T, a, m);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int at = act_at(T.p0 + 4 * kq + r, j);
+                const float2 g = unpack_c(S.x1[at]);
+                float2 ga = make_float2(0.f, 0.f), gm = make_float2(0.f, 0.f);
+                cmac_cw(ga, make_float2(1.f + m[0][r], m[1][r]), g);
+                cmac_cw(gm, make_float2(a[0][r], a[1][r]), g);
+                S.x1[at] = pack_bf16(ga.x, ga.y);
+                S.x2[at] = pack_bf16(gm.x, gm.y);
+            }
         }
     }
     __syncthreads();
-    // dW1[t][o][0] = sum_p g_a_o(p) conj(r~(p + d_t)), dW1[t][o][1] likewise
-    // from g_m and kappa~; thread = (o, i) x 4 groups of 8 rows, then a
-    // fixed-order sum of the 4 partials (kept in the d / z buffers)
+    // dW1[t][o][0] = sum_p g_a_o(p) conj(r~(p + d_t)), dW1[t][o][1] likewise from
+    // g_m and kappa~ (columns = taps); each wave two patch rows
     {
-        float2 *part = &S.d[0];   // 2 x 1024 float2, d and z are contiguous
-        const int pr = tid % 32, grp = tid / 32, o = pr / 2, i = pr % 2;
-        if (grp < 4) {
-            float2 acc[9];
+        f4 acc[2][2];
 #pragma unroll
-            for (int t = 0; t < 9; ++t) acc[t] = make_float2(0.f, 0.f);
-            for (int py = grp * 8; py < grp * 8 + 8; ++py)
-                for (int px = 0; px < TP; ++px) {
-                    const float2 g = unpack_c(i == 0 ? S.x1[py * TP + px][o] : S.x2[py * TP + px][o]);
+        for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f4{0.f, 0.f, 0.f, 0.f};
+        const int ty = j / 3;
+#pragma unroll 1
+        for (int s = 0; s < 4; ++s) {
+            const int y = 2 * wave + (s >> 1), x0 = 16 * (s & 1) + kq;
+            int p[4];
 #pragma unroll
-                    for (int t = 0; t < 9; ++t) {
-                        const int yy = py + tap_dy(t), xx = px + tap_dx(t);
-                        if (in_patch(yy, xx)) cmac_cx(acc[t], g, unpack_c(S.x0[yy * TP + xx][i]));
-                    }
-                }
+            for (int c = 0; c < 4; ++c)
+                p[c] = j < 9 ? point_or_zero(y + ty - 1, x0 + 4 * c + j - 3 * ty - 1) : TPP;
 #pragma unroll
-            for (int t = 0; t < 9; ++t) part[(grp * 9 + t) * 32 + pr] = acc[t];
-        }
-        __syncthreads();
-        for (int e = tid; e < 288; e += 256) {
-            const int t = e / 32, pe = e % 32;
-            float2 s = make_float2(0.f, 0.f);
-            for (int gg = 0; gg < 4; ++gg) {
-                float2 v = part[(gg * 9 + t) * 32 + pe];
-                s.x += v.x;
-                s.y += v.y;
+            for (int i = 0; i < 2; ++i) {
+                const unsigned *in = i ? S.k0 : S.r0, *gr = i ? S.x2 : S.x1;
+                unsigned a[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[c] = gr[act_at(y * TP + x0 + 4 * c, j)];
+                const bf8 bv = as_bf8(in[p[0]], in[p[1]], in[p[2]], in[p[3]]);
+                acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a[0], a[1], a[2], a[3]), bv, acc[i][0], 0, 0, 0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[c] = swap_halves(a[c]) ^ NEG_HI;
+                acc[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a[0], a[1], a[2], a[3]), bv, acc[i][1], 0, 0, 0);
             }
-            const int oo = pe / 2, ii = pe % 2;
-            dW[NET_W1 + (t * 16 + oo) * 2 + ii] = s;
+        }
+        float2 *sum = S.d;      // d and what follows it are dead
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (wave / TRAIN_SETS == half && j < 9)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float2 *at = sum + (wave % TRAIN_SETS) * 288 + (j * 16 + 4 * kq + r) * 2 + i;
+                        float2 s = make_float2(acc[i][0][r], acc[i][1][r]);
+                        if (half) {
+                            s.x += at->x;
+                            s.y += at->y;
+                        }
+                        *at = s;
+                    }
+            __syncthreads();
+        }
+        if (tid < 288) {
+            float2 s = make_float2(0.f, 0.f);
+            for (int k = 0; k < TRAIN_SETS; ++k) {
+                s.x += sum[k * 288 + tid].x;
+                s.y += sum[k * 288 + tid].y;
+            }
+            dW[NET_W1 + tid] = s;
         }
     }
 }
 
-// Mean of the per-patch gradients (fixed order) and of the losses.
-__global__ __launch_bounds__(256) void k_reduce_grads(const float2 *__restrict__ dW_part, int count,
-                                                      float2 *__restrict__ grad)
+// Mean of the per-patch gradients and of the losses: 64 weights a block, every
+// 16th patch a wave, then the waves in order.  (One thread a weight over all
+// patches is a chain of dependent loads: 61 us for 256 patches; this form 5 us.)
+__global__ __launch_bounds__(1024) void k_reduce_grads(const float2 *__restrict__ dW_part, int count,
+                                                       float2 *__restrict__ grad)
 {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= NET_NW) return;
+    __shared__ float2 part[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane, kk = min(k, NET_NW - 1);
     float2 s = make_float2(0.f, 0.f);
-    for (int p = 0; p < count; ++p) {
-        float2 v = dW_part[(size_t)p * NET_NW + k];
+#pragma unroll 4
+    for (int p = wave; p < count; p += 16) {
+        const float2 v = dW_part[(size_t)p * NET_NW + kk];
         s.x += v.x;
         s.y += v.y;
     }
-    const float inv = 1.f / (float)count;
-    grad[k] = make_float2(s.x * inv, s.y * inv);
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && k < NET_NW) {
+        for (int w = 1; w < 16; ++w) {
+            s.x += part[w][lane].x;
+            s.y += part[w][lane].y;
+        }
+        const float inv = 1.f / (float)count;
+        grad[k] = make_float2(s.x * inv, s.y * inv);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_reduce_loss(const float *__restrict__ part, int count, float *__restrict__ out)
@@ -479,14 +678,14 @@ void launch_train_patches(const float2 *rt, const float2 *kt, const float2 *et, 
         return true;
     }();
     (void)attr;
-    hipLaunchKernelGGL(k_train_patch, dim3(count), dim3(256), sizeof(TrainLds), s, rt, kt, et, Wq, dW_part,
+    hipLaunchKernelGGL(k_train_patch, dim3(count), dim3(1024), sizeof(TrainLds), s, rt, kt, et, Wq, dW_part,
                        loss_part, border);
 }
 
 void launch_reduce_grads(const float2 *dW_part, int count, float2 *grad, const float *loss_part, float *loss,
                          hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce_grads, dim3((NET_NW + 255) / 256), dim3(256), 0, s, dW_part, count, grad);
+    hipLaunchKernelGGL(k_reduce_grads, dim3((NET_NW + 63) / 64), dim3(1024), 0, s, dW_part, count, grad);
     hipLaunchKernelGGL(k_reduce_loss, dim3(1), dim3(256), 0, s, loss_part, count, loss);
 }
 
@@ -527,7 +726,6 @@ void launch_round_weights(const float2 *Wm, float2 *Wq, hipStream_t s)
 // values on 20 x 20 and the inputs on 22 x 22 (zero outside the grid); the
 // activations live in LDS as BF16 [point][channel].  The weight fragments
 // (prepared on the host by pack_net_mfma) stay in registers.
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 
 constexpr int IT = 16;                       // output tile side
@@ -559,13 +757,6 @@ __device__ __forceinline__ bf8 as_bf8(us8 v) { return __builtin_bit_cast(bf8, v)
 
 // Hardware round-to-nearest-even FP32 -> BF16 (v_cvt_pk_bf16_f32 on gfx950).
 __device__ __forceinline__ unsigned short to_bf16(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
-typedef float fv2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bv2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi)
-{
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(fv2{lo, hi}, bv2));
-}
-
 // Point (y, x) of row-major region of width R for index p.
 struct RegionPos {
     int y, x;
