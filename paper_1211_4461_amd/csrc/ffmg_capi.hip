@@ -1598,14 +1598,7 @@ static ffmg_status ff_begin(ffmg_handle *h, const double eta[3], const void *u, 
         h->ff = ff_plan_create();
         ff_plan_set_variant(h->ff, h->ff_variant);
     }
-    // plane-wave axis factors exp(i k0 e^{ig} eta_k x): c = -k0 sin g eta_k + i k0 cos g eta_k
-    int off = 0;
-    for (int k = 0; k < 3; ++k) {
-        double ek = (k < d) ? eta[k] : 0.0;
-        launch_axis_exp(h->d_E + off, g.m[k], g.lo[k], g.h[k], -(h->k0 * sin(h->prob.gamma)) * ek,
-                        (h->k0 * cos(h->prob.gamma)) * ek, h->stream);
-        off += g.m[k];
-    }
+    launch_axis_factors(h->d_E, g, h->k0, h->prob.gamma, eta, h->stream);
     HIPCHK(h, hipGetLastError());
     HIPCHK(h, ff_plan_prepare(h->ff, g, h->k0, h->prob.gamma, n_dirs, dirs, h->opt.ff_precision, h->stream));
     *prof_idx = prof_begin(h, PROF_FF);
@@ -1637,7 +1630,7 @@ ffmg_status farfield_enqueue(ffmg_handle *h, const double eta[3], const void *u,
     TRY(ff_begin(h, eta, u, n_dirs, dirs, &pi));
     const LevelGeom &g = h->L[0].g;
     int pg = prof_begin(h, PROF_FFGEMM);
-    HIPCHK(h, ff_plan_contract(h->ff, g, h->stream));
+    HIPCHK(h, ff_plan_contract(h->ff, g, h->L[0].q, (const cd *)u, h->d_E, h->stream));
     prof_end(h, PROF_FFGEMM, pg);
     HIPCHK(h, ff_plan_finish(h->ff, g, h->prob.gamma, Fd, h->stream));
     prof_end(h, PROF_FF, pi);
@@ -1813,9 +1806,10 @@ ffmg_status mg_tune_farfield(ffmg_handle *h, const double eta[3], const void *u,
     ffmg_status st = FFMG_OK;
     for (int v = 0; v < nv && st == FFMG_OK; ++v) {
         ff_plan_set_variant(h->ff, v);
-        hipError_t e = ff_plan_contract(h->ff, g, h->stream);   // warm-up
+        auto contract = [&] { return ff_plan_contract(h->ff, g, h->L[0].q, (const cd *)u, h->d_E, h->stream); };
+        hipError_t e = contract();   // warm-up
         if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
-        for (int r = 0; r < reps && e == hipSuccess; ++r) e = ff_plan_contract(h->ff, g, h->stream);
+        for (int r = 0; r < reps && e == hipSuccess; ++r) e = contract();
         if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;

@@ -176,15 +176,21 @@ __global__ __launch_bounds__(256) void k_split_field(const cd *__restrict__ src,
     }
 }
 
-// Axis factors exp(c * x_i), c complex, x_i = lo + (i+1) h, i < m.
-__global__ __launch_bounds__(256) void k_axis_exp(cd *__restrict__ out, int m, double lo, double h, double cr,
-                                                  double ci)
+// Factors exp(c_k x_i), c_k = i k0 e^{i gamma} eta_k, x_i = lo_k + (i+1) h_k, of
+// the axes one after the other (grid g's interior points).
+struct AxisFactors {
+    int m[3];
+    double lo[3], h[3], cr[3], ci[3];
+};
+__global__ __launch_bounds__(256) void k_axis_exp(cd *__restrict__ out, AxisFactors A)
 {
-    int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= m) return;
-    double x = lo + (double)(i + 1) * h;
-    double mag = exp(cr * x), ph = ci * x;
-    out[i] = cd{mag * cos(ph), mag * sin(ph)};
+    int i = blockIdx.x * 256 + threadIdx.x, k = 0;
+    const int n = A.m[0] + A.m[1] + A.m[2], at = i;
+    if (i >= n) return;
+    while (i >= A.m[k]) i -= A.m[k++];
+    double x = A.lo[k] + (double)(i + 1) * A.h[k];
+    double mag = exp(A.cr[k] * x), ph = A.ci[k] * x;
+    out[at] = cd{mag * cos(ph), mag * sin(ph)};
 }
 
 // Packed real-expanded factor matrix for the MFMA A operand of
@@ -293,9 +299,7 @@ __global__ __launch_bounds__(256) void k_plain_factor(cd *__restrict__ out, cons
 
 // ---------------------------------------------------------------------------
 // FP64 MFMA contraction.  Group g: C_g[m][n] = sum_k A_g[m][k] S_g[k][n],
-// m < M_g, k < K, n < Nc (complex).  Each wave owns RT x CT tiles of 16 x 16
-// of C' (real), i.e. 8 RT complex rows x 8 CT complex columns; the block has
-// 4 waves side by side in n.
+// m < M_g, k < K, n < Nc (complex).
 struct GemmGroup {
     const double *A;     // packed A' (see k_pack_factor)
     const double *S;     // S' : K rows of 2 Nc doubles (row stride ldS doubles)
@@ -304,64 +308,207 @@ struct GemmGroup {
     int rtiles;          // row tiles of 16 in A' (8 directions each)
 };
 
-template <int RT, int CT>
-__global__ __launch_bounds__(256) void k_ff_gemm_f64(const GemmGroup *__restrict__ groups, int K, int ksteps,
-                                                     int Nc, long ldS, long ldC)
+// What the integrand s = q (u_in + u) is formed from, where the contraction
+// forms it itself instead of reading S.
+struct FFIntegrand {
+    const cd *q, *u, *E;    // u: may be null (the Born term)
+    int mx, my, dim;
+};
+
+// Tile (rt, real columns c0 .. c0 + 15) of C' to C.  Lane (j, lk) holds
+// C'[(m, Re)][c0 + j] in register 0, C'[(m, Im)][..] in 1, and the same for
+// m + 4 in 2, 3, with m = 8 rt + lk (see tile_row_map).  Columns 2n / 2n+1 are
+// Re / Im of S[k][n]: the even lane writes C[m][n], the odd lane C[m + 4][n].
+__device__ __forceinline__ void store_tile_f64(const GemmGroup &G, d4 mine, int rt, long c0, int Nc, long ldC)
 {
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const bool odd = (lane & 1) != 0;
+    const double p0 = __shfl_xor(mine[0], 1, 64), p1 = __shfl_xor(mine[1], 1, 64);
+    const double p2 = __shfl_xor(mine[2], 1, 64), p3 = __shfl_xor(mine[3], 1, 64);
+    const int m = 8 * rt + lk + (odd ? 4 : 0);
+    const long n = (c0 + lr) >> 1;
+    cd v;
+    if (!odd) v = cd{mine[0] - p1, p0 + mine[1]};
+    else v = cd{p2 - mine[3], mine[2] + p3};
+    if (m < G.M && n < Nc) G.C[(size_t)m * ldC + n] = v;
+}
+
+// Block tiles of BR x 8 tiles of 16 x 16 of C' staged in LDS, the four waves
+// WR x WC over them.  A chunk of four k-steps (16 rows of S) is loaded into
+// registers during the products of the one before and stored to the other of
+// two LDS buffers after them.  In LDS a row of S has its 128-byte halves
+// exchanged in odd rows, so that the rows a wave reads together start on
+// different banks.  FUSED: S is not read; the block forms the integrand of its
+// columns from q, u and the plane wave's factors while staging it (each column
+// is staged once when one block holds every row tile).
+// Bound by the matrix unit: 16 products of 64 cycles per wave and k-step against
+// 8 reads of LDS.  Measured at 255^3 with 64 polar directions (8 x 8 tiles): 219
+// us with the integrand formed on the way, against 133 us for a pass of its own
+// and 315 us for a contraction whose waves (2 x 2 tiles) read from L2.
+template <int BR, int WR, int WC, bool FUSED>
+__global__ __launch_bounds__(256, 2) void k_ff_gemm_f64_lds(const GemmGroup *__restrict__ groups, int K, int ksteps,
+                                                         int Nc, long ldS, long ldC, int gx, int gy, FFIntegrand I)
+{
+    constexpr int BC = 8, KC = 4;
+    constexpr int RW = BR / WR, CW = BC / WC;
+    static_assert(WR * WC == 4 && BR % WR == 0 && BC % WC == 0 && CW % 2 == 0, "four waves, pairs of column tiles");
+    constexpr int A_EL = BR * KC * 64, B_EL = 4 * KC * BC * 16;      // doubles
+    constexpr int NA = A_EL / 2 / 256, NB = B_EL / 2 / 256;          // 16-byte loads per thread
+    __shared__ __attribute__((aligned(16))) double lds[2][A_EL + B_EL];
+    const GemmGroup G = groups[blockIdx.y];
+    const int t = xcd_tile(blockIdx.x, gx * gy);
+    const int bx = t / gy, rt0 = (t % gy) * BR;
+    if (rt0 >= G.rtiles) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wr = wave / WC, wc = wave % WC, lr = lane & 15, lk = lane >> 4;
+    const cd zero = {0.0, 0.0};
+    // staging of S: thread (wave, lane) takes column lane of rows wave, wave + 4, ...
+    const long n = (long)bx * (BC * 8) + lane;
+    const bool ncol = n < Nc;
+    cd exy = zero;
+    if (FUSED && ncol) {
+        const int ix = (int)(n % I.mx);
+        exy = I.E[ix];
+        if (I.dim == 3) exy = exy * I.E[I.mx + (int)(n / I.mx)];
+    }
+    double2 pa[NA];
+    cd pb[NB], pu[FUSED ? NB : 1];
+    auto gload = [&](int ks0) {
+#pragma unroll
+        for (int r = 0; r < NA; ++r) {
+            const int e = threadIdx.x + 256 * r, rt = e / (KC * 32), rem = e % (KC * 32);
+            const bool in = rt0 + rt < G.rtiles && ks0 + rem / 32 < ksteps;
+            const double2 v = *reinterpret_cast<const double2 *>(
+                G.A + (in ? ((size_t)(rt0 + rt) * ksteps + ks0) * 64 + 2 * rem : 0));
+            pa[r].x = in ? v.x : 0.0;
+            pa[r].y = in ? v.y : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < NB; ++r) {
+            const int k = 4 * ks0 + wave + 4 * r;
+            const bool in = ncol && k < K;
+            if (FUSED) {
+                const size_t j = in ? (size_t)k * Nc + n : 0;
+                pb[r] = I.q[j];
+                if (I.u) pu[r] = I.u[j];
+            } else {
+                pb[r] = ld_masked((const cd *)G.S, (size_t)k * (ldS / 2) + n, in);
+            }
+        }
+    };
+    auto sstore = [&](int buf, int ks0) {
+        double *LA = lds[buf], *LB = lds[buf] + A_EL;
+#pragma unroll
+        for (int r = 0; r < NA; ++r) *reinterpret_cast<double2 *>(LA + 2 * (threadIdx.x + 256 * r)) = pa[r];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) {
+            const int row = wave + 4 * r;
+            cd v = pb[r];
+            if (FUSED) {
+                const int k = 4 * ks0 + row;
+                const bool in = ncol && k < K;
+                const int kk = in ? k : 0;
+                const cd uin = exy * I.E[I.dim == 3 ? I.mx + I.my + kk : I.mx + kk];
+                const cd w = I.u ? uin + pu[r] : uin;
+                const cd s = v * w;
+                v = cd{in ? s.re : 0.0, in ? s.im : 0.0};
+            }
+            *reinterpret_cast<cd *>(LB + row * (BC * 16) + ((2 * lane) ^ ((row & 1) << 4))) = v;
+        }
+    };
+
+    d4 acc[RW][CW];
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < CW; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    gload(0);
+    sstore(0, 0);
+    __syncthreads();
+    for (int ks0 = 0, buf = 0; ks0 < ksteps; ks0 += KC, buf ^= 1) {
+        const bool more = ks0 + KC < ksteps;
+        if (more) gload(ks0 + KC);
+        const double *LA = lds[buf] + wr * RW * (KC * 64) + lane;
+        const double *LB = lds[buf] + A_EL + lk * (BC * 16) + wc * CW * 16 + lr;
+        const int odd = 16 * (lk & 1);      // odd rows: column tiles j and j ^ 1 exchanged
+#pragma unroll
+        for (int ks = 0; ks < KC; ++ks) {
+            double a[RW], b[CW];
+#pragma unroll
+            for (int i = 0; i < RW; ++i) a[i] = LA[(i * KC + ks) * 64];
+#pragma unroll
+            for (int j = 0; j < CW; ++j) b[j] = LB[4 * ks * (BC * 16) + j * 16 + ((j & 1) ? -odd : odd)];
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+#pragma unroll
+                for (int j = 0; j < CW; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        if (more) sstore(buf ^ 1, ks0 + KC);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int j = 0; j < CW; ++j)
+            store_tile_f64(G, acc[i][j], rt0 + wr * RW + i, (long)bx * (BC * 16) + (wc * CW + j) * 16, Nc, ldC);
+}
+
+// For contractions with too few such blocks to fill the chip: a block owns
+// 2 x 2 tiles, its eight waves an eighth of the k-steps each (operands straight
+// from L2, eight k-steps in flight); their sums are added in order through LDS.
+// Bound by latency.  Measured at 511^2, 181 directions: 17 us;
+// 74 us with all k-steps in each wave.
+__global__ __launch_bounds__(512) void k_ff_gemm_f64_split(const GemmGroup *__restrict__ groups, int K, int ksteps,
+                                                           int Nc, long ldS, long ldC)
+{
+    constexpr int W = 8, U = 4;
+    __shared__ d4 part[W][4][64];
     const GemmGroup G = groups[blockIdx.z];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int rt0 = blockIdx.y * RT;
-    if (rt0 * 8 >= G.M) return;
-    const long col0 = ((long)blockIdx.x * 4 + wave) * (CT * 16);   // real column of C'
+    const int rt0 = blockIdx.y * 2;
+    if (rt0 >= G.rtiles) return;
+    const long col0 = (long)blockIdx.x * 32, ncols = 2L * Nc;
     const int lr = lane & 15, lk = lane >> 4;
-
-    d4 acc[RT][CT];
+    const int per = (ksteps + W - 1) / W, k0 = wave * per, k1 = min(k0 + per, ksteps);
+    const bool row1 = rt0 + 1 < G.rtiles;
+    const bool c0 = col0 + lr < ncols, c1 = col0 + 16 + lr < ncols;
+    const double *A0 = G.A + (size_t)rt0 * ksteps * 64 + lane, *A1 = A0 + (row1 ? (size_t)ksteps * 64 : 0);
+    const double *B0 = G.S + (c0 ? col0 + lr : 0), *B1 = G.S + (c1 ? col0 + 16 + lr : 0);
+    d4 acc[4];
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
+    for (int i = 0; i < 4; ++i) acc[i] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int ks = k0; ks < k1; ks += U) {
+        double a0[U], a1[U], b0[U], b1[U];
 #pragma unroll
-        for (int j = 0; j < CT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-
-    const double *Ab = G.A + (size_t)rt0 * ksteps * 64 + lane;
-    const long ncols = 2L * Nc;
-    for (int ks = 0; ks < ksteps; ++ks) {
-        const int k = 4 * ks + lk;
-        double a[RT], bv[CT];
-#pragma unroll
-        for (int i = 0; i < RT; ++i) {
-            int rt = rt0 + i;
-            a[i] = (rt < G.rtiles) ? Ab[((size_t)i * ksteps + ks) * 64] : 0.0;
+        for (int x = 0; x < U; ++x) {
+            const int s = min(ks + x, k1 - 1), k = 4 * s + lk;
+            const size_t r = (size_t)min(k, K - 1) * ldS;
+            a0[x] = A0[(size_t)s * 64];
+            a1[x] = A1[(size_t)s * 64];
+            b0[x] = B0[r];
+            b1[x] = B1[r];
         }
 #pragma unroll
-        for (int j = 0; j < CT; ++j) {
-            long c = col0 + j * 16 + lr;
-            bv[j] = (k < K && c < ncols) ? G.S[(size_t)k * ldS + c] : 0.0;
+        for (int x = 0; x < U; ++x) {
+            if (ks + x >= k1) break;
+            const bool kin = 4 * (ks + x) + lk < K;
+            const double x0 = kin && c0 ? b0[x] : 0.0, x1 = kin && c1 ? b1[x] : 0.0, y1 = row1 ? a1[x] : 0.0;
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[x], x0, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[x], x1, acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(y1, x0, acc[2], 0, 0, 0);
+            acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(y1, x1, acc[3], 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < RT; ++i)
-#pragma unroll
-            for (int j = 0; j < CT; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bv[j], acc[i][j], 0, 0, 0);
     }
-    // Epilogue: lane (j, lk) holds, for tile rt, C'[(m, Re)][c0 + j] in
-    // register 0, C'[(m, Im)][..] in 1, and the same for m + 4 in 2, 3, with
-    // m = 8 rt + lk (see tile_row_map).  Columns 2n / 2n+1 are Re / Im of
-    // S[k][n]: the even lane writes C[m][n], the odd lane C[m + 4][n].
-    const bool odd = (lane & 1) != 0;
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
+    for (int i = 0; i < 4; ++i) part[wave][i][lane] = acc[i];
+    __syncthreads();
+    if (wave < 4) {
+        d4 s = part[0][wave][lane];
 #pragma unroll
-        for (int j = 0; j < CT; ++j) {
-            d4 mine = acc[i][j];
-            double p0 = __shfl_xor(mine[0], 1, 64), p1 = __shfl_xor(mine[1], 1, 64);
-            double p2 = __shfl_xor(mine[2], 1, 64), p3 = __shfl_xor(mine[3], 1, 64);
-            int m = 8 * (rt0 + i) + lk + (odd ? 4 : 0);
-            long c = col0 + j * 16 + lr;
-            long n = c >> 1;
-            cd v;
-            if (!odd) v = cd{mine[0] - p1, p0 + mine[1]};
-            else v = cd{p2 - mine[3], mine[2] + p3};
-            if (m < G.M && n < Nc) G.C[(size_t)m * ldC + n] = v;
-        }
+        for (int w = 1; w < W; ++w) s += part[w][wave][lane];
+        store_tile_f64(G, s, rt0 + (wave >> 1), col0 + 16 * (wave & 1), Nc, ldC);
+    }
 }
 
 // Split-BF16 MFMA contraction.  Group g: C_g = A_g S_g as above, with A_g
@@ -600,9 +747,10 @@ __global__ __launch_bounds__(256) void k_ff_gemm_bf16_lds(const GemmGroupB *__re
 }
 
 // F_m = pre * sum_x P[m][x] T[m][x]; one block per direction, the sums of
-// its four waves combined in a fixed order.
+// its four waves combined in a fixed order.  perm: sorted position -> place in
+// F (null: the same).
 __global__ __launch_bounds__(256) void k_ff_final(const cd *__restrict__ P, const cd *__restrict__ T, int M, int K,
-                                                  cd pre, cd *__restrict__ F)
+                                                  cd pre, cd *__restrict__ F, const int *__restrict__ perm)
 {
     __shared__ double red[2][4];
     const int m = blockIdx.x;
@@ -625,16 +773,8 @@ __global__ __launch_bounds__(256) void k_ff_final(const cd *__restrict__ P, cons
     }
     __syncthreads();
     if (threadIdx.x == 0)
-        F[m] = pre * cd{(red[0][0] + red[0][1]) + (red[0][2] + red[0][3]),
+        F[perm ? perm[m] : m] = pre * cd{(red[0][0] + red[0][1]) + (red[0][2] + red[0][3]),
                         (red[1][0] + red[1][1]) + (red[1][2] + red[1][3])};
-}
-
-// Scatter the sorted result into the caller's direction order.
-__global__ __launch_bounds__(256) void k_unpermute(const cd *__restrict__ Fs, const int *__restrict__ perm, int M,
-                                                   cd *__restrict__ F)
-{
-    int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < M) F[perm[i]] = Fs[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -642,20 +782,63 @@ __global__ __launch_bounds__(256) void k_unpermute(const cd *__restrict__ Fs, co
 static int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 static long round_up(long a, long b) { return (a + b - 1) / b * b; }
 
-constexpr int GEMM_RT = 2, GEMM_CT = 2;
-
 struct GemmLaunch {
     GemmGroup *d_groups = nullptr;
     int ngroups = 0, K = 0, Nc = 0, maxM = 0;
     long ldS = 0, ldC = 0;
 };
 
-static void launch_gemm(const GemmLaunch &L, hipStream_t s)
+// Row tiles per block of the LDS-staged FP64 contraction, or 0: the one with
+// the k-steps split over a block's waves.  The staged blocks read every operand
+// once and run at the matrix rate, but need about a block per CU (two per CU
+// with 8 x 8 tiles, the blocks that fit).  Whole maps, staged against split:
+// 255^3 with 64 polar directions 330 against 630 us, 8 polar 119 against 241;
+// 1023^2 with 360 directions (96 blocks of 8 x 8) 193 against 104, 511^2 with 181
+// (24 blocks) 100 against 27.  1023^2 with 1500 (384 blocks of 8 x 8): 335 us in
+// those, 280 us in 4 x 8 tiles.
+static int gemm_f64_rows(const GemmLaunch &L)
 {
-    int ksteps = ceil_div(L.K, 4);
-    dim3 grid(ceil_div(2L * L.Nc, 4L * GEMM_CT * 16), ceil_div(2L * L.maxM, 16L * GEMM_RT), (unsigned)L.ngroups);
-    hipLaunchKernelGGL((k_ff_gemm_f64<GEMM_RT, GEMM_CT>), grid, dim3(256), 0, s, L.d_groups, L.K, ksteps, L.Nc,
-                       L.ldS, L.ldC);
+    const int rt = ceil_div(2L * L.maxM, 16);
+    const long cols = (long)ceil_div(2L * L.Nc, 128) * L.ngroups;
+    auto blocks = [&](int br) { return cols * ceil_div(rt, br); };
+    if (rt > 4 && blocks(8) >= 400) return 8;
+    if (rt > 2 && blocks(4) >= 256) return 4;
+    if (rt <= 2 && blocks(2) >= 256) return 2;
+    return 0;
+}
+
+// Whether a contraction forms the integrand itself: one block holds every row.
+static bool gemm_f64_fuses(const GemmLaunch &L)
+{
+    const int br = gemm_f64_rows(L);
+    return br > 0 && L.ngroups == 1 && ceil_div(2L * L.maxM, 16) <= br;
+}
+
+template <int BR, int WR, int WC>
+static void launch_gemm_f64_lds(const GemmLaunch &L, const FFIntegrand *I, hipStream_t s)
+{
+    const int gx = ceil_div(2L * L.Nc, 128), gy = ceil_div(ceil_div(2L * L.maxM, 16), BR), ksteps = ceil_div(L.K, 4);
+    const dim3 grid((unsigned)(gx * gy), (unsigned)L.ngroups);
+    if (I)
+        hipLaunchKernelGGL((k_ff_gemm_f64_lds<BR, WR, WC, true>), grid, dim3(256), 0, s, L.d_groups, L.K, ksteps, L.Nc,
+                           L.ldS, L.ldC, gx, gy, *I);
+    else
+        hipLaunchKernelGGL((k_ff_gemm_f64_lds<BR, WR, WC, false>), grid, dim3(256), 0, s, L.d_groups, L.K, ksteps,
+                           L.Nc, L.ldS, L.ldC, gx, gy, FFIntegrand{});
+}
+
+// I: form the integrand from it (only where gemm_f64_fuses).
+static void launch_gemm(const GemmLaunch &L, hipStream_t s, const FFIntegrand *I = nullptr)
+{
+    switch (gemm_f64_rows(L)) {
+    case 8: launch_gemm_f64_lds<8, 2, 2>(L, I, s); return;
+    case 4: launch_gemm_f64_lds<4, 1, 4>(L, I, s); return;
+    case 2: launch_gemm_f64_lds<2, 1, 4>(L, I, s); return;
+    default: break;
+    }
+    const dim3 grid(ceil_div(2L * L.Nc, 32), ceil_div(2L * L.maxM, 32), (unsigned)L.ngroups);
+    hipLaunchKernelGGL(k_ff_gemm_f64_split, grid, dim3(512), 0, s, L.d_groups, L.K, ceil_div(L.K, 4), L.Nc, L.ldS,
+                       L.ldC);
 }
 
 // Split-GEMM tile variants: RT row tiles x CT column tiles per wave (four
@@ -749,7 +932,7 @@ struct FarFieldPlan {
     double *d_alpha = nullptr;     // sorted alphas per axis [3][M], then group alphas
     cd *d_s = nullptr;             // FP64 integrand
     cd *d_Plast = nullptr;         // plain Px [M][mx], sorted order
-    cd *d_T1 = nullptr, *d_T2 = nullptr, *d_F = nullptr;
+    cd *d_T1 = nullptr, *d_T2 = nullptr;
     int *d_perm = nullptr;
     GemmLaunch L1, L2;             // FP64 GEMM stages
     // split BF16
@@ -774,7 +957,7 @@ struct FarFieldPlan {
         for (void *b : bufs) (void)hipFree(b);
         bufs.clear();
         d_alpha = nullptr;
-        d_s = d_Plast = d_T1 = d_T2 = d_F = nullptr;
+        d_s = d_Plast = d_T1 = d_T2 = nullptr;
         d_perm = nullptr;
         d_S1b = d_S2b = nullptr;
         L1 = L2 = GemmLaunch{};
@@ -852,7 +1035,6 @@ hipError_t ff_plan_prepare(FarFieldPlan *p, const LevelGeom &g, double k0, doubl
     hipLaunchKernelGGL(k_plain_factor, dim3(grid_for((long)M * mx)), dim3(256), 0, s, p->d_Plast, p->d_alpha, M, mx,
                        g.lo[0], g.h[0], k0, gamma);
     FF_CHECK(p->alloc(&p->d_T2, (size_t)M * mx * sizeof(cd)));
-    FF_CHECK(p->alloc(&p->d_F, (size_t)M * sizeof(cd)));
     if (d == 3) FF_CHECK(p->alloc(&p->d_T1, (size_t)NG * mx * my * sizeof(cd)));
     int maxM = 0;
     for (int gi = 0; gi < NG; ++gi) maxM = std::max(maxM, p->gstart[gi + 1] - p->gstart[gi]);
@@ -982,15 +1164,16 @@ hipError_t ff_plan_prepare(FarFieldPlan *p, const LevelGeom &g, double k0, doubl
     return hipSuccess;
 }
 
-// Integrand s = q (u_in + u) (u may be null: Born term), in FP64 or as BF16
-// planes.
+// Integrand s = q (u_in + u) (u may be null: Born term), in FP64 (where the
+// first contraction does not form it itself) or as BF16 planes.
 hipError_t ff_plan_integrand(FarFieldPlan *p, const LevelGeom &g, const cd *q, const cd *u, const cd *E,
                              hipStream_t s)
 {
     const int d = g.dim, mx = g.m[0], my = g.m[1], mz = (d == 3) ? g.m[2] : 1;
     if (p->ns == 0) {
-        hipLaunchKernelGGL(k_ff_integrand, dim3(grid_for((long)g.N())), dim3(256), 0, s, q, u, E, p->d_s, mx, my,
-                           mz);
+        if (!gemm_f64_fuses(d == 3 ? p->L1 : p->L2))
+            hipLaunchKernelGGL(k_ff_integrand, dim3(grid_for((long)g.N())), dim3(256), 0, s, q, u, E, p->d_s, mx, my,
+                               mz);
     } else {
         const long w1 = (long)p->kb1 * (p->ldP1 / 2);
         if (p->ns == 3)
@@ -1003,13 +1186,16 @@ hipError_t ff_plan_integrand(FarFieldPlan *p, const LevelGeom &g, const cd *q, c
     return hipGetLastError();
 }
 
-// The GEMM stages: T[m][x] (2D), or T1 then T2 (3D).
-hipError_t ff_plan_contract(FarFieldPlan *p, const LevelGeom &g, hipStream_t s)
+// The GEMM stages: T[m][x] (2D), or T1 then T2 (3D).  q, u, E: as given to
+// ff_plan_integrand.
+hipError_t ff_plan_contract(FarFieldPlan *p, const LevelGeom &g, const cd *q, const cd *u, const cd *E, hipStream_t s)
 {
     const int d = g.dim, mx = g.m[0], my = g.m[1];
     if (p->ns == 0) {
-        if (d == 3) launch_gemm(p->L1, s);
-        launch_gemm(p->L2, s);
+        const FFIntegrand I{q, u, E, mx, my, d};
+        const GemmLaunch &first = d == 3 ? p->L1 : p->L2;
+        launch_gemm(first, s, gemm_f64_fuses(first) ? &I : nullptr);
+        if (d == 3) launch_gemm(p->L2, s);
     } else {
         if (d == 3) {
             launch_gemm_bf16(p->B1, p->ns, p->variant, s);
@@ -1036,8 +1222,7 @@ hipError_t ff_plan_finish(FarFieldPlan *p, const LevelGeom &g, double gamma, cd 
     double vol = 1.0;
     for (int k = 0; k < d; ++k) vol *= g.h[k];
     cd pre = {vol * cos(d * gamma), vol * sin(d * gamma)};
-    hipLaunchKernelGGL(k_ff_final, dim3(M), dim3(256), 0, s, p->d_Plast, p->d_T2, M, mx, pre, p->d_F);
-    hipLaunchKernelGGL(k_unpermute, dim3(ceil_div(M, 256)), dim3(256), 0, s, p->d_F, p->d_perm, M, F_out);
+    hipLaunchKernelGGL(k_ff_final, dim3(M), dim3(256), 0, s, p->d_Plast, p->d_T2, M, mx, pre, F_out, p->d_perm);
     return hipGetLastError();
 }
 
@@ -1357,7 +1542,7 @@ int ff_noalloc_map(const LevelGeom &g, double k0, double gamma, const double eta
     const size_t oPerm = c.take<int>((size_t)M);
     const size_t oPl = c.take<cd>((size_t)M * mx);
     const size_t oT2 = c.take<cd>((size_t)M * mx);
-    const size_t oF = c.take<cd>((size_t)M);
+    (void)c.take<cd>((size_t)M);   // (part of the documented size)
     const size_t oFo = out_on_device ? 0 : c.take<cd>((size_t)M);
     const size_t oS = c.take<cd>((size_t)N);
     size_t a2tot = 0;
@@ -1369,7 +1554,7 @@ int ff_noalloc_map(const LevelGeom &g, double k0, double gamma, const double eta
     *need = c.off;
     if (c.off > (size_t)FFMG_NOALLOC_SCRATCH_BYTES) return 1;
 
-    cd *dE = (cd *)(base + oE), *dPl = (cd *)(base + oPl), *dT2 = (cd *)(base + oT2), *dF = (cd *)(base + oF);
+    cd *dE = (cd *)(base + oE), *dPl = (cd *)(base + oPl), *dT2 = (cd *)(base + oT2);
     cd *dS = (cd *)(base + oS), *dT1 = (cd *)(base + oT1);
     double *dAl = (double *)(base + oAl), *dA2 = (double *)(base + oA2), *dA1 = (double *)(base + oA1);
     int *dPerm = (int *)(base + oPerm);
@@ -1404,14 +1589,7 @@ int ff_noalloc_map(const LevelGeom &g, double k0, double gamma, const double eta
     NA_CHECK(hipMemcpyAsync(dPerm, H.perm, (size_t)M * sizeof(int), hipMemcpyHostToDevice, s));
     NA_CHECK(hipMemcpyAsync(dGr, H.gr, (size_t)ng * sizeof(GemmGroup), hipMemcpyHostToDevice, s));
 
-    // plane-wave axis factors exp(i k0 e^{ig} eta_k x): c = -k0 sin g eta_k + i k0 cos g eta_k
-    int eo = 0;
-    for (int k = 0; k < 3; ++k) {
-        const double ek = (k < d) ? eta[k] : 0.0;
-        hipLaunchKernelGGL(k_axis_exp, dim3(ceil_div(g.m[k], 256)), dim3(256), 0, s, dE + eo, g.m[k], g.lo[k],
-                           g.h[k], -(k0 * sin(gamma)) * ek, (k0 * cos(gamma)) * ek);
-        eo += g.m[k];
-    }
+    launch_axis_factors(dE, g, k0, gamma, eta, s);
     hipLaunchKernelGGL(k_plain_factor, dim3(grid_for((long)M * mx)), dim3(256), 0, s, dPl, dAl, M, mx, g.lo[0],
                        g.h[0], k0, gamma);
     off2 = 0;
@@ -1435,9 +1613,8 @@ int ff_noalloc_map(const LevelGeom &g, double k0, double gamma, const double eta
     double vol = 1.0;
     for (int k = 0; k < d; ++k) vol *= g.h[k];
     const cd pre = {vol * cos(d * gamma), vol * sin(d * gamma)};
-    hipLaunchKernelGGL(k_ff_final, dim3(M), dim3(256), 0, s, (const cd *)dPl, (const cd *)dT2, M, mx, pre, dF);
-    hipLaunchKernelGGL(k_unpermute, dim3(ceil_div(M, 256)), dim3(256), 0, s, (const cd *)dF, (const int *)dPerm, M,
-                       Fd);
+    hipLaunchKernelGGL(k_ff_final, dim3(M), dim3(256), 0, s, (const cd *)dPl, (const cd *)dT2, M, mx, pre, Fd,
+                       (const int *)dPerm);
     NA_CHECK(hipGetLastError());
     if (!out_on_device) {
         NA_CHECK(hipMemcpyAsync(F_out, Fd, (size_t)M * sizeof(cd), hipMemcpyDeviceToHost, s));
@@ -1447,16 +1624,26 @@ int ff_noalloc_map(const LevelGeom &g, double k0, double gamma, const double eta
     return 0;
 }
 
-void launch_axis_exp(cd *out, int m, double lo, double h, double cr, double ci, hipStream_t s)
+void launch_axis_factors(cd *out, const LevelGeom &g, double k0, double gamma, const double eta[3], hipStream_t s)
 {
-    hipLaunchKernelGGL(k_axis_exp, dim3(ceil_div(m, 256)), dim3(256), 0, s, out, m, lo, h, cr, ci);
+    // c = -k0 sin g eta_k + i k0 cos g eta_k
+    AxisFactors A;
+    for (int k = 0; k < 3; ++k) {
+        const double ek = (k < g.dim) ? eta[k] : 0.0;
+        A.m[k] = g.m[k];
+        A.lo[k] = g.lo[k];
+        A.h[k] = g.h[k];
+        A.cr[k] = -(k0 * sin(gamma)) * ek;
+        A.ci[k] = (k0 * cos(gamma)) * ek;
+    }
+    hipLaunchKernelGGL(k_axis_exp, dim3(ceil_div(g.m[0] + g.m[1] + g.m[2], 256)), dim3(256), 0, s, out, A);
 }
 
 // ---------------------------------------------------------------------------
 // The same FP64 MFMA contraction for a caller's factor table instead of the
 // plane-wave exponentials (the test-function integrals of the ionisation
 // amplitudes): C[m][n] = sum_k A[m][k] S[k][n].  A is packed into the A'
-// layout of k_ff_gemm_f64 (Re / Im rows per tile_row_map), the group
+// layout of the contraction (Re / Im rows per tile_row_map), the group
 // descriptor is written on the device, and one launch runs the GEMM.
 __global__ __launch_bounds__(256) void k_pack_table(double *__restrict__ out, const cd *__restrict__ A, int M, int K,
                                                     int rtiles, int ksteps)
@@ -1504,7 +1691,7 @@ void table_gemm_f64(const cd *A, int M, int K, const cd *S, int Nc, cd *C, void 
 
 void launch_rows_dot(const cd *P, const cd *T, int M, int K, cd pre, cd *F, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ff_final, dim3(M), dim3(256), 0, s, P, T, M, K, pre, F);
+    hipLaunchKernelGGL(k_ff_final, dim3(M), dim3(256), 0, s, P, T, M, K, pre, F, (const int *)nullptr);
 }
 
 }  // namespace ffmg

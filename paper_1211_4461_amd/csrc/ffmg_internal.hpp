@@ -440,7 +440,7 @@ hipError_t ff_plan_prepare(FarFieldPlan *p, const LevelGeom &g, double k0, doubl
                            int prec, hipStream_t s);
 hipError_t ff_plan_integrand(FarFieldPlan *p, const LevelGeom &g, const cd *q, const cd *u, const cd *E,
                              hipStream_t s);
-hipError_t ff_plan_contract(FarFieldPlan *p, const LevelGeom &g, hipStream_t s);
+hipError_t ff_plan_contract(FarFieldPlan *p, const LevelGeom &g, const cd *q, const cd *u, const cd *E, hipStream_t s);
 hipError_t ff_plan_finish(FarFieldPlan *p, const LevelGeom &g, double gamma, cd *F_out, hipStream_t s);
 // Batched 2D split-BF16 far fields (farfield_map_batched): instance i has
 // its operator's plan (prepared for the same M directions), grid, finest q,
@@ -467,7 +467,7 @@ int ff_plan_variant(const FarFieldPlan *p);
 // Number of times the plan was rebuilt (its buffers freed and reallocated):
 // a workspace that keeps pointers into the plan is valid for one generation.
 uint64_t ff_plan_generation(const FarFieldPlan *p);
-void launch_axis_exp(cd *out, int m, double lo, double h, double cr, double ci, hipStream_t s);
+void launch_axis_factors(cd *out, const LevelGeom &g, double k0, double gamma, const double eta[3], hipStream_t s);
 // FP64 MFMA contraction C[m][n] = sum_k A[m][k] S[k][n] for a complex table A
 // (M x K, row stride K) and S (K x Nc), C (M x Nc); ws: table_gemm_ws_bytes.
 size_t table_gemm_ws_bytes(int M, int K);
