@@ -514,7 +514,7 @@ __global__ __launch_bounds__(512) void k_ff_gemm_f64_split(const GemmGroup *__re
 // Split-BF16 MFMA contraction.  Group g: C_g = A_g S_g as above, with A_g
 // and S_g given as NS BF16 planes (padded: rtiles rows of tiles, K to a
 // multiple of 32, ldP real columns, all zero-filled, so the inner loop has no
-// bounds checks).  Each wave owns RT x CT tiles of 16 x 16 of C' (8 RT
+// bounds checks; rtiles counts the tiles that hold rows).  Each wave owns RT x CT tiles of 16 x 16 of C' (8 RT
 // directions x 8 CT complex columns); the block has 4 waves side by side in n.
 // The flat block index is mapped XCD-contiguously onto (column slab, row
 // block) with row blocks fastest, so the blocks that share one slab of the
@@ -852,15 +852,34 @@ struct BfVariant {
 static const BfVariant BF_VARIANTS[] = {{2, 1, false}, {2, 2, false}, {4, 1, false}, {4, 2, false}, {2, 4, false},
                                         {4, 4, false}, {8, 4, true},  {4, 8, true},  {8, 8, true}};
 constexpr int BF_NVARIANTS = (int)(sizeof(BF_VARIANTS) / sizeof(BF_VARIANTS[0]));
-constexpr int BF_DEFAULT_VARIANT = 3;
+constexpr int BF_DEFAULT_VARIANT = 3;     // the one mg_tune_get names while none is set
+constexpr int BF_AUTO_VARIANT = -1;       // chosen per launch by bf_variant_for
 constexpr int BF_RT_PAD = 8;
 constexpr long BF_COL_PAD = 4 * 4 * 16;   // 4 waves x CT <= 4 tiles x 16 columns (LDS blocks: <= 8 x 16)
 
 struct GemmLaunchB {
     GemmGroupB *d_groups = nullptr;
-    int ngroups = 0, ksteps = 0, rtiles = 0;   // rtiles: the largest group's (padded)
+    int ngroups = 0, ksteps = 0, rtiles = 0;   // rtiles: the largest group's
     long ldP = 0;
 };
+
+// The variant for a contraction nothing was tuned for, by its tiles of 16 x 16:
+// the smallest wave tiles while they do not fill the chip (latency), then larger
+// ones, then, with three parts and enough rows, the blocks staged in LDS (with
+// two parts they move too little per product to pay).  All compute the same
+// bits.  Measured (3 parts, us; 2 x 1, 2 x 2, 4 x 2 per wave, 4 x 4, 8 x 4 in
+// LDS): 1023^2 with 97 directions (1700 tiles) 18, 25, 42, 47, 41; 2047^2 with
+// 360 (11500) 130, 106, 150, 106, 114; 511^3 with 64 x 128 (both stages; 260000
+// and 65000) 1328, 957, 1098, 807, 754.
+static int bf_variant_for(const GemmLaunchB &L, int ns)
+{
+    const long tiles = (long)L.rtiles * (L.ldP / 16) * L.ngroups;
+    if (tiles < 8000) return 0;
+    if (tiles < 24000) return 1;
+    if (L.rtiles <= 2) return 4;
+    if (ns != 3) return 5;
+    return L.rtiles <= 4 ? 7 : 6;
+}
 
 // An LDS-staged variant: its two operand buffers (the attribute is raised
 // once per instantiation, by a thread-safe static initialisation).
@@ -911,6 +930,7 @@ static void launch_gemm_bf16_ns(const GemmLaunchB &L, int variant, hipStream_t s
 
 static void launch_gemm_bf16(const GemmLaunchB &L, int ns, int variant, hipStream_t s)
 {
+    if (variant == BF_AUTO_VARIANT) variant = bf_variant_for(L, ns);
     if (ns == 3) launch_gemm_bf16_ns<3>(L, variant, s);
     else launch_gemm_bf16_ns<2>(L, variant, s);
 }
@@ -922,7 +942,7 @@ struct FarFieldPlan {
     int M = 0;
     int prec = -1;                 // ffmg_ff_precision of the built factors
     int ns = 0;                    // BF16 parts (split precisions)
-    int variant = BF_DEFAULT_VARIANT;
+    int variant = BF_AUTO_VARIANT;
     uint64_t gen = 0;              // rebuilds so far (every rebuild frees and reallocates the buffers below)
     std::vector<double> dirs;      // cache key
     std::vector<int> perm;         // sorted position -> direction index
@@ -973,7 +993,7 @@ FarFieldPlan *ff_plan_create() { return new FarFieldPlan(); }
 void ff_plan_destroy(FarFieldPlan *p) { delete p; }
 int ff_plan_variants() { return BF_NVARIANTS; }
 int ff_plan_default_variant() { return BF_DEFAULT_VARIANT; }
-void ff_plan_set_variant(FarFieldPlan *p, int v) { p->variant = (v >= 0 && v < BF_NVARIANTS) ? v : BF_DEFAULT_VARIANT; }
+void ff_plan_set_variant(FarFieldPlan *p, int v) { p->variant = (v >= 0 && v < BF_NVARIANTS) ? v : BF_AUTO_VARIANT; }
 int ff_plan_variant(const FarFieldPlan *p) { return p->variant; }
 uint64_t ff_plan_generation(const FarFieldPlan *p) { return p->gen; }
 
@@ -1101,8 +1121,8 @@ hipError_t ff_plan_prepare(FarFieldPlan *p, const LevelGeom &g, double k0, doubl
         int maxrt = 0;
         for (int gi = 0; gi < NG; ++gi) {
             int Mg = p->gstart[gi + 1] - p->gstart[gi];
-            rts[gi] = (int)round_up(ceil_div(2L * Mg, 16), BF_RT_PAD);
-            maxrt = std::max(maxrt, rts[gi]);
+            rts[gi] = (int)round_up(ceil_div(2L * Mg, 16), BF_RT_PAD);   // stored (zero rows behind the last)
+            maxrt = std::max(maxrt, ceil_div(2L * Mg, 16));
             off[gi] = tot;
             tot += (size_t)rts[gi] * ks_y * 64;
         }
@@ -1133,7 +1153,7 @@ hipError_t ff_plan_prepare(FarFieldPlan *p, const LevelGeom &g, double k0, doubl
                 hipLaunchKernelGGL(k_pack_factor_bf16<2>, dim3(grid_for(n1)), dim3(256), 0, s, A1, n1,
                                    p->d_alpha + (size_t)3 * M, NG, mz, rt1, ks1, g.lo[2], g.h[2], k0, gamma);
             gr.push_back(GemmGroupB{(const bf8 *)A1, n1, (const bf8 *)p->d_S1b, p->ps1, p->d_T1, (long)mx * my, NG,
-                                    (int)Nc1, rt1});
+                                    (int)Nc1, ceil_div(2L * NG, 16)});
             // stage-1 result planes for stage 2 (one set per group)
             p->kb2 = 4 * ks_y;
             p->ldP2 = round_up(2L * mx, BF_COL_PAD);
@@ -1146,13 +1166,13 @@ hipError_t ff_plan_prepare(FarFieldPlan *p, const LevelGeom &g, double k0, doubl
             const us8 *S = (d == 3) ? p->d_S2b + (size_t)gi * p->gs2 : p->d_S1b;
             long ps = (d == 3) ? p->ps2 : p->ps1;
             gr.push_back(GemmGroupB{(const bf8 *)(A2 + off[gi]), (long)tot, (const bf8 *)S, ps,
-                                    p->d_T2 + (size_t)p->gstart[gi] * mx, (long)mx, Mg, mx, rts[gi]});
+                                    p->d_T2 + (size_t)p->gstart[gi] * mx, (long)mx, Mg, mx, ceil_div(2L * Mg, 16)});
         }
         GemmGroupB *dg = nullptr;
         FF_CHECK(upload(p, &dg, gr));
         if (d == 2) p->h_B2g = gr[0];
         if (d == 3) {
-            p->B1 = GemmLaunchB{dg, 1, ks1, (int)round_up(ceil_div(2L * NG, 16), BF_RT_PAD), p->ldP1};
+            p->B1 = GemmLaunchB{dg, 1, ks1, ceil_div(2L * NG, 16), p->ldP1};
             p->B2 = GemmLaunchB{dg + 1, NG, ks_y, maxrt, p->ldP2};
         } else {
             p->B2 = GemmLaunchB{dg, 1, ks_y, maxrt, p->ldP1};
