@@ -32,12 +32,17 @@
 // path reads and writes them in global memory).
 #include "ffmg_internal.hpp"
 #include "ffmg_point.hpp"
+#include "ffmg_wave.hpp"
 
 namespace ffmg {
 
 namespace {
 
-constexpr int GM_BLOCKS = 1024;   // grid-stride blocks (and partial sums per value)
+// Grid-stride blocks (and partial sums per value) and their threads.  Every
+// block of a pass adds up all blocks' partial sums of the pass before, so few
+// large blocks: with 1024 of 256 threads a pass read 57 MB of partial sums
+// (511 x 511, FP32, m = 3: the four passes that do, 33 us then, 25 us now).
+constexpr int GM_BLOCKS = 512, GM_BT = 512;
 // partial-sum slots: n_i at slot i (i <= m), d_ij (re, im) at NSLOT_D + 2 (j GMRES_MAX_M + i)
 constexpr int NSLOT_D = GMRES_MAX_M + 1;
 
@@ -72,123 +77,165 @@ __device__ __forceinline__ cx<T> apply_at(const Stencil<T> &P, const cx<T> *__re
     return apply_at_f<T, DIM>(P, [&](size_t k) { return z[k]; }, z[j], qj, j);
 }
 
-// Sums of NV doubles per thread of a 256-thread block into
-// parts[slot[v] * GM_BLOCKS + blockIdx.x] (wave shuffles, then the four
-// waves in order).
+// Sums of NV doubles per thread of a block into parts[slot[v] * GM_BLOCKS +
+// blockIdx.x] (by halving, within each wave and over the waves).
 template <int NV>
-__device__ __forceinline__ void block_partials(double (&acc)[NV], const int (&slot)[NV], double *__restrict__ parts)
+__device__ __forceinline__ void block_partials(const double (&acc)[NV], const int (&slot)[NV],
+                                               double *__restrict__ parts)
 {
-    __shared__ double red[4][NV];
+    constexpr int NW = GM_BT / 64;
+    __shared__ double red[NV * NW];
+    double s[(NV + 3) / 4];
+    wave_sums<NV>(acc, s);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, v0 = wave_sum_value(lane >> 4);
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
-        for (int off = 32; off > 0; off >>= 1) acc[v] += __shfl_down(acc[v], off, 64);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) red[wv][v] = acc[v];
+    for (int h = 0; h < (NV + 3) / 4; ++h)
+        if ((lane & 15) == 0 && 4 * h + v0 < NV) red[(4 * h + v0) * NW + wv] = s[h];
     __syncthreads();
-    if (threadIdx.x < NV) {
-        const int v = threadIdx.x;
-        parts[(size_t)slot[v] * GM_BLOCKS + blockIdx.x] = (red[0][v] + red[1][v]) + (red[2][v] + red[3][v]);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        if ((int)threadIdx.x != v) continue;
+        double a[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) a[w] = red[v * NW + w];
+#pragma unroll
+        for (int st = NW / 2; st > 0; st >>= 1)
+#pragma unroll
+            for (int w = 0; w < st; ++w) a[w] += a[w + st];
+        parts[(size_t)slot[v] * GM_BLOCKS + blockIdx.x] = a[0];
     }
 }
 
-// The sum over the nb blocks of the partials of slot slot0 + v into out[v],
-// v < nv, in block order (lane-strided, then a wave tree; one wave per value):
-// the order of k_gm_reduce.
-__device__ __forceinline__ void reduce_slots(const double *parts, int nb, int slot0, int nv, double *out)
+// The sums over the nb blocks of the partials of slots slot0 + v into out[v],
+// v < NV (lane-strided, then by halving; a wave takes every GM_BT / 64-th
+// value).  A lane's loads are issued together, before they are added in order:
+// a chain of load and add takes longer than the pass on a small level.
+template <int NV>
+__device__ __forceinline__ void reduce_slots(const double *parts, int nb, int slot0, double *out)
 {
+    constexpr int NL = GM_BLOCKS / 64, NW = GM_BT / 64, NR = (NV + NW - 1) / NW;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int v = wv; v < nv; v += 4) {
-        double a = 0.0;
-        for (int i = lane; i < nb; i += 64) a += parts[(size_t)(slot0 + v) * GM_BLOCKS + i];
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-        if (lane == 0) out[v] = a;
+    double x[NR][NL];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const double *p = parts + (size_t)(slot0 + min(wv + r * NW, NV - 1)) * GM_BLOCKS;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (64 * k < nb) x[r][k] = p[min(lane + 64 * k, nb - 1)];
     }
+    double a[NR], s[(NR + 3) / 4];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        a[r] = 0.0;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (64 * k < nb && lane + 64 * k < nb) a[r] += x[r][k];
+    }
+    wave_sums<NR>(a, s);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        if (lane == wave_sum_lane(r & 3) && wv + r * NW < NV) out[wv + r * NW] = s[r / 4];
 }
 
-// The small least-squares problem (one thread, FP64, working arrays in LDS):
-// from the squared norms n[0..m] and the products d[2 (j GMRES_MAX_M + i)] =
-// <Z_i, A Z_j> (re, im), the coefficients c[2 j] (re, im) of the
-// unnormalised basis vectors, c_j = y_j / sqrt(n_j), zero past a breakdown.
-struct GmWork {
-    cd H[GMRES_MAX_M + 1][GMRES_MAX_M], g[GMRES_MAX_M + 1], cs[GMRES_MAX_M], sn[GMRES_MAX_M], y[GMRES_MAX_M];
-};
-
-__device__ void gm_solve_small(const double *n, const double *d, int m, double *c, GmWork &W)
+// The small least-squares problem (one thread, FP64; H is in registers, as every
+// index is a constant once the loops are unrolled, up to 4 columns, and in LDS
+// beyond): from the squared norms n[0..M]
+// and the products d[2 (j GMRES_MAX_M + i)] = <Z_i, A Z_j> (re, im), the
+// coefficients c[2 j] (re, im) of the unnormalised basis vectors, c_j = y_j /
+// sqrt(n_j), zero past a breakdown (after k columns).
+template <int M>
+__device__ __forceinline__ void gm_solve_in(const double *n, const double *d, double *c, cd (&H)[M + 1][M])
 {
-    for (int j = 0; j < m; ++j) c[2 * j] = c[2 * j + 1] = 0.0;
-    const double n0 = n[0];
-    if (!(n0 > 0.0)) return;
-    int k = m;
-    for (int j = 0; j < m; ++j) {
-        const double nj = n[j];
+    cd g[M + 1], cs[M], sn[M], y[M];
+#pragma unroll
+    for (int j = 0; j < M; ++j) c[2 * j] = c[2 * j + 1] = 0.0;
+    double nv[M + 1];
+#pragma unroll
+    for (int j = 0; j <= M; ++j) nv[j] = n[j];
+    if (!(nv[0] > 0.0)) return;
+    int k = M;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        if (j >= k) continue;
+#pragma unroll
         for (int i = 0; i <= j; ++i) {
-            const double sc = 1.0 / sqrt(n[i] * nj);
-            W.H[i][j] = cd{d[2 * (j * GMRES_MAX_M + i)] * sc, d[2 * (j * GMRES_MAX_M + i) + 1] * sc};
+            const double sc = 1.0 / sqrt(nv[i] * nv[j]);
+            H[i][j] = cd{d[2 * (j * GMRES_MAX_M + i)] * sc, d[2 * (j * GMRES_MAX_M + i) + 1] * sc};
         }
-        for (int i = j + 1; i <= m; ++i) W.H[i][j] = cd{0.0, 0.0};
-        const double nn = n[j + 1];
-        W.H[j + 1][j] = cd{nn > 0.0 ? sqrt(nn / nj) : 0.0, 0.0};
-        if (!(nn > 0.0)) {   // the Krylov space is invariant: solve with j + 1 columns
-            k = j + 1;
-            break;
-        }
+        const double nn = nv[j + 1];
+        H[j + 1][j] = cd{nn > 0.0 ? sqrt(nn / nv[j]) : 0.0, 0.0};
+        if (!(nn > 0.0)) k = j + 1;   // the Krylov space is invariant: solve with j + 1 columns
     }
-    for (int i = 0; i <= k; ++i) W.g[i] = cd{0.0, 0.0};
-    W.g[0] = cd{sqrt(n0), 0.0};
-    for (int j = 0; j < k; ++j) {
+#pragma unroll
+    for (int i = 0; i <= M; ++i) g[i] = cd{0.0, 0.0};
+    g[0] = cd{sqrt(nv[0]), 0.0};
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        if (j >= k) continue;
+#pragma unroll
         for (int i = 0; i < j; ++i) {
-            cd t = W.cs[i] * W.H[i][j] + W.sn[i] * W.H[i + 1][j];
-            W.H[i + 1][j] = cd{-W.sn[i].re, W.sn[i].im} * W.H[i][j] + W.cs[i] * W.H[i + 1][j];
-            W.H[i][j] = t;
+            const cd t = cs[i] * H[i][j] + sn[i] * H[i + 1][j];
+            H[i + 1][j] = cd{-sn[i].re, sn[i].im} * H[i][j] + cs[i] * H[i + 1][j];
+            H[i][j] = t;
         }
-        const cd a = W.H[j][j], cc = W.H[j + 1][j];
+        const cd a = H[j][j], cc = H[j + 1][j];
         const double r = sqrt(a.re * a.re + a.im * a.im + cc.re * cc.re + cc.im * cc.im);
-        if (r == 0.0) {
-            W.cs[j] = cd{1.0, 0.0};
-            W.sn[j] = cd{0.0, 0.0};
-            continue;
-        }
+        cs[j] = cd{1.0, 0.0};
+        sn[j] = cd{0.0, 0.0};
+        if (r == 0.0) continue;
         const double aa = sqrt(a.re * a.re + a.im * a.im);
         if (aa == 0.0) {
-            W.cs[j] = cd{0.0, 0.0};
-            W.sn[j] = cd{cc.re / r, -cc.im / r};
+            cs[j] = cd{0.0, 0.0};
+            sn[j] = cd{cc.re / r, -cc.im / r};
         } else {
-            W.cs[j] = cd{aa / r, 0.0};
+            cs[j] = cd{aa / r, 0.0};
             const cd ph = {a.re / aa, a.im / aa};
-            W.sn[j] = ph * cd{cc.re / r, -cc.im / r};
+            sn[j] = ph * cd{cc.re / r, -cc.im / r};
         }
-        W.H[j][j] = W.cs[j] * a + W.sn[j] * cc;
-        W.H[j + 1][j] = cd{0.0, 0.0};
-        cd t = W.cs[j] * W.g[j] + W.sn[j] * W.g[j + 1];
-        W.g[j + 1] = cd{-W.sn[j].re, W.sn[j].im} * W.g[j] + W.cs[j] * W.g[j + 1];
-        W.g[j] = t;
+        H[j][j] = cs[j] * a + sn[j] * cc;
+        H[j + 1][j] = cd{0.0, 0.0};
+        const cd t = cs[j] * g[j] + sn[j] * g[j + 1];
+        g[j + 1] = cd{-sn[j].re, sn[j].im} * g[j] + cs[j] * g[j + 1];
+        g[j] = t;
     }
-    for (int i = k - 1; i >= 0; --i) {
-        cd t = W.g[i];
-        for (int j = i + 1; j < k; ++j) t = t - W.H[i][j] * W.y[j];
-        const cd dd_ = W.H[i][i];
+#pragma unroll
+    for (int i = M - 1; i >= 0; --i) {
+        if (i >= k) continue;
+        cd t = g[i];
+#pragma unroll
+        for (int j = i + 1; j < M; ++j)
+            if (j < k) t = t - H[i][j] * y[j];
+        const cd dd_ = H[i][i];
         const double dd = dd_.re * dd_.re + dd_.im * dd_.im;
-        W.y[i] = dd > 0.0 ? cd{(t.re * dd_.re + t.im * dd_.im) / dd, (t.im * dd_.re - t.re * dd_.im) / dd}
-                          : cd{0.0, 0.0};
+        y[i] = dd > 0.0 ? cd{(t.re * dd_.re + t.im * dd_.im) / dd, (t.im * dd_.re - t.re * dd_.im) / dd}
+                        : cd{0.0, 0.0};
+        const double sc = 1.0 / sqrt(nv[i]);
+        c[2 * i] = y[i].re * sc;
+        c[2 * i + 1] = y[i].im * sc;
     }
-    for (int j = 0; j < k; ++j) {
-        const double sc = 1.0 / sqrt(n[j]);
-        c[2 * j] = W.y[j].re * sc;
-        c[2 * j + 1] = W.y[j].im * sc;
+}
+
+template <int M>
+__device__ __forceinline__ void gm_solve_small(const double *n, const double *d, double *c)
+{
+    if constexpr (M <= 4) {
+        cd H[M + 1][M];
+        gm_solve_in<M>(n, d, c, H);
+    } else {
+        __shared__ double Hs[2 * (M + 1) * M];
+        gm_solve_in<M>(n, d, c, reinterpret_cast<cd(&)[M + 1][M]>(Hs));
     }
 }
 
 // Z0 = b - A u (zero: u is 0 and is set to 0), partial n_0 = |Z0|^2.
 template <typename T, int DIM>
-__global__ __launch_bounds__(256) void k_gm_resid(cx<T> *__restrict__ u, int zero, const cx<T> *__restrict__ b,
+__global__ __launch_bounds__(GM_BT) void k_gm_resid(cx<T> *__restrict__ u, int zero, const cx<T> *__restrict__ b,
                                                   const cx<T> *__restrict__ q, cx<T> *__restrict__ z0, Stencil<T> P,
                                                   size_t N, double *__restrict__ parts, const int *__restrict__ stop)
 {
     if (stop && *stop) return;
     double acc[1] = {0.0};
-    for (size_t j = (size_t)blockIdx.x * 256 + threadIdx.x; j < N; j += (size_t)gridDim.x * 256) {
+    for (size_t j = (size_t)blockIdx.x * GM_BT + threadIdx.x; j < N; j += (size_t)gridDim.x * GM_BT) {
         cx<T> r = b[j];
         if (zero) {
             u[j] = cx<T>{T(0), T(0)};
@@ -206,7 +253,7 @@ __global__ __launch_bounds__(256) void k_gm_resid(cx<T> *__restrict__ u, int zer
 // W = A Z_j into w (the reference path: Z_{j+1}'s slot); partial d_ij =
 // <Z_i, W> for i <= j (j = NJ - 1).
 template <typename T, int DIM, int NJ>
-__global__ __launch_bounds__(256) void k_gm_apply_dots(cx<T> *__restrict__ Z, cx<T> *__restrict__ w, size_t N,
+__global__ __launch_bounds__(GM_BT) void k_gm_apply_dots(cx<T> *__restrict__ Z, cx<T> *__restrict__ w, size_t N,
                                                        const cx<T> *__restrict__ q, Stencil<T> P,
                                                        double *__restrict__ parts, const int *__restrict__ stop)
 {
@@ -216,7 +263,7 @@ __global__ __launch_bounds__(256) void k_gm_apply_dots(cx<T> *__restrict__ Z, cx
     double acc[2 * NJ];
 #pragma unroll
     for (int v = 0; v < 2 * NJ; ++v) acc[v] = 0.0;
-    for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < N; p += (size_t)gridDim.x * 256) {
+    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
         cx<T> Wp = apply_at<T, DIM>(P, zj, q[p], p);
         w[p] = Wp;
         const double wr = Wp.re, wi = Wp.im;
@@ -272,8 +319,8 @@ __device__ __forceinline__ void step_scalars(const double *__restrict__ parts, i
 {
     constexpr int dcol = GM_D + 2 * ((J - 1) * GMRES_MAX_M);
     if (threadIdx.x < J - 1) Sl[threadIdx.x] = S[threadIdx.x];
-    reduce_slots(parts, nb, J - 1, 1, Sl + (J - 1));
-    reduce_slots(parts, nb, NSLOT_D + 2 * ((J - 1) * GMRES_MAX_M), 2 * J, Sl + dcol);
+    reduce_slots<1>(parts, nb, J - 1, Sl + (J - 1));
+    reduce_slots<2 * J>(parts, nb, NSLOT_D + 2 * ((J - 1) * GMRES_MAX_M), Sl + dcol);
     __syncthreads();
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) S[J - 1] = Sl[J - 1];
@@ -286,7 +333,7 @@ __device__ __forceinline__ void step_scalars(const double *__restrict__ parts, i
 // = A Z_J; the partial |Z_J|^2 and <Z_i, A Z_J> (i <= J).  The values and
 // partial sums of k_gm_orth<J> followed by k_gm_apply_dots<J + 1>.
 template <typename T, int DIM, int J>
-__global__ __launch_bounds__(256) void k_gm_orth_apply(cx<T> *__restrict__ Z, const cx<T> *__restrict__ wprev,
+__global__ __launch_bounds__(GM_BT) void k_gm_orth_apply(cx<T> *__restrict__ Z, const cx<T> *__restrict__ wprev,
                                                        cx<T> *__restrict__ wout, size_t N,
                                                        const cx<T> *__restrict__ q, Stencil<T> P,
                                                        double *__restrict__ S, double *__restrict__ parts,
@@ -302,7 +349,7 @@ __global__ __launch_bounds__(256) void k_gm_orth_apply(cx<T> *__restrict__ Z, co
     double acc[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < N; p += (size_t)gridDim.x * 256) {
+    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
         const cx<T> zc = orth_at<T, J>(wprev, Z, N, g, p);
         const cx<T> Wp = apply_at_f<T, DIM>(P, [&](size_t k) { return orth_at<T, J>(wprev, Z, N, g, k); }, zc, q[p], p);
         zJ[p] = zc;
@@ -326,7 +373,7 @@ __global__ __launch_bounds__(256) void k_gm_orth_apply(cx<T> *__restrict__ Z, co
 // The last Arnoldi vector's partial norm: n_M = |A Z_{M-1} - sum_{i<M} g_i
 // Z_i|^2 (the vector itself is not needed).
 template <typename T, int M>
-__global__ __launch_bounds__(256) void k_gm_orth_norm(const cx<T> *__restrict__ Z, const cx<T> *__restrict__ wprev,
+__global__ __launch_bounds__(GM_BT) void k_gm_orth_norm(const cx<T> *__restrict__ Z, const cx<T> *__restrict__ wprev,
                                                       size_t N, double *__restrict__ S, double *__restrict__ parts,
                                                       const int *__restrict__ stop)
 {
@@ -336,7 +383,7 @@ __global__ __launch_bounds__(256) void k_gm_orth_norm(const cx<T> *__restrict__ 
     cx<T> g[M];
     orth_coeffs<T, M>(Sl, g);
     double acc[1] = {0.0};
-    for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < N; p += (size_t)gridDim.x * 256) {
+    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
         const cx<T> v = orth_at<T, M>(wprev, Z, N, g, p);
         acc[0] += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
     }
@@ -348,19 +395,18 @@ __global__ __launch_bounds__(256) void k_gm_orth_norm(const cx<T> *__restrict__ 
 // block sums n_M from the partials, takes the other scalars from S and solves
 // the small problem (the first block also stores n_M and the coefficients).
 template <typename T, int M>
-__global__ __launch_bounds__(256) void k_gm_solve_update(cx<T> *__restrict__ u, const cx<T> *__restrict__ Z,
+__global__ __launch_bounds__(GM_BT) void k_gm_solve_update(cx<T> *__restrict__ u, const cx<T> *__restrict__ Z,
                                                          size_t N, double *__restrict__ S,
                                                          const double *__restrict__ parts,
                                                          const int *__restrict__ stop)
 {
     if (stop && *stop) return;
     __shared__ double Sl[GM_S];
-    __shared__ GmWork W;
     if (threadIdx.x < M) Sl[threadIdx.x] = S[threadIdx.x];
-    for (int t = threadIdx.x; t < 2 * M * GMRES_MAX_M; t += 256) Sl[GM_D + t] = S[GM_D + t];
-    reduce_slots(parts, gridDim.x, M, 1, Sl + M);
+    for (int t = threadIdx.x; t < 2 * M * GMRES_MAX_M; t += GM_BT) Sl[GM_D + t] = S[GM_D + t];
+    reduce_slots<1>(parts, gridDim.x, M, Sl + M);
     __syncthreads();
-    if (threadIdx.x == 0) gm_solve_small(Sl, Sl + GM_D, M, Sl + GM_C, W);
+    if (threadIdx.x == 0) gm_solve_small<M>(Sl, Sl + GM_D, Sl + GM_C);
     __syncthreads();
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0) S[M] = Sl[M];
@@ -369,7 +415,7 @@ __global__ __launch_bounds__(256) void k_gm_solve_update(cx<T> *__restrict__ u, 
     cx<T> c[M];
 #pragma unroll
     for (int j = 0; j < M; ++j) c[j] = cx<T>{T(Sl[GM_C + 2 * j]), T(Sl[GM_C + 2 * j + 1])};
-    for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < N; p += (size_t)gridDim.x * 256) {
+    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
         cx<T> v = u[p];
 #pragma unroll
         for (int j = 0; j < M; ++j) {
@@ -382,7 +428,7 @@ __global__ __launch_bounds__(256) void k_gm_solve_update(cx<T> *__restrict__ u, 
 
 // Z_{j+1} = W - sum_{i<=j} (d_ij / n_i) Z_i in place, partial |Z_{j+1}|^2.
 template <typename T, int NJ>
-__global__ __launch_bounds__(256) void k_gm_orth(cx<T> *__restrict__ Z, size_t N, const double *__restrict__ S,
+__global__ __launch_bounds__(GM_BT) void k_gm_orth(cx<T> *__restrict__ Z, size_t N, const double *__restrict__ S,
                                                  double *__restrict__ parts, const int *__restrict__ stop)
 {
     if (stop && *stop) return;
@@ -390,7 +436,7 @@ __global__ __launch_bounds__(256) void k_gm_orth(cx<T> *__restrict__ Z, size_t N
     orth_coeffs<T, NJ>(S, g);
     cx<T> *w = Z + (size_t)NJ * N;
     double acc[1] = {0.0};
-    for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < N; p += (size_t)gridDim.x * 256) {
+    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
         const cx<T> v = orth_at<T, NJ>(w, Z, N, g, p);
         w[p] = v;
         acc[0] += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
@@ -399,34 +445,31 @@ __global__ __launch_bounds__(256) void k_gm_orth(cx<T> *__restrict__ Z, size_t N
     block_partials<1>(acc, slot, parts);
 }
 
-// out[v] = sum over the nb blocks of the partials of slot0 + v, in block order
-// (one block, one wave per value), and likewise out1[v] from slot1 + v for
-// v < nv1; solve_m > 0: then the small problem.
-__global__ __launch_bounds__(256) void k_gm_reduce(const double *__restrict__ parts, int nb, int slot0, int nv,
-                                                   double *__restrict__ out, int solve_m, double *__restrict__ S,
-                                                   const int *__restrict__ stop, int slot1 = 0, int nv1 = 0,
-                                                   double *__restrict__ out1 = nullptr)
+// out[v] = sum over the nb blocks of the partials of slot0 + v for v < NV (one
+// block); SOLVE_M > 0: then the small problem (out lies in S: neither is
+// restrict, or the loads of S may come before the store, by the scalar cache).
+template <int NV, int SOLVE_M>
+__global__ __launch_bounds__(GM_BT) void k_gm_reduce(const double *__restrict__ parts, int nb, int slot0, double *out,
+                                                     double *S, const int *__restrict__ stop)
 {
     if (stop && *stop) return;
-    reduce_slots(parts, nb, slot0, nv, out);
-    if (nv1 > 0) reduce_slots(parts, nb, slot1, nv1, out1);
-    if (solve_m > 0) {
-        __shared__ GmWork W;
+    reduce_slots<NV>(parts, nb, slot0, out);
+    if constexpr (SOLVE_M > 0) {
         __syncthreads();
-        if (threadIdx.x == 0) gm_solve_small(S, S + GM_D, solve_m, S + GM_C, W);
+        if (threadIdx.x == 0) gm_solve_small<SOLVE_M>(S, S + GM_D, S + GM_C);
     }
 }
 
 // u += sum_j c_j Z_j.
 template <typename T, int M>
-__global__ __launch_bounds__(256) void k_gm_update(cx<T> *__restrict__ u, const cx<T> *__restrict__ Z, size_t N,
+__global__ __launch_bounds__(GM_BT) void k_gm_update(cx<T> *__restrict__ u, const cx<T> *__restrict__ Z, size_t N,
                                                    const double *__restrict__ S, const int *__restrict__ stop)
 {
     if (stop && *stop) return;
     cx<T> c[M];
 #pragma unroll
     for (int j = 0; j < M; ++j) c[j] = cx<T>{T(S[GM_C + 2 * j]), T(S[GM_C + 2 * j + 1])};
-    for (size_t p = (size_t)blockIdx.x * 256 + threadIdx.x; p < N; p += (size_t)gridDim.x * 256) {
+    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
         cx<T> v = u[p];
 #pragma unroll
         for (int j = 0; j < M; ++j) {
@@ -447,28 +490,20 @@ constexpr size_t GM_SMALL_POINTS = 1024;   // = GM_REG_PTS * GM_SMALL_THREADS
 constexpr size_t GM_BLOCK_MAX_POINTS = 4096;
 
 template <int NV, int BT>
-__device__ __forceinline__ void block_reduce_bt(double (&acc)[NV], double *out, double (*red)[2 * GMRES_MAX_M])
+__device__ __forceinline__ void block_reduce_bt(const double (&acc)[NV], double *out, double *red)
 {
+    double s[(NV + 3) / 4];
+    block_sums<NV, BT / 64>(acc, s, red);
 #pragma unroll
     for (int v = 0; v < NV; ++v)
-        for (int off = 32; off > 0; off >>= 1) acc[v] += __shfl_down(acc[v], off, 64);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) red[wv][v] = acc[v];
-    __syncthreads();
-    if (threadIdx.x < NV) {
-        double a = 0.0;
-        for (int w_ = 0; w_ < BT / 64; ++w_) a += red[w_][threadIdx.x];
-        out[threadIdx.x] = a;
-    }
+        if ((int)threadIdx.x == wave_sum_lane(v & 3)) out[v] = s[v / 4];
     __syncthreads();
 }
 
 template <typename T, int DIM, int NJ, int BT>
 __device__ __forceinline__ void gm_block_arnoldi(cx<T> *__restrict__ Z, size_t N, const cx<T> *__restrict__ q,
                                                  const Stencil<T> &P, double *n, double *d,
-                                                 double (*red)[2 * GMRES_MAX_M])
+                                                 double *red)
 {
     constexpr int j = NJ - 1;
     const cx<T> *zj = Z + (size_t)j * N;
@@ -511,7 +546,7 @@ __device__ __forceinline__ void gm_block_arnoldi(cx<T> *__restrict__ Z, size_t N
 
 template <typename T, int DIM, int NJ, int M, int BT>
 __device__ __forceinline__ void gm_block_arnoldi_all(cx<T> *Z, size_t N, const cx<T> *q, const Stencil<T> &P,
-                                                     double *n, double *d, double (*red)[2 * GMRES_MAX_M])
+                                                     double *n, double *d, double *red)
 {
     gm_block_arnoldi<T, DIM, NJ, BT>(Z, N, q, P, n, d, red);
     if constexpr (NJ < M) gm_block_arnoldi_all<T, DIM, NJ + 1, M, BT>(Z, N, q, P, n, d, red);
@@ -523,9 +558,8 @@ __global__ __launch_bounds__(BT) void k_gm_step_block(const cx<T> *__restrict__ 
                                                         Stencil<T> P, size_t N, const int *__restrict__ stop)
 {
     if (stop && *stop) return;
-    __shared__ double red[BT / 64][2 * GMRES_MAX_M];
+    __shared__ double red[2 * GMRES_MAX_M * (BT / 64)];
     __shared__ double n[GMRES_MAX_M + 1], d[2 * GMRES_MAX_M * GMRES_MAX_M], c[2 * GMRES_MAX_M];
-    __shared__ GmWork W;
     double acc[1] = {0.0};
     for (size_t p = threadIdx.x; p < N; p += BT) {
         cx<T> r = b[p];
@@ -540,7 +574,7 @@ __global__ __launch_bounds__(BT) void k_gm_step_block(const cx<T> *__restrict__ 
     }
     block_reduce_bt<1, BT>(acc, n, red);
     gm_block_arnoldi_all<T, DIM, 1, M, BT>(Z, N, q, P, n, d, red);
-    if (threadIdx.x == 0) gm_solve_small(n, d, M, c, W);
+    if (threadIdx.x == 0) gm_solve_small<M>(n, d, c);
     __syncthreads();
     cx<T> cc[M];
 #pragma unroll
@@ -558,32 +592,66 @@ __global__ __launch_bounds__(BT) void k_gm_step_block(const cx<T> *__restrict__ 
 
 // The same step with the level's vectors held in registers (thread t holds
 // the points p = t + BT k, k < GM_REG_PTS) and only the vector that A is
-// applied to staged in LDS (dynamic shared memory, N values): no global
-// traffic inside the step but the loads of b, q, u and the store of u.  The
-// values, the sums and their order are those of k_gm_step_block.
+// applied to staged in LDS (dynamic shared memory, N + 1 values, the last one
+// zero): no global traffic inside the step but the loads of b, q, u and the
+// store of u.  The values, the sums and their order are those of
+// k_gm_step_block.
+//
+// Bound by the chain of sums and, with 1024 threads, by one CU's vector rate,
+// so what every product needs again is formed once: the LDS offsets of a
+// point's neighbours (16 bits each; the zero's where there is none), and one
+// division a coefficient instead of one a coefficient and thread.  The sums end
+// in every wave (one barrier each); the scalars are wave-uniform registers.
+// FP32, m = 3: 31 x 31 9.9 us (15.0 with the neighbours found from each point's
+// coordinates, sums by shuffles and the scalars in LDS), 63 x 63 17.5 us (25.6).
 constexpr int GM_REG_PTS = (int)(GM_BLOCK_MAX_POINTS / GM_BLOCK_THREADS);   // also for the small blocks
+static_assert(2 * GM_BLOCK_MAX_POINTS <= 65535, "neighbour offsets in units of 8 bytes");
+
+template <typename T>
+__device__ __forceinline__ cx<T> staged(const cx<T> *stage, unsigned off8)
+{
+    return *reinterpret_cast<const cx<T> *>(reinterpret_cast<const unsigned char *>(stage) + 8 * off8);
+}
+
+// A z at a point from the stage; nb: the point's neighbours, west | east << 16,
+// south | north << 16, down | up << 16, in units of 8 bytes.
+template <typename T, int DIM>
+__device__ __forceinline__ cx<T> apply_staged(const Stencil<T> &P, const cx<T> *stage, unsigned nx, unsigned ny,
+                                              unsigned nz, cx<T> zc, cx<T> qj)
+{
+    cx<T> L = lap_xy(P, zc, staged(stage, nx & 0xffff), staged(stage, nx >> 16), staged(stage, ny & 0xffff),
+                     staged(stage, ny >> 16));
+    if (DIM == 3) L = lap_add_z(P, L, zc, staged(stage, nz & 0xffff), staged(stage, nz >> 16));
+    return apply_point(P, L, zc, qj);
+}
+
+// The scalars of the step, the same in every wave.
+struct GmScalars {
+    double n[GMRES_MAX_M + 1], d[2 * GMRES_MAX_M * GMRES_MAX_M];
+};
 
 template <typename T, int DIM, int NJ, int M, int BT>
 __device__ __forceinline__ void gm_reg_arnoldi(cx<T> (&Z)[M + 1][GM_REG_PTS], const cx<T> (&qv)[GM_REG_PTS],
-                                               cx<T> *stage, const Stencil<T> &P, int N, double *n, double *d,
-                                               double (*red)[2 * GMRES_MAX_M])
+                                               cx<T> *stage, const unsigned (&nbr)[3][GM_REG_PTS],
+                                               const Stencil<T> &P, int N, GmScalars &sc,
+                                               double (&red)[2][2 * M * (BT / 64)])
 {
-    constexpr int j = NJ - 1;
-    // the reduction before ended with a barrier: every thread is past its reads of the stage
+    constexpr int j = NJ - 1, NH = (2 * NJ + 3) / 4;
+    // every thread is past its reads of the stage: a block-wide sum came after them
 #pragma unroll
     for (int k = 0; k < GM_REG_PTS; ++k) {
         const int p = (int)threadIdx.x + BT * k;
         if (p < N) stage[p] = Z[j][k];
     }
     __syncthreads();
-    double acc[2 * NJ];
+    double acc[2 * NJ], s[NH];
 #pragma unroll
     for (int v = 0; v < 2 * NJ; ++v) acc[v] = 0.0;
 #pragma unroll
     for (int k = 0; k < GM_REG_PTS; ++k) {
         const int p = (int)threadIdx.x + BT * k;
         if (p < N) {
-            const cx<T> Wp = apply_at_f<T, DIM>(P, [&](size_t i) { return stage[i]; }, Z[j][k], qv[k], (size_t)p);
+            const cx<T> Wp = apply_staged<T, DIM>(P, stage, nbr[0][k], nbr[1][k], nbr[2][k], Z[j][k], qv[k]);
             Z[NJ][k] = Wp;
             const double wr = Wp.re, wi = Wp.im;
 #pragma unroll
@@ -594,15 +662,23 @@ __device__ __forceinline__ void gm_reg_arnoldi(cx<T> (&Z)[M + 1][GM_REG_PTS], co
             }
         }
     }
-    block_reduce_bt<2 * NJ, BT>(acc, d + 2 * (j * GMRES_MAX_M), red);
+    block_sums<2 * NJ, BT / 64>(acc, s, red[1]);
     cx<T> g[NJ];
+    const bool odd = (threadIdx.x >> 4) & 1;   // the rows of 16 lanes that hold values 2 and 3 of four
+    T gv[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+        const double ni = 2 * h + 1 < NJ ? (odd ? sc.n[2 * h + 1 < NJ ? 2 * h + 1 : 0] : sc.n[2 * h]) : sc.n[2 * h];
+        gv[h] = T(ni > 0.0 ? s[h] / ni : 0.0);
+    }
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
-        const double ni = n[i];
-        const double dr = d[2 * (j * GMRES_MAX_M + i)], di = d[2 * (j * GMRES_MAX_M + i) + 1];
-        g[i] = cx<T>{T(ni > 0.0 ? dr / ni : 0.0), T(ni > 0.0 ? di / ni : 0.0)};
+        const int re = wave_sum_lane(2 * (i & 1)), im = wave_sum_lane(2 * (i & 1) + 1);
+        sc.d[2 * (j * GMRES_MAX_M + i)] = lane_value(s[i / 2], re);
+        sc.d[2 * (j * GMRES_MAX_M + i) + 1] = lane_value(s[i / 2], im);
+        g[i] = cx<T>{lane_value(gv[i / 2], re), lane_value(gv[i / 2], im)};
     }
-    double nacc[1] = {0.0};
+    double nacc[1] = {0.0}, ns[1];
 #pragma unroll
     for (int k = 0; k < GM_REG_PTS; ++k) {
         const int p = (int)threadIdx.x + BT * k;
@@ -617,8 +693,9 @@ __device__ __forceinline__ void gm_reg_arnoldi(cx<T> (&Z)[M + 1][GM_REG_PTS], co
             nacc[0] += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
         }
     }
-    block_reduce_bt<1, BT>(nacc, n + NJ, red);
-    if constexpr (NJ < M) gm_reg_arnoldi<T, DIM, NJ + 1, M, BT>(Z, qv, stage, P, N, n, d, red);
+    block_sums<1, BT / 64>(nacc, ns, red[0]);
+    sc.n[NJ] = lane_value(ns[0], 0);
+    if constexpr (NJ < M) gm_reg_arnoldi<T, DIM, NJ + 1, M, BT>(Z, qv, stage, nbr, P, N, sc, red);
 }
 
 template <typename T, int DIM, int M, int BT>
@@ -628,12 +705,11 @@ __global__ __launch_bounds__(BT) void k_gm_step_reg(const cx<T> *__restrict__ b,
 {
     if (stop && *stop) return;
     extern __shared__ __attribute__((aligned(16))) unsigned char gm_stage_raw[];
+    __shared__ double red[2][2 * M * (BT / 64)], c[2 * GMRES_MAX_M];
     cx<T> *stage = reinterpret_cast<cx<T> *>(gm_stage_raw);
-    __shared__ double red[BT / 64][2 * GMRES_MAX_M];
-    __shared__ double n[GMRES_MAX_M + 1], d[2 * GMRES_MAX_M * GMRES_MAX_M], c[2 * GMRES_MAX_M];
-    __shared__ GmWork W;
     const cx<T> zc = {T(0), T(0)};
     cx<T> qv[GM_REG_PTS], uv[GM_REG_PTS], Z[M + 1][GM_REG_PTS];
+    unsigned nbr[3][GM_REG_PTS];
 #pragma unroll
     for (int k = 0; k < GM_REG_PTS; ++k) {
         const int p = (int)threadIdx.x + BT * k;
@@ -642,30 +718,44 @@ __global__ __launch_bounds__(BT) void k_gm_step_reg(const cx<T> *__restrict__ b,
         for (int j = 0; j <= M; ++j) Z[j][k] = zc;
         if (p < N) {
             qv[k] = q[p];
+            Z[0][k] = b[p];
             if (!zero) {
                 uv[k] = u[p];
                 stage[p] = uv[k];
             }
         }
     }
+    if (threadIdx.x == 0) stage[N] = zc;
+#pragma unroll
+    for (int k = 0; k < GM_REG_PTS; ++k) {
+        const int p = min((int)threadIdx.x + BT * k, N - 1), sy = P.mx, sz = P.mx * P.my;
+        int ix, iy, iz;
+        split3((unsigned)p, P.mx, P.my, ix, iy, iz);
+        auto off = [&](bool in, int i) { return (unsigned)(sizeof(cx<T>) / 8) * (unsigned)(in ? i : N); };
+        nbr[0][k] = off(ix > 0, p - 1) | off(ix < P.mx - 1, p + 1) << 16;
+        nbr[1][k] = off(iy > 0, p - sy) | off(iy < P.my - 1, p + sy) << 16;
+        nbr[2][k] = DIM == 2 ? 0 : off(iz > 0, p - sz) | off(iz < P.mz - 1, p + sz) << 16;
+    }
     __syncthreads();
-    double acc[1] = {0.0};
+    GmScalars sc;
+    double acc[1] = {0.0}, ns[1];
 #pragma unroll
     for (int k = 0; k < GM_REG_PTS; ++k) {
         const int p = (int)threadIdx.x + BT * k;
         if (p < N) {
-            cx<T> r = b[p];
+            cx<T> r = Z[0][k];
             if (!zero) {
-                const cx<T> Au = apply_at_f<T, DIM>(P, [&](size_t i) { return stage[i]; }, uv[k], qv[k], (size_t)p);
+                const cx<T> Au = apply_staged<T, DIM>(P, stage, nbr[0][k], nbr[1][k], nbr[2][k], uv[k], qv[k]);
                 r = cx<T>{r.re - Au.re, r.im - Au.im};
             }
             Z[0][k] = r;
             acc[0] += (double)r.re * (double)r.re + (double)r.im * (double)r.im;
         }
     }
-    block_reduce_bt<1, BT>(acc, n, red);
-    gm_reg_arnoldi<T, DIM, 1, M, BT>(Z, qv, stage, P, N, n, d, red);
-    if (threadIdx.x == 0) gm_solve_small(n, d, M, c, W);
+    block_sums<1, BT / 64>(acc, ns, red[0]);
+    sc.n[0] = lane_value(ns[0], 0);
+    gm_reg_arnoldi<T, DIM, 1, M, BT>(Z, qv, stage, nbr, P, N, sc, red);
+    if (threadIdx.x == 0) gm_solve_small<M>(sc.n, sc.d, c);
     __syncthreads();
     cx<T> cc[M];
 #pragma unroll
@@ -698,11 +788,11 @@ static void launch_step_reg(const cx<T> *b, const cx<T> *q, cx<T> *u, bool zero,
     static const bool attr_set = [] {
         (void)hipFuncSetAttribute((const void *)k_gm_step_reg<T, DIM, M, BT>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)(GM_REG_PTS * BT * sizeof(cx<T>)));
+                                  (int)((GM_REG_PTS * BT + 1) * sizeof(cx<T>)));
         return true;
     }();
     (void)attr_set;
-    hipLaunchKernelGGL((k_gm_step_reg<T, DIM, M, BT>), dim3(1), dim3(BT), N * sizeof(cx<T>), s, b, q, u, zero ? 1 : 0,
+    hipLaunchKernelGGL((k_gm_step_reg<T, DIM, M, BT>), dim3(1), dim3(BT), (N + 1) * sizeof(cx<T>), s, b, q, u, zero ? 1 : 0,
                        P, (int)N, stop);
 }
 
@@ -711,13 +801,13 @@ void launch_arnoldi_all(cx<T> *Z, size_t N, const cx<T> *q, const Stencil<T> &P,
                         hipStream_t s, const int *stop)
 {
     constexpr int j = NJ - 1;
-    hipLaunchKernelGGL((k_gm_apply_dots<T, DIM, NJ>), dim3(nb), dim3(256), 0, s, Z, Z + (size_t)NJ * N, N, q, P,
+    hipLaunchKernelGGL((k_gm_apply_dots<T, DIM, NJ>), dim3(nb), dim3(GM_BT), 0, s, Z, Z + (size_t)NJ * N, N, q, P,
                        parts, stop);
-    hipLaunchKernelGGL(k_gm_reduce, dim3(1), dim3(256), 0, s, parts, nb, NSLOT_D + 2 * (j * GMRES_MAX_M), 2 * NJ,
-                       S + GM_D + 2 * (j * GMRES_MAX_M), 0, S, stop, 0, 0, nullptr);
-    hipLaunchKernelGGL((k_gm_orth<T, NJ>), dim3(nb), dim3(256), 0, s, Z, N, S, parts, stop);
-    hipLaunchKernelGGL(k_gm_reduce, dim3(1), dim3(256), 0, s, parts, nb, NJ, 1, S + NJ, NJ == M ? M : 0, S, stop, 0, 0,
-                       nullptr);
+    hipLaunchKernelGGL((k_gm_reduce<2 * NJ, 0>), dim3(1), dim3(GM_BT), 0, s, parts, nb,
+                       NSLOT_D + 2 * (j * GMRES_MAX_M), S + GM_D + 2 * (j * GMRES_MAX_M), S, stop);
+    hipLaunchKernelGGL((k_gm_orth<T, NJ>), dim3(nb), dim3(GM_BT), 0, s, Z, N, S, parts, stop);
+    hipLaunchKernelGGL((k_gm_reduce<1, NJ == M ? M : 0>), dim3(1), dim3(GM_BT), 0, s, parts, nb, NJ, S + NJ, S,
+                       stop);
     if constexpr (NJ < M) launch_arnoldi_all<T, DIM, NJ + 1, M>(Z, N, q, P, S, parts, nb, s, stop);
 }
 
@@ -728,7 +818,7 @@ void launch_orth_apply_all(cx<T> *Z, size_t N, const cx<T> *q, const Stencil<T> 
                            hipStream_t s, const int *stop)
 {
     if constexpr (J < M) {
-        hipLaunchKernelGGL((k_gm_orth_apply<T, DIM, J>), dim3(nb), dim3(256), 0, s, Z,
+        hipLaunchKernelGGL((k_gm_orth_apply<T, DIM, J>), dim3(nb), dim3(GM_BT), 0, s, Z,
                            Z + (size_t)(M + ((J - 1) & 1)) * N, Z + (size_t)(M + (J & 1)) * N, N, q, P, S, parts,
                            stop);
         launch_orth_apply_all<T, DIM, J + 1, M>(Z, N, q, P, S, parts, nb, s, stop);
@@ -759,20 +849,20 @@ void launch_step_m(const LevelGeom &g, const Stencil<T> &P, const cx<T> *b, cons
                                b, q, u, zero ? 1 : 0, Z, P, N, stop);
         return;
     }
-    const int nb = (int)std::min<size_t>((N + 255) / 256, GM_BLOCKS);
-    hipLaunchKernelGGL((k_gm_resid<T, DIM>), dim3(nb), dim3(256), 0, s, u, zero ? 1 : 0, b, q, Z, P, N, parts, stop);
+    const int nb = (int)std::min<size_t>((N + GM_BT - 1) / GM_BT, GM_BLOCKS);
+    hipLaunchKernelGGL((k_gm_resid<T, DIM>), dim3(nb), dim3(GM_BT), 0, s, u, zero ? 1 : 0, b, q, Z, P, N, parts, stop);
     if (fused) {
-        hipLaunchKernelGGL((k_gm_apply_dots<T, DIM, 1>), dim3(nb), dim3(256), 0, s, Z, Z + (size_t)M * N, N, q, P,
+        hipLaunchKernelGGL((k_gm_apply_dots<T, DIM, 1>), dim3(nb), dim3(GM_BT), 0, s, Z, Z + (size_t)M * N, N, q, P,
                            parts, stop);
         launch_orth_apply_all<T, DIM, 1, M>(Z, N, q, P, S, parts, nb, s, stop);
-        hipLaunchKernelGGL((k_gm_orth_norm<T, M>), dim3(nb), dim3(256), 0, s, Z, Z + (size_t)(M + ((M - 1) & 1)) * N,
+        hipLaunchKernelGGL((k_gm_orth_norm<T, M>), dim3(nb), dim3(GM_BT), 0, s, Z, Z + (size_t)(M + ((M - 1) & 1)) * N,
                            N, S, parts, stop);
-        hipLaunchKernelGGL((k_gm_solve_update<T, M>), dim3(nb), dim3(256), 0, s, u, Z, N, S, parts, stop);
+        hipLaunchKernelGGL((k_gm_solve_update<T, M>), dim3(nb), dim3(GM_BT), 0, s, u, Z, N, S, parts, stop);
         return;
     }
-    hipLaunchKernelGGL(k_gm_reduce, dim3(1), dim3(256), 0, s, parts, nb, 0, 1, S, 0, S, stop, 0, 0, nullptr);
+    hipLaunchKernelGGL((k_gm_reduce<1, 0>), dim3(1), dim3(GM_BT), 0, s, parts, nb, 0, S, S, stop);
     launch_arnoldi_all<T, DIM, 1, M>(Z, N, q, P, S, parts, nb, s, stop);
-    hipLaunchKernelGGL((k_gm_update<T, M>), dim3(nb), dim3(256), 0, s, u, Z, N, S, stop);
+    hipLaunchKernelGGL((k_gm_update<T, M>), dim3(nb), dim3(GM_BT), 0, s, u, Z, N, S, stop);
 }
 
 template <typename T, int DIM>

@@ -29,30 +29,11 @@
 
 #include "ffmg_internal.hpp"
 #include "ffmg_point.hpp"
+#include "ffmg_wave.hpp"
 
 namespace ffmg {
 
 namespace {
-
-// The value of the lane below (x - 1) or above (x + 1); 0 beyond the wave.
-template <int CTRL>
-__device__ __forceinline__ unsigned dpp_u32(unsigned v)
-{
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v)
-{
-    return __builtin_bit_cast(float, dpp_u32<CTRL>(__builtin_bit_cast(unsigned, v)));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double v)
-{
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = dpp_u32<CTRL>((unsigned)b), hi = dpp_u32<CTRL>((unsigned)(b >> 32));
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-constexpr int DPP_WAVE_SHR1 = 0x138, DPP_WAVE_SHL1 = 0x130, DPP_ROW_SHL = 0x100;
 
 // v where `in` holds, else 0 (by component: a conditional of the structs may
 // become a load through a selected address).
