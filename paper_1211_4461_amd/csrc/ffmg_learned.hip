@@ -708,20 +708,21 @@ void launch_round_weights(const float2 *Wm, float2 *Wq, hipStream_t s)
 // Inference on a grid with the BF16 MFMA v_mfma_f32_16x16x32_bf16 (A[i][k]
 // from lane i + 16 (k / 8), element k % 8; B[k][j] likewise with j; D[i][j]
 // in lane j + 16 (i / 4), register i % 4).  Each convolution is an implicit
-// GEMM over points: rows are 16 points of a region, columns the real output
-// channels (Re / Im of each complex channel), K the (tap, real input
-// channel) pairs.  A complex weight w acts on (Re x, Im x) as the real 2 x 2
-// block [[Re w, -Im w], [Im w, Re w]].
-//   layer 1: K = 9 taps x 2 (Re / Im), padded to 32, one k-step.  For the
-//            column of part p of channel c, four products give
-//            A = p of a, A' = (-Im a, Re a)[p], M = 1 + Re m (accumulator
-//            started at 1), M' = Im m, and the gate is x1 = A M + A' M'
-//            (Re: a_re (1 + m_re) - a_im m_im; Im: a_im (1 + m_re) +
-//            a_re m_im) without any exchange between lanes
-//   layer 2: K = 32 channels per tap, one k-step per tap; N = 32
-//   layer 3: one output channel, so the 9 taps go to the columns instead:
-//            Z_t = W3[t] x2 per point (K = 32, columns 2 t + part, 18 of 32
+// GEMM over points: rows are the real output channels (Re / Im of each complex
+// channel), columns 16 points of a region, K the (tap, real input channel)
+// pairs.  A complex weight w acts on (Re x, Im x) as the real 2 x 2 block
+// [[Re w, -Im w], [Im w, Re w]].
+//   layer 1: K = 9 taps x 2 (Re / Im), padded to 32, one k-step, a product
+//            for a and one for m (accumulator started at 1 for Re m); a lane
+//            holds Re and Im of both for its channels, so the gate
+//            x1 = a (1 + m) needs no exchange between lanes
+//   layer 2: K = 32 channels per tap, one k-step per tap
+//   layer 3: one output channel, so the 9 taps go to the rows instead:
+//            Z_t = W3[t] x2 per point (K = 32, rows 2 t + part, 18 of 32
 //            used), then N(p) = sum_t Z_t(p + d_t) by a gather from LDS
+// With the points in the columns a lane's two accumulators are 8 channels of
+// one point: layer 1 writes them with one 128-bit store and layer 2's are
+// layer 3's operand as they are, so x2 never leaves the registers.
 // A 16 x 16 output tile needs layer-2 values on 18 x 18 points, layer-1
 // values on 20 x 20 and the inputs on 22 x 22 (zero outside the grid); the
 // activations live in LDS as BF16 [point][channel].  The weight fragments
@@ -732,31 +733,25 @@ constexpr int IT = 16;                       // output tile side
 constexpr int R1 = IT + 4, R2 = IT + 2;      // layer-1 / layer-2 region sides
 constexpr int R0 = IT + 6;                   // input region side
 constexpr int NR1 = (R1 * R1 + 15) / 16;     // row tiles of the layer-1 region
-constexpr int NR2 = (R2 * R2 + 15) / 16;
 constexpr int IN_PER_THREAD = (R0 * R0 + 255) / 256;
 
 // Activations: 32 BF16 channel slots per point, padded to 40 (80 bytes): the
 // 8 lanes a 128-bit LDS read serves together then start 20 dwords apart and
-// cover all 32 banks once.  Slot s holds accumulator column
-// 16 (s & 1) + (s >> 1) of the producing layer, so that the lane owning
-// column li of both column tiles writes slots 2 li and 2 li + 1 as one dword;
-// column j is Re (j even) or Im (j odd) of channel j / 2.
+// cover all 32 banks once.  Slot s holds row 16 (s & 1) + (s >> 1) of the
+// producing layer: the lanes of group lg, which hold rows 4 lg .. 4 lg + 3 of
+// both row tiles, write slots 8 lg .. 8 lg + 7.  Row j is Re (j even) or Im
+// (j odd) of channel j / 2.
 constexpr int XS = 40;
 // Per-tap layer-3 products: 18 floats per point, rows of 20 (80 bytes).
 constexpr int ZS = 20;
 struct alignas(16) InferLds {
-    unsigned short x0[R0 * R0][4];           // r~ re, r~ im, kappa~ re, kappa~ im
-    union {
-        unsigned short x1[NR1 * 16][XS];
-        float z[NR2 * 16][ZS];               // layer-3 per-tap products (after layer 2)
-    };
-    unsigned short x2[NR2 * 16][XS];         // rows past R2 * R2 take unused writes
+    unsigned r0[R0 * R0], k0[R0 * R0];       // r~, kappa~ (packed re, im)
+    unsigned short x1[NR1 * 16][XS];
+    float z[R2 * R2][ZS];
 };
 
 __device__ __forceinline__ bf8 as_bf8(us8 v) { return __builtin_bit_cast(bf8, v); }
 
-// Hardware round-to-nearest-even FP32 -> BF16 (v_cvt_pk_bf16_f32 on gfx950).
-__device__ __forceinline__ unsigned short to_bf16(float f) { return __builtin_bit_cast(unsigned short, (__bf16)f); }
 // Point (y, x) of row-major region of width R for index p.
 struct RegionPos {
     int y, x;
@@ -766,14 +761,6 @@ __device__ __forceinline__ RegionPos region_pos(int p)
 {
     return RegionPos{p / R, p - (p / R) * R};
 }
-template <int R>
-__device__ __forceinline__ void region_next(RegionPos &q)
-{
-    const bool wrap = q.x == R - 1;
-    q.x = wrap ? 0 : q.x + 1;
-    q.y += wrap ? 1 : 0;
-}
-
 // Inputs of one tile's 22 x 22 region (origin oy - 3, ox - 3), held in
 // registers between their global load and their LDS store so that the next
 // tile's loads overlap the current tile's layers.
@@ -782,11 +769,23 @@ struct TileInput {
     unsigned k[IN_PER_THREAD];
 };
 
-__device__ __forceinline__ bool input_in_grid(int p, int mx, int my, int oy, int ox)
+// Position of input i of this thread in the region; past its end the origin.
+__device__ __forceinline__ RegionPos input_pos(int i)
 {
-    const RegionPos q = region_pos<R0>(p < R0 * R0 ? p : 0);
+    const int p = threadIdx.x + 256 * i;
+    return region_pos<R0>(p < R0 * R0 ? p : 0);
+}
+
+// Whether the region of the tile at (oy, ox) lies inside the grid.
+__device__ __forceinline__ bool input_interior(int mx, int my, int oy, int ox)
+{
+    return oy >= 3 && ox >= 3 && oy + IT + 3 <= my && ox + IT + 3 <= mx;
+}
+
+__device__ __forceinline__ bool input_in_grid(RegionPos q, int mx, int my, int oy, int ox)
+{
     const int gy = oy - 3 + q.y, gx = ox - 3 + q.x;
-    return p < R0 * R0 && gy >= 0 && gy < my && gx >= 0 && gx < mx;
+    return gy >= 0 && gy < my && gx >= 0 && gx < mx;
 }
 
 // Issues the loads only (points outside the grid read element 0 and are
@@ -794,11 +793,13 @@ __device__ __forceinline__ bool input_in_grid(int p, int mx, int my, int oy, int
 __device__ __forceinline__ void load_tile_input(TileInput &in, const cd *__restrict__ r,
                                                 const unsigned *__restrict__ kh2, int mx, int my, int oy, int ox)
 {
+    const bool inside = input_interior(mx, my, oy, ox);
+    const long long origin = (long long)(oy - 3) * mx + (ox - 3);
 #pragma unroll
     for (int i = 0; i < IN_PER_THREAD; ++i) {
-        const int p = threadIdx.x + 256 * i;
-        const RegionPos q = region_pos<R0>(p < R0 * R0 ? p : 0);
-        const size_t j = input_in_grid(p, mx, my, oy, ox) ? (size_t)(oy - 3 + q.y) * mx + (ox - 3 + q.x) : 0;
+        const RegionPos q = input_pos(i);
+        const long long at = origin + (q.y * mx + q.x);
+        const size_t j = inside || input_in_grid(q, mx, my, oy, ox) ? (size_t)at : 0;
         in.r[i] = r[j];
         in.k[i] = kh2[j];
     }
@@ -806,153 +807,189 @@ __device__ __forceinline__ void load_tile_input(TileInput &in, const cd *__restr
 
 __device__ __forceinline__ void store_tile_input(InferLds &S, const TileInput &in, int mx, int my, int oy, int ox)
 {
+    const bool inside = input_interior(mx, my, oy, ox);
 #pragma unroll
     for (int i = 0; i < IN_PER_THREAD; ++i) {
         const int p = threadIdx.x + 256 * i;
-        const bool ok = input_in_grid(p, mx, my, oy, ox);
-        if (p < R0 * R0)
-            *reinterpret_cast<uint2 *>(&S.x0[p][0]) =
-                ok ? make_uint2(pack_bf16((float)in.r[i].re, (float)in.r[i].im), in.k[i]) : make_uint2(0u, 0u);
+        unsigned r = pack_bf16((float)in.r[i].re, (float)in.r[i].im), k = in.k[i];
+        if (!inside && !input_in_grid(input_pos(i), mx, my, oy, ox)) r = k = 0u;
+        if (p < R0 * R0) {
+            S.r0[p] = r;
+            S.k0[p] = k;
+        }
     }
 }
 
-// Layers of one 16 x 16 output tile (origin oy, ox) whose inputs are in
-// S.x0; leaves layer 3's per-tap products in S.z.  The weight fragments stay
-// in registers.  In layer 2 each wave takes two row tiles at a time so that
-// four independent MFMA accumulation chains interleave.  EDGE: the tile's layer-1 region reaches
-// outside the grid, so activations there are set to zero (interior tiles
-// skip the test).
-template <bool EDGE>
-__device__ __forceinline__ void net_layers(InferLds &S, int mx, int my, int oy, int ox, const bf8 (&w1)[4][2],
-                                           const bf8 (&w2)[9][2], const bf8 (&w3)[2], int wave)
+// The network's weight fragments, the same for every tile.
+struct NetFrags {
+    bf8 a1[2], m1[2], w2[9][2], w3[2];
+};
+
+// The 8 channels of a point that a lane's two accumulators hold, as the slots
+// 8 lg .. 8 lg + 7.
+__device__ __forceinline__ uint4 pack_slots(const float (&x0)[4], const float (&x1)[4])
 {
-    const int lane = threadIdx.x & 63;
-    const int li = lane & 15, lg = lane >> 4;
-    // layer-1 operand: lane group lg holds taps 4 lg .. 4 lg + 3; taps 9 ..
-    // 15 are zero padding whose weights are zero, so they may read any
-    // (finite) slot: the point itself
+    return make_uint4(pack_bf16(x0[0], x1[0]), pack_bf16(x0[1], x1[1]), pack_bf16(x0[2], x1[2]), pack_bf16(x0[3], x1[3]));
+}
+
+// Layers 2 and 3 of one wave: the points (y0 .. y0 + NR - 1, x = 0 .. 15) of the
+// 18 x 18 region, a row a column tile, and where SIDE the points 16 k .. 16 k +
+// 15 of the 36 of its last two columns.  A row's layer-1 values are read once for
+// the up to three rows whose taps they are (3 (NR + 2) reads for 9 NR k-steps), a
+// row of reads ahead of their products; the taps of a point are added in the
+// order 0 .. 8.  Each stage is issued for all column tiles before the next, so
+// that no product waits for the one before it.
+template <bool EDGE, int NR, bool SIDE>
+__device__ __forceinline__ void layers23(InferLds &S, const NetFrags &W, int mx, int my, int oy, int ox, int y0, int k)
+{
+    constexpr int NT = NR + (SIDE ? 1 : 0);   // column tiles
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    const f4 z = f4{0.f, 0.f, 0.f, 0.f};
+    f4 acc[NT][2];
+#pragma unroll
+    for (int r = 0; r < NT; ++r) acc[r][0] = acc[r][1] = z;
+    const int e = min(16 * k + li, 2 * R2 - 1), sy = e >> 1, sx = 16 + (e & 1);   // SIDE
+    const us8 *base = reinterpret_cast<const us8 *>(&S.x1[y0 * R1 + li][8 * lg]);
+    const us8 *side = reinterpret_cast<const us8 *>(&S.x1[sy * R1 + sx][8 * lg]);
+    us8 x[2][3], xs[9];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) x[0][dx] = base[dx * (XS / 8)];
+#pragma unroll
+    for (int yy = 0; yy < NR + 2; ++yy) {
+        if (yy + 1 < NR + 2) {
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) x[(yy + 1) & 1][dx] = base[((yy + 1) * R1 + dx) * (XS / 8)];
+        } else if (SIDE) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) xs[t] = side[((t / 3) * R1 + t % 3) * (XS / 8)];
+        }
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int r = yy - dy;
+                if (r < 0 || r >= NR) continue;
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    acc[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.w2[3 * dy + dx][nt], as_bf8(x[yy & 1][dx]),
+                                                                         acc[r][nt], 0, 0, 0);
+            }
+    }
+    if (SIDE) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                acc[NT - 1][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.w2[t][nt], as_bf8(xs[t]), acc[NT - 1][nt],
+                                                                          0, 0, 0);
+    }
+    // layer 3's operand: the accumulators as they are, zero outside the grid
+    uint4 b[NT];
+#pragma unroll
+    for (int r = 0; r < NT; ++r) {
+        const float c0[4] = {acc[r][0][0], acc[r][0][1], acc[r][0][2], acc[r][0][3]};
+        const float c1[4] = {acc[r][1][0], acc[r][1][1], acc[r][1][2], acc[r][1][3]};
+        b[r] = pack_slots(c0, c1);
+        if (EDGE) {
+            const int gy = oy - 1 + (r < NR ? y0 + r : sy), gx = ox - 1 + (r < NR ? li : sx);
+            if (!(gy >= 0 && gy < my && gx >= 0 && gx < mx)) b[r] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NT; ++r)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+            acc[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.w3[nt], as_bf8(b[r].x, b[r].y, b[r].z, b[r].w), z,
+                                                                 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < NT; ++r) {
+        float *zp = S.z[r < NR ? (y0 + r) * R2 + li : sy * R2 + sx];
+        if (r < NR || 16 * k + li < 2 * R2) *reinterpret_cast<f4 *>(zp + 4 * lg) = acc[r][0];
+    }
+    if (lg == 0) {
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {
+            float *zp = S.z[r < NR ? (y0 + r) * R2 + li : sy * R2 + sx];
+            if (r < NR || 16 * k + li < 2 * R2)
+                *reinterpret_cast<float2 *>(zp + 16) = make_float2(acc[r][1][0], acc[r][1][1]);
+        }
+    }
+}
+
+// Layer 1 on the column tiles rt, rt + 4, .. (NR of them) of the 20 x 20
+// region (origin -2), each stage issued for all of them before the next.
+template <bool EDGE, int NR>
+__device__ __forceinline__ void layer1(InferLds &S, const NetFrags &W, int mx, int my, int oy, int ox, int rt)
+{
+    const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    // operand: lane group lg holds taps 4 lg .. 4 lg + 3; taps 9 .. 15 are zero
+    // padding whose weights are zero, so they may read any (finite) slot: the
+    // point itself
     int off1[4];
 #pragma unroll
     for (int hh = 0; hh < 4; ++hh) {
         const int t = 4 * lg + hh;
-        off1[hh] = t < 9 ? 2 * ((t / 3 - 1) * R0 + (t % 3 - 1)) : 0;
+        off1[hh] = t < 9 ? (t / 3 - 1) * R0 + (t % 3 - 1) : 0;
     }
-    // layer 1 on the 20 x 20 region (origin -2), one row tile per iteration,
-    // two iterations interleaved
-#pragma unroll 2
-    for (int rt = wave; rt < NR1; rt += 4) {
-        const int p = rt * 16 + li;
-        const RegionPos P = region_pos<R1>(p);
-        const uint2 *base = reinterpret_cast<const uint2 *>(&S.x0[(P.y + 1) * R0 + P.x + 1][0]);
-        us8 ar, ak;   // the r~ and kappa~ operands
+    unsigned r[NR][4], k[NR][4];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const RegionPos P = region_pos<R1>((rt + 4 * i) * 16 + li);
+        const int at = (P.y + 1) * R0 + P.x + 1;
 #pragma unroll
         for (int hh = 0; hh < 4; ++hh) {
-            const uint2 v = base[off1[hh] / 2];
-            ar[2 * hh] = (unsigned short)(v.x & 0xFFFFu);
-            ar[2 * hh + 1] = (unsigned short)(v.x >> 16);
-            ak[2 * hh] = (unsigned short)(v.y & 0xFFFFu);
-            ak[2 * hh + 1] = (unsigned short)(v.y >> 16);
+            r[i][hh] = S.r0[at + off1[hh]];
+            k[i][hh] = S.k0[at + off1[hh]];
         }
-        float x[2][4];
+    }
+    f4 A[NR][2], M[NR][2];   // rows (Re, Im) of two channels
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const bf8 br = as_bf8(r[i][0], r[i][1], r[i][2], r[i][3]), bk = as_bf8(k[i][0], k[i][1], k[i][2], k[i][3]);
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            const f4 z = f4{0.f, 0.f, 0.f, 0.f}, one = f4{1.f, 1.f, 1.f, 1.f};
-            const f4 A = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(ar), w1[0][nt], z, 0, 0, 0);
-            const f4 Ap = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(ar), w1[1][nt], z, 0, 0, 0);
-            const f4 M = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(ak), w1[2][nt], one, 0, 0, 0);
-            const f4 Mp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(ak), w1[3][nt], z, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) x[nt][v] = fmaf(A[v], M[v], Ap[v] * Mp[v]);
-        }
-        const int pp = rt * 16 + 4 * lg;
-        RegionPos Q = region_pos<R1>(pp);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            unsigned val = pack_bf16(x[0][v], x[1][v]);
-            if (EDGE) {
-                const int gy = oy - 2 + Q.y, gx = ox - 2 + Q.x;
-                const bool in = gy >= 0 && gy < my && gx >= 0 && gx < mx;
-                val = in ? val : 0u;
-                region_next<R1>(Q);
-            }
-            *reinterpret_cast<unsigned *>(&S.x1[pp + v][2 * li]) = val;
+            A[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.a1[nt], br, f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            M[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W.m1[nt], bk, f4{1.f, 0.f, 1.f, 0.f}, 0, 0, 0);
         }
     }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        float x[2][4];
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int c = 0; c < 4; c += 2) {
+                x[nt][c] = fmaf(A[i][nt][c], M[i][nt][c], -(A[i][nt][c + 1] * M[i][nt][c + 1]));
+                x[nt][c + 1] = fmaf(A[i][nt][c + 1], M[i][nt][c], A[i][nt][c] * M[i][nt][c + 1]);
+            }
+        uint4 val = pack_slots(x[0], x[1]);
+        const int p = (rt + 4 * i) * 16 + li;
+        if (EDGE) {
+            const RegionPos P = region_pos<R1>(p);
+            const int gy = oy - 2 + P.y, gx = ox - 2 + P.x;
+            if (!(gy >= 0 && gy < my && gx >= 0 && gx < mx)) val = make_uint4(0u, 0u, 0u, 0u);
+        }
+        *reinterpret_cast<uint4 *>(&S.x1[p][8 * lg]) = val;
+    }
+}
+
+// Layers of one 16 x 16 output tile (origin oy, ox) whose inputs are in
+// S.r0, S.k0; leaves layer 3's per-tap products in S.z.  EDGE: the tile's layer-1
+// region reaches outside the grid, so activations there are set to zero
+// (interior tiles skip the test).
+template <bool EDGE>
+__device__ __forceinline__ void net_layers(InferLds &S, int mx, int my, int oy, int ox, const NetFrags &W, int wave)
+{
+    static_assert(NR1 == 25, "column tiles of layer 1: 6 a wave and one");
+    layer1<EDGE, 3>(S, W, mx, my, oy, ox, wave);
+    layer1<EDGE, 3>(S, W, mx, my, oy, ox, wave + 12);
+    if (wave == 1) layer1<EDGE, 1>(S, W, mx, my, oy, ox, 24);
     __syncthreads();
-    // layer 2 on the 18 x 18 region (origin -1)
-    for (int rt0 = wave; rt0 < NR2; rt0 += 8) {
-        f4 acc[2][2];
-        const us8 *base[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            int p = (rt0 + 4 * q) * 16 + li;
-            if (p >= R2 * R2) p = 0;
-            const RegionPos P = region_pos<R2>(p);
-            base[q] = reinterpret_cast<const us8 *>(&S.x1[(P.y + 1) * R1 + P.x + 1][8 * lg]);
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) acc[q][nt] = f4{0.f, 0.f, 0.f, 0.f};
-        }
-        us8 a[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) a[q] = base[q][(tap_dy(0) * R1 + tap_dx(0)) * (XS / 8)];
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            us8 an[2];
-            if (t + 1 < 9) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) an[q] = base[q][(tap_dy(t + 1) * R1 + tap_dx(t + 1)) * (XS / 8)];
-            }
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
-                    acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a[q]), w2[t][nt], acc[q][nt], 0, 0, 0);
-            if (t + 1 < 9) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) a[q] = an[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int rt = rt0 + 4 * q;
-            if (rt >= NR2) break;
-            const int pp = rt * 16 + 4 * lg;
-            RegionPos P = region_pos<R2>(pp);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                unsigned val = pack_bf16(acc[q][0][v], acc[q][1][v]);
-                if (EDGE) {
-                    const int gy = oy - 1 + P.y, gx = ox - 1 + P.x;
-                    const bool in = gy >= 0 && gy < my && gx >= 0 && gx < mx;
-                    val = in ? val : 0u;
-                    region_next<R2>(P);
-                }
-                *reinterpret_cast<unsigned *>(&S.x2[pp + v][2 * li]) = val;
-            }
-        }
-    }
-    __syncthreads();
-    // layer 3, first part: per-tap products Z_t(q) = W3[t] x2(q) at every
-    // point q of the 18 x 18 region (one k-step, columns 2 t + part; taps
-    // 0..7 in column tile 0, tap 8 in column tile 1), written to S.z, which
-    // reuses the layer-1 storage (dead once layer 2 has been read).  The
-    // second part, the 9-point gather N(p) = sum_t Z_t(p + d_t), follows the
-    // next barrier (layer3_gather).
-#pragma unroll 2
-    for (int rt = wave; rt < NR2; rt += 4) {
-        int p = rt * 16 + li;
-        if (p >= R2 * R2) p = 0;
-        const us8 a = *reinterpret_cast<const us8 *>(&S.x2[p][8 * lg]);
-        const f4 z = f4{0.f, 0.f, 0.f, 0.f};
-        const f4 Z0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a), w3[0], z, 0, 0, 0);
-        const f4 Z1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a), w3[1], z, 0, 0, 0);
-        const int pp = rt * 16 + 4 * lg;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            S.z[pp + v][li] = Z0[v];
-            if (li < 2) S.z[pp + v][16 + li] = Z1[v];
-        }
-    }
+    // layers 2 and 3 on the 18 x 18 region (origin -1): rows 5, 5, 4, 4 a wave,
+    // and the three column tiles of the last two columns
+    if (wave == 0) layers23<EDGE, 5, true>(S, W, mx, my, oy, ox, 0, 2);
+    else if (wave == 1) layers23<EDGE, 5, false>(S, W, mx, my, oy, ox, 5, 0);
+    else layers23<EDGE, 4, true>(S, W, mx, my, oy, ox, 4 * wave + 2, wave - 2);
 }
 
 // Layer 3, second part, for this thread's output point (py, px) of the tile:
@@ -977,7 +1014,14 @@ __device__ __forceinline__ float2 layer3_gather(const InferLds &S, int py, int p
 // contiguous range of tiles (ranges of neighbouring workgroups sit on one
 // XCD); the inputs of the next tile are loaded while the current one is
 // computed, and u is updated by all threads, one point each.
-__global__ __launch_bounds__(256) void k_net_apply(const cd *__restrict__ r, const unsigned *__restrict__ kh2,
+//
+// 520 matrix instructions a tile, 4160 cycles for a SIMD's two waves; the
+// stages' LDS latency and three barriers a tile are not all hidden behind them
+// (the weights in registers leave room for two waves a SIMD).  1023 x 1023:
+// 43 us a step; with the points in the rows (674 instructions a tile: a and m
+// twice in layer 1, idle column tiles in layer 2; x2 through LDS, a read for each
+// k-step) 69 us.
+__global__ __launch_bounds__(256, 2) void k_net_apply(const cd *__restrict__ r, const unsigned *__restrict__ kh2,
                                                    cd *__restrict__ u, int mx, int my, int tiles_x, int ntiles,
                                                    int per_block, const us8 *__restrict__ wfrag, double h2,
                                                    const int *__restrict__ stop)
@@ -986,17 +1030,17 @@ __global__ __launch_bounds__(256) void k_net_apply(const cd *__restrict__ r, con
     __shared__ InferLds S;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    bf8 w1[4][2], w2[9][2], w3[2];
+    NetFrags W;
 #pragma unroll
-    for (int ty = 0; ty < 4; ++ty)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) w1[ty][nt] = as_bf8(wfrag[(ty * 2 + nt) * 64 + lane]);
+    for (int nt = 0; nt < 2; ++nt) {
+        W.a1[nt] = as_bf8(wfrag[nt * 64 + lane]);
+        W.m1[nt] = as_bf8(wfrag[128 + nt * 64 + lane]);
+        W.w3[nt] = as_bf8(wfrag[256 + 1152 + nt * 64 + lane]);
+    }
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) w2[t][nt] = as_bf8(wfrag[512 + (t * 2 + nt) * 64 + lane]);
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) w3[nt] = as_bf8(wfrag[512 + 1152 + nt * 64 + lane]);
+        for (int nt = 0; nt < 2; ++nt) W.w2[t][nt] = as_bf8(wfrag[256 + (t * 2 + nt) * 64 + lane]);
     const int first = xcd_tile(blockIdx.x, gridDim.x) * per_block;
     const int last = min(first + per_block, ntiles);
     if (first >= last) return;
@@ -1017,16 +1061,16 @@ __global__ __launch_bounds__(256) void k_net_apply(const cd *__restrict__ r, con
         // the layer-1 region (origin -2, side 20) lies inside the grid
         const bool interior = oy >= 2 && ox >= 2 && oy + IT + 2 <= my && ox + IT + 2 <= mx;
         if (interior)
-            net_layers<false>(S, mx, my, oy, ox, w1, w2, w3, wave);
+            net_layers<false>(S, mx, my, oy, ox, W, wave);
         else
-            net_layers<true>(S, mx, my, oy, ox, w1, w2, w3, wave);
+            net_layers<true>(S, mx, my, oy, ox, W, wave);
         __syncthreads();
         if (mine) {
             const float2 yv = layer3_gather(S, py, px);
             u[j] = cd{uv.re + h2 * (double)yv.x, uv.im + h2 * (double)yv.y};
         }
-        // the next tile's layers start after its input barrier, so S.z (the
-        // layer-1 storage) is not overwritten before it is read here
+        // the next tile's layers 2 and 3 start two barriers on, so S.z is not
+        // overwritten before it is read here
     }
 }
 
@@ -1034,7 +1078,7 @@ __global__ __launch_bounds__(256) void k_net_apply(const cd *__restrict__ r, con
 static int slot_channel(int s) { return (16 * (s & 1) + (s >> 1)) / 2; }
 static int slot_part(int s) { return (s >> 1) & 1; }
 
-// MFMA B-operand fragments of the three layers from the complex weights
+// MFMA A-operand fragments of the three layers from the complex weights
 // (rounded to BF16): 64 lanes x 8 values per fragment, in the order read by
 // k_net_apply.
 void pack_net_mfma(const float *w, unsigned short *out)
@@ -1046,26 +1090,17 @@ void pack_net_mfma(const float *w, unsigned short *out)
     };
     auto bf = [](float f) { return (unsigned short)bf16_bits(f); };
     size_t o = 0;
-    // layer 1, k = 2 tap + part (k < 18); four products per column j (part
-    // po of channel j / 2): type 0 A = part po of a, type 1
-    // A' = (-Im a, Re a)[po] (both from the r~ weights), type 2 Re m, type 3
-    // Im m (both from the kappa~ weights)
-    for (int ty = 0; ty < 4; ++ty)
+    // layer 1, k = 2 tap + part (k < 18), row j part j % 2 of channel j / 2: of
+    // a (from the r~ weights), then of m (from the kappa~ weights)
+    for (int in = 0; in < 2; ++in)
         for (int nt = 0; nt < 2; ++nt)
             for (int lane = 0; lane < 64; ++lane)
                 for (int e = 0; e < 8; ++e) {
                     const int k = 8 * (lane / 16) + e, j = 16 * nt + lane % 16;
                     float v = 0.f;
                     if (k < 18) {
-                        const int t = k / 2, pi = k % 2, oc = j / 2, po = j % 2;
-                        const int idx = (t * 16 + oc) * 2 + (ty < 2 ? 0 : 1);
-                        const float re = W(NET_W1, idx, 0), im = W(NET_W1, idx, 1);
-                        switch (ty) {
-                        case 0: v = real_block(re, im, po, pi); break;
-                        case 1: v = po == 0 ? -real_block(re, im, 1, pi) : real_block(re, im, 0, pi); break;
-                        case 2: v = real_block(re, im, 0, pi); break;
-                        default: v = real_block(re, im, 1, pi); break;
-                        }
+                        const int idx = ((k / 2) * 16 + j / 2) * 2 + in;
+                        v = real_block(W(NET_W1, idx, 0), W(NET_W1, idx, 1), j % 2, k % 2);
                     }
                     out[o++] = bf(v);
                 }
@@ -1078,7 +1113,7 @@ void pack_net_mfma(const float *w, unsigned short *out)
                     const int idx = (t * 16 + oc) * 16 + i;
                     out[o++] = bf(real_block(W(NET_W2, idx, 0), W(NET_W2, idx, 1), po, pi));
                 }
-    // layer 3: column c = 16 nt + lane % 16 is part c % 2 of tap c / 2 (< 9)
+    // layer 3: row c = 16 nt + lane % 16 is part c % 2 of tap c / 2 (< 9)
     for (int nt = 0; nt < 2; ++nt)
         for (int lane = 0; lane < 64; ++lane)
             for (int e = 0; e < 8; ++e) {
@@ -1094,7 +1129,7 @@ void pack_net_mfma(const float *w, unsigned short *out)
             }
 }
 
-size_t net_mfma_frag_count() { return (size_t)(8 + 18 + 2) * 64 * 8; }
+size_t net_mfma_frag_count() { return (size_t)(4 + 18 + 2) * 64 * 8; }
 
 // kappa h^2 as packed BF16 complex
 __global__ __launch_bounds__(256) void k_kappa_h2(const cd *__restrict__ q, double k02, double h2, size_t N,
