@@ -695,19 +695,19 @@ __global__ __launch_bounds__(NT) void k_sweep2_3d(const cx<T> *__restrict__ u, c
         const bool in = t < CH * CW && ax >= 0 && ax < mxc && ay >= 0 && ay < myc;
         offc[i] = in ? (unsigned)(ay * mxc + ax) * (unsigned)sizeof(cx<T>) : BUF_OOB;
     }
-    auto fetch_coarse = [&](int a) {
+    auto fetch_coarse = [&](int a, cx<T> (&dst)[NCL]) {
         const bool ain = a >= 0 && a < mzc;
         const size_t cpl = (size_t)mxc * myc;
         const auto rc = buf_rsrc(ec + (ain ? (size_t)a * cpl : 0), ain ? (unsigned)(cpl * sizeof(cx<T>)) : 0u);
 #pragma unroll
-        for (int i = 0; i < NCL; ++i) creg[i] = ld_buf<T>(rc, offc[i]);
+        for (int i = 0; i < NCL; ++i) dst[i] = ld_buf<T>(rc, offc[i]);
     };
-    auto store_coarse = [&](int a) {
+    auto store_coarse = [&](int a, const cx<T> (&src)[NCL]) {
         cx<T> *dst = &cs[a & (NCS - 1)][0][0];
 #pragma unroll
         for (int i = 0; i < NCL; ++i) {
             const int t = threadIdx.x + NT * i;
-            if (t < CH * CW) dst[t] = creg[i];
+            if (t < CH * CW) dst[t] = src[i];
         }
     };
     // the z step of the interpolation for fine plane z: ezs = wz0 c(az) + wz1 c(az + 1)
@@ -771,20 +771,21 @@ __global__ __launch_bounds__(NT) void k_sweep2_3d(const cx<T> *__restrict__ u, c
     // an iteration, for the next stage-0 plane) after a barrier.
     int a_reg = 0;
     bool c_pending = false;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) pu[k] = pb[k] = pq[k] = zero;
+    if (!ZERO) fetch_u(z0 - 2);
     if (PROL) {
         const int Alo = ((z0 - 1) >> 1) - 1;
-        for (int a = Alo; a <= ((z0 + 1) >> 1); ++a) {
-            fetch_coarse(a);
-            store_coarse(a);
-        }
-        a_reg = (z0 + 1) >> 1;
+        a_reg = (z0 + 1) >> 1;   // = Alo + 2
+        cx<T> first[3][NCL];     // all on their way before the first is waited for
+#pragma unroll
+        for (int i = 0; i < 3; ++i) fetch_coarse(Alo + i, first[i]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) store_coarse(Alo + i, first[i]);
         lds_barrier();
         combine_z(z0 - 2);
         lds_barrier();
     }
-#pragma unroll
-    for (int k = 0; k < NS; ++k) pu[k] = pb[k] = pq[k] = zero;
-    if (!ZERO) fetch_u(z0 - 2);
 
     cx<T> a0[NS], a1[NS], a2[NS];   // stage 0 at planes z - 2, z - 1, z
     cx<T> c0[NS], c1[NS], c2[NS];   // stage 1 at planes z - 3, z - 2, z - 1
@@ -807,11 +808,11 @@ __global__ __launch_bounds__(NT) void k_sweep2_3d(const cx<T> *__restrict__ u, c
         }
         if (PROL) {
             if (c_pending) {   // fetched last iteration; combined from the next iteration on
-                store_coarse(a_reg);
+                store_coarse(a_reg, creg);
                 c_pending = false;
             }
             if (((z + 4) >> 1) > a_reg) {
-                fetch_coarse(++a_reg);
+                fetch_coarse(++a_reg, creg);
                 c_pending = true;
             }
         }
@@ -1008,25 +1009,13 @@ void launch_sweep3d_fused(bool zero2, const LevelGeom &g, const Stencil<T> &P, c
                                tz, stop);
     }
 }
-// Tile of the fused two-sweep 3D kernel (its LDS and registers grow with
-// the tile), by FFMG_TUNE_SWEEP3D variant: 0 the default per type (64 x 8
-// FP32, 64 x 4 FP64), 2 twice the rows, 3 half the width and twice the rows
-// (fewer halo columns per output point) for the interpolating pass and the
-// default for the others (measured: the narrow tile pays off where the pass
-// also stages coarse planes).
-template <typename T> constexpr int sweep2_rows(int shape)
-{
-    return sizeof(T) == 4 ? (shape == 0 ? 8 : 16) : (shape == 0 ? 4 : 8);
-}
-constexpr int sweep2_width(int shape) { return shape == 3 ? 32 : 64; }
-
 template <typename T, int TY, int TXW, int NT = 256>
 static void launch_sweep2_3d_tile(const LevelGeom &g, const Stencil<T> &P, const cx<T> *u, const cx<T> *ec,
                                   const cx<T> *b, const cx<T> *q, cx<T> *out, hipStream_t s, bool finest,
-                                  const int *stop, bool zero)
+                                  const int *stop, bool zero, long min_blocks = MIN_BLOCKS_SWEEP3)
 {
     const int tx = (g.m[0] + TXW - 1) / TXW, ty = (g.m[1] + TY - 1) / TY;
-    const int tz = planes_per_block((long)tx * ty, g.m[2], TZ3, MIN_BLOCKS_SWEEP3);
+    const int tz = planes_per_block((long)tx * ty, g.m[2], TZ3, min_blocks);
     const int nb = tx * ty * ((g.m[2] + tz - 1) / tz);
     if (zero) {
         // u is not read: any valid pointer serves the unused loads' base
@@ -1053,16 +1042,42 @@ static void launch_sweep2_3d_tile(const LevelGeom &g, const Stencil<T> &P, const
     }
 }
 
+// Tile of the fused two-sweep 3D kernel (its LDS and registers grow with the
+// tile, the halo's share of the work falls), by FFMG_TUNE_SWEEP3D variant and
+// the number of points.  A thread takes whole columns of the tile and its halo,
+// so what counts is how many column slots of the block an output column costs,
+// and how many planes a block marches ahead of its output.
+//   FP64: 32 x 16 (1.5 slots a column, 512 blocks at least) against 64 x 4 (3
+//   slots, 1024 blocks), interpolating and plain pass: 127^3 33 and 28 us
+//   against 50 and 32, 511^3 2.04 and 1.94 ms against 2.60 and 2.00.
+//   FP32: 32 x 16 where the pass interpolates (it also stages coarse planes),
+//   else 64 x 8.
+// Small levels are latency bound: up to 2^17 points small tiles (12 x 12, one
+// column a thread: 31^3 interpolating 7.3 us against 9.1 and 15^3 6.2 against
+// 9.3 with 64 x 4; FP64), up to 2^20 the large tile with a column and a half a
+// thread (63^3 10.6 us against 20.2).
 template <typename T>
 void launch_sweep2_3d(const LevelGeom &g, const Stencil<T> &P, const cx<T> *u, const cx<T> *ec, const cx<T> *b,
                       const cx<T> *q, cx<T> *out, hipStream_t s, bool finest, const int *stop, bool zero, int shape)
 {
-    if (shape == 2)
-        launch_sweep2_3d_tile<T, sweep2_rows<T>(2), sweep2_width(2)>(g, P, u, ec, b, q, out, s, finest, stop, zero);
-    else if ((shape == 3 || shape == 4) && ec && !zero)
-        launch_sweep2_3d_tile<T, sweep2_rows<T>(3), sweep2_width(3)>(g, P, u, ec, b, q, out, s, finest, stop, zero);
-    else
-        launch_sweep2_3d_tile<T, sweep2_rows<T>(0), sweep2_width(0)>(g, P, u, ec, b, q, out, s, finest, stop, zero);
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr size_t SMALL = (size_t)1 << 17, MEDIUM = (size_t)1 << 20;
+    const size_t N = g.N();
+    const bool narrow = ec && !zero && (shape == 3 || shape == 4);
+    if (shape == 2) {
+        launch_sweep2_3d_tile<T, F64 ? 8 : 16, 64>(g, P, u, ec, b, q, out, s, finest, stop, zero);
+    } else if (F64 && shape == 3 && narrow) {
+        launch_sweep2_3d_tile<T, F64 ? 8 : 16, 32>(g, P, u, ec, b, q, out, s, finest, stop, zero);
+    } else if (F64 || narrow) {
+        if (N < SMALL)
+            launch_sweep2_3d_tile<T, 12, 12>(g, P, u, ec, b, q, out, s, finest, stop, zero, 256);
+        else if (N < MEDIUM)
+            launch_sweep2_3d_tile<T, 16, 32, 512>(g, P, u, ec, b, q, out, s, finest, stop, zero, 256);
+        else
+            launch_sweep2_3d_tile<T, 16, 32>(g, P, u, ec, b, q, out, s, finest, stop, zero, F64 ? 512 : MIN_BLOCKS_SWEEP3);
+    } else {
+        launch_sweep2_3d_tile<T, 8, 64>(g, P, u, ec, b, q, out, s, finest, stop, zero);
+    }
 }
 template void launch_sweep2_3d<double>(const LevelGeom &, const Stencil<double> &, const cd *, const cd *, const cd *,
                                        const cd *, cd *, hipStream_t, bool, const int *, bool, int);
@@ -1258,13 +1273,13 @@ __global__ __launch_bounds__(256) void k_resid_restrict3d(const cx<T> *__restric
         const bool in = t < RFH * RFW && gx < mx && gy < my;
         offr[k] = in ? (unsigned)(gy * mx + gx) * (unsigned)sizeof(cx<T>) : BUF_OOB;
     }
-    auto issue_u = [&](int fz) {
+    auto issue_u = [&](int fz, cx<T> (&un)[NUL]) {
         const bool zin = fz >= 0 && fz < mz;
         const auto ru = buf_rsrc(u + (zin ? (size_t)fz * plane : 0), zin ? pbytes : 0u);
 #pragma unroll
         for (int k = 0; k < NUL; ++k) un[k] = ld_buf<T>(ru, offu[k]);
     };
-    auto store_u = [&](int fz) {
+    auto store_u = [&](int fz, const cx<T> (&un)[NUL]) {
         cx<T> *dst = &us[(fz + 3) % 3][0][0];
 #pragma unroll
         for (int k = 0; k < NUL; ++k) {
@@ -1283,14 +1298,17 @@ __global__ __launch_bounds__(256) void k_resid_restrict3d(const cx<T> *__restric
         }
     };
     const int fz_first = 2 * K0, fz_last = 2 * K1;        // fine residual planes of the block
-    issue_u(fz_first - 1);
-    store_u(fz_first - 1);
-    issue_u(fz_first);
-    store_u(fz_first);
-    issue_u(fz_first + 1);
-    issue_bq(fz_first);
+    {   // the first planes all on their way before one is waited for
+        cx<T> u0[NUL], u1[NUL];
+        issue_u(fz_first - 1, u0);
+        issue_u(fz_first, u1);
+        issue_u(fz_first + 1, un);
+        issue_bq(fz_first);
+        store_u(fz_first - 1, u0);
+        store_u(fz_first, u1);
+    }
     for (int fz = fz_first; fz <= fz_last; ++fz) {
-        store_u(fz + 1);
+        store_u(fz + 1, un);
         cx<T> bc_[NRL], qc_[NRL];
 #pragma unroll
         for (int k = 0; k < NRL; ++k) {
@@ -1299,7 +1317,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict3d(const cx<T> *__restric
         }
         lds_barrier();
         if (fz < fz_last) {
-            issue_u(fz + 2);
+            issue_u(fz + 2, un);
             issue_bq(fz + 1);
         }
         // fine residual plane fz on the RFW x RFH region (0 outside the grid)
