@@ -150,32 +150,57 @@ __global__ __launch_bounds__(256) void k_ref_index(const cd *__restrict__ v, int
 // 1/(A sqrt k), where A^2 = (p_r^2 + p_{r+1}^2 - 2 c p_r p_{r+1}) / (1 - c^2),
 // c = 1 - h~^2 k^2 / 2, is the squared free-wave amplitude at the reference
 // node r (the invariant of the free recurrence), A with Re A > 0.
+//
+// Bound by the recurrence's chain.  It runs twice, up to node r + 1 for the
+// amplitude and over the axis with the scaled values as the only stores, with V
+// read from LDS (staged TF_CHUNK nodes at a time by the one wave of a block): with
+// V from memory, and the unscaled values stored and read back to be scaled, 255
+// nodes took 105 us.
+constexpr int TF_CHUNK = 256;
+
 __global__ __launch_bounds__(64) void k_test_functions(const cd *__restrict__ v, int m, cd ht2,
                                                        const double *__restrict__ kk, int M,
                                                        const int *__restrict__ ref, cd *__restrict__ out)
 {
+    __shared__ cd vs[TF_CHUNK];
     const int t = blockIdx.x * 64 + threadIdx.x;
-    if (t >= M) return;
-    const double k = kk[t];
-    cd *p = out + (size_t)t * m;
+    const bool own = t < M;
+    const double k = kk[own ? t : 0];
+    cd *p = out + (size_t)(own ? t : 0) * m;
     const cd k2 = cd{k * k, 0.0};
-    cd prev = cd{0.0, 0.0}, cur = cd{1.0, 0.0};
-    p[0] = cur;
-    for (int i = 0; i + 1 < m; ++i) {
-        cd g = ht2 * (2.0 * v[i] - k2);
-        cd nxt = (2.0 * cur - prev) + g * cur;
-        p[i + 1] = nxt;
-        prev = cur;
-        cur = nxt;
-    }
+    // the recurrence over nodes 0 .. last, each handed to `node`
+    auto march = [&](int last, auto node) {
+        cd prev = cd{0.0, 0.0}, cur = cd{1.0, 0.0};
+        node(0, cur);
+        for (int i0 = 0; i0 < last; i0 += TF_CHUNK) {
+            const int n = min(TF_CHUNK, last - i0);
+            __syncthreads();
+            for (int i = threadIdx.x; i < n; i += 64) vs[i] = v[i0 + i];
+            __syncthreads();
+#pragma unroll 4
+            for (int i = 0; i < n; ++i) {
+                cd g = ht2 * (2.0 * vs[i] - k2);
+                cd nxt = (2.0 * cur - prev) + g * cur;
+                prev = cur;
+                cur = nxt;
+                node(i0 + i + 1, cur);
+            }
+        }
+    };
     const int r = ref[0];
+    cd pr = cd{0.0, 0.0}, pn = pr;
+    march(r + 1, [&](int i, cd x) {
+        if (i == r) pr = x;
+        pn = x;
+    });
     const cd c = cd{1.0, 0.0} - 0.5 * (ht2 * k2);
-    const cd pr = p[r], pn = p[r + 1];
     const cd num = (pr * pr + pn * pn) - 2.0 * (c * (pr * pn));
     const cd a2 = num * recip(cd{1.0, 0.0} - c * c);
     const cd A = csqrt_pos(a2);
     const cd sc = recip(sqrt(k) * A);
-    for (int i = 0; i < m; ++i) p[i] = sc * p[i];
+    march(m - 1, [&](int i, cd x) {
+        if (own) p[i] = sc * x;
+    });
 }
 
 // rho = phi - V12 u (the contraction operand, x fastest), and per-block
