@@ -13,15 +13,15 @@
 // min |sqrt(n_0) e_1 - H y| is solved on the device by one thread with
 // complex Givens rotations (FP64), and u += sum_j (y_j / sqrt(n_j)) Z_j.
 //
-// Kernels (one point per thread, grid-stride, neighbours read from global
-// memory): the residual with its partial norm; A Z_0 with the partial
-// product <Z_0, A Z_0>; for j = 1 .. m - 1 one pass that forms Z_j from
-// W = A Z_{j-1} and Z_0 .. Z_{j-1} (at the point and at its stencil
-// neighbours, so that the orthogonalisation needs no pass of its own) and
-// applies A to it, with the partial |Z_j|^2 and <Z_i, A Z_j>; the norm of
-// Z_m (not stored); the small problem and the update.  Each pass adds the
-// previous passes' partial sums itself, in block order (every block the same
-// sums, so no pass waits on a one-block kernel): m + 3 launches per step.
+// Kernels (a point a thread, tiles of 64 x 8 points in 2D): the residual and
+// A Z_0 with the partial |Z_0|^2 and <Z_0, A Z_0>, as one pass or two; for
+// j = 1 .. m - 1 one pass that forms Z_j from W = A Z_{j-1} and Z_0 .. Z_{j-1}
+// (on the tile and around it, through LDS in 2D, so that the orthogonalisation
+// needs no pass of its own) and applies A to it, with the partial |Z_j|^2 and
+// <Z_i, A Z_j>; the norm of Z_m (not stored); the small problem and the update.
+// Each pass adds the previous passes' partial sums itself, in block order (every
+// block the same sums, so no pass waits on a one-block kernel): m + 2 or m + 3
+// launches per step.
 // The reference kernel path (a pass per product and one for the
 // orthogonalisation, each finished by a one-block kernel: 4 m + 3 launches)
 // computes the same values in the same order, so both give the same bits.
@@ -71,10 +71,54 @@ __device__ __forceinline__ cx<T> apply_at_f(const Stencil<T> &P, ZAt zat, cx<T> 
     return apply_point(P, L, zc, qj);
 }
 
+// The 2D product where the coordinates of point j are known.
+template <typename T, typename ZAt>
+__device__ __forceinline__ cx<T> apply_xy_f(const Stencil<T> &P, ZAt zat, cx<T> zc, cx<T> qj, size_t j, int ix, int iy)
+{
+    const cx<T> zero = {T(0), T(0)};
+    const size_t sy = (size_t)P.mx;
+    cx<T> w = ix > 0 ? zat(j - 1) : zero, e = ix < P.mx - 1 ? zat(j + 1) : zero;
+    cx<T> s = iy > 0 ? zat(j - sy) : zero, n = iy < P.my - 1 ? zat(j + sy) : zero;
+    return apply_point(P, lap_xy(P, zc, w, e, s, n), zc, qj);
+}
+
+template <typename T, int DIM>
+__device__ __forceinline__ cx<T> apply_pt(const Stencil<T> &P, const cx<T> *__restrict__ z, cx<T> qj, size_t j, int ix,
+                                          int iy)
+{
+    if constexpr (DIM == 2) return apply_xy_f<T>(P, [&](size_t k) { return z[k]; }, z[j], qj, j, ix, iy);
+    else return apply_at_f<T, DIM>(P, [&](size_t k) { return z[k]; }, z[j], qj, j);
+}
+
 template <typename T, int DIM>
 __device__ __forceinline__ cx<T> apply_at(const Stencil<T> &P, const cx<T> *__restrict__ z, cx<T> qj, size_t j)
 {
     return apply_at_f<T, DIM>(P, [&](size_t k) { return z[k]; }, z[j], qj, j);
+}
+
+// The points of this thread in a pass over a level: in 2D the block's tiles of
+// GM_TX x GM_TY points, a point a thread, else every gridDim.x-th run of GM_BT
+// points.  Every pass of a step takes them alike, so their sums agree between
+// the default and the reference passes.  visit(j, ix, iy, own): own is false for
+// a thread without a point in the tile (2D only; j is then 0).
+constexpr int GM_TX = 64, GM_TY = GM_BT / GM_TX;
+__host__ __device__ constexpr int gm_tiles_x(int mx) { return (mx + GM_TX - 1) / GM_TX; }
+__host__ __device__ constexpr int gm_tiles(int mx, int my) { return gm_tiles_x(mx) * ((my + GM_TY - 1) / GM_TY); }
+template <int DIM, typename T, typename F>
+__device__ __forceinline__ void for_points(const Stencil<T> &P, size_t N, F visit)
+{
+    if constexpr (DIM == 2) {
+        const int tx = gm_tiles_x(P.mx), nt = gm_tiles(P.mx, P.my);
+        for (int tile = blockIdx.x; tile < nt; tile += gridDim.x) {
+            const int ix = (tile % tx) * GM_TX + (int)(threadIdx.x % GM_TX);
+            const int iy = (tile / tx) * GM_TY + (int)(threadIdx.x / GM_TX);
+            const bool own = ix < P.mx && iy < P.my;
+            visit(own ? (size_t)iy * P.mx + ix : 0, ix, iy, own);
+        }
+    } else {
+        for (size_t j = (size_t)blockIdx.x * GM_BT + threadIdx.x; j < N; j += (size_t)gridDim.x * GM_BT)
+            visit(j, 0, 0, true);
+    }
 }
 
 // Sums of NV doubles per thread of a block into parts[slot[v] * GM_BLOCKS +
@@ -235,17 +279,18 @@ __global__ __launch_bounds__(GM_BT) void k_gm_resid(cx<T> *__restrict__ u, int z
 {
     if (stop && *stop) return;
     double acc[1] = {0.0};
-    for (size_t j = (size_t)blockIdx.x * GM_BT + threadIdx.x; j < N; j += (size_t)gridDim.x * GM_BT) {
+    for_points<DIM>(P, N, [&](size_t j, int ix, int iy, bool own) {
+        if (!own) return;
         cx<T> r = b[j];
         if (zero) {
             u[j] = cx<T>{T(0), T(0)};
         } else {
-            cx<T> Au = apply_at<T, DIM>(P, u, q[j], j);
+            cx<T> Au = apply_pt<T, DIM>(P, u, q[j], j, ix, iy);
             r = cx<T>{r.re - Au.re, r.im - Au.im};
         }
         z0[j] = r;
         acc[0] += (double)r.re * (double)r.re + (double)r.im * (double)r.im;
-    }
+    });
     const int slot[1] = {0};
     block_partials<1>(acc, slot, parts);
 }
@@ -263,8 +308,9 @@ __global__ __launch_bounds__(GM_BT) void k_gm_apply_dots(cx<T> *__restrict__ Z, 
     double acc[2 * NJ];
 #pragma unroll
     for (int v = 0; v < 2 * NJ; ++v) acc[v] = 0.0;
-    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
-        cx<T> Wp = apply_at<T, DIM>(P, zj, q[p], p);
+    for_points<DIM>(P, N, [&](size_t p, int ix, int iy, bool own) {
+        if (!own) return;
+        cx<T> Wp = apply_pt<T, DIM>(P, zj, q[p], p, ix, iy);
         w[p] = Wp;
         const double wr = Wp.re, wi = Wp.im;
 #pragma unroll
@@ -273,11 +319,57 @@ __global__ __launch_bounds__(GM_BT) void k_gm_apply_dots(cx<T> *__restrict__ Z, 
             acc[2 * i] += (double)zi.re * wr + (double)zi.im * wi;       // conj(z_i) w
             acc[2 * i + 1] += (double)zi.re * wi - (double)zi.im * wr;
         }
-    }
+    });
     int slot[2 * NJ];
 #pragma unroll
     for (int v = 0; v < 2 * NJ; ++v) slot[v] = NSLOT_D + 2 * (j * GMRES_MAX_M) + v;
     block_partials<2 * NJ>(acc, slot, parts);
+}
+
+// The first two passes in one: Z_0 = b - A u (formed at the point and its
+// neighbours; from a zero guess b itself, and u is set to 0), W = A Z_0, the
+// partial |Z_0|^2 and <Z_0, W>.  The values and partial sums of k_gm_resid
+// followed by k_gm_apply_dots<1>.
+template <typename T, int DIM, bool ZERO>
+__global__ __launch_bounds__(GM_BT) void k_gm_resid_dots(cx<T> *__restrict__ u, const cx<T> *__restrict__ b,
+                                                         const cx<T> *__restrict__ q, cx<T> *__restrict__ z0,
+                                                         cx<T> *__restrict__ w, Stencil<T> P, size_t N,
+                                                         double *__restrict__ parts, const int *__restrict__ stop)
+{
+    if (stop && *stop) return;
+    double acc[3] = {0.0, 0.0, 0.0};
+    for_points<DIM>(P, N, [&](size_t j, int ix, int iy, bool own) {
+        if (!own) return;
+        const cx<T> qj = q[j];
+        cx<T> zc, Wp;
+        if constexpr (ZERO) {
+            zc = b[j];
+            Wp = apply_pt<T, DIM>(P, b, qj, j, ix, iy);
+            u[j] = cx<T>{T(0), T(0)};
+        } else {
+            // u is read at up to two points' distance: not written in this pass
+            auto resid = [&](size_t k, int kx, int ky, cx<T> qk) {
+                const cx<T> r = b[k], Au = apply_pt<T, DIM>(P, u, qk, k, kx, ky);
+                return cx<T>{r.re - Au.re, r.im - Au.im};
+            };
+            const cx<T> zero = {T(0), T(0)};
+            const size_t sy = (size_t)P.mx;
+            zc = resid(j, ix, iy, qj);
+            const cx<T> zw = ix > 0 ? resid(j - 1, ix - 1, iy, q[j - 1]) : zero;
+            const cx<T> ze = ix < P.mx - 1 ? resid(j + 1, ix + 1, iy, q[j + 1]) : zero;
+            const cx<T> zs = iy > 0 ? resid(j - sy, ix, iy - 1, q[j - sy]) : zero;
+            const cx<T> zn = iy < P.my - 1 ? resid(j + sy, ix, iy + 1, q[j + sy]) : zero;
+            Wp = apply_point(P, lap_xy(P, zc, zw, ze, zs, zn), zc, qj);
+        }
+        z0[j] = zc;
+        w[j] = Wp;
+        const double wr = Wp.re, wi = Wp.im;
+        acc[0] += (double)zc.re * (double)zc.re + (double)zc.im * (double)zc.im;
+        acc[1] += (double)zc.re * wr + (double)zc.im * wi;
+        acc[2] += (double)zc.re * wi - (double)zc.im * wr;
+    });
+    const int slot[3] = {0, NSLOT_D, NSLOT_D + 1};
+    block_partials<3>(acc, slot, parts);
 }
 
 // The coefficients of the orthogonalisation of A Z_{J-1} against Z_0 ..
@@ -349,9 +441,8 @@ __global__ __launch_bounds__(GM_BT) void k_gm_orth_apply(cx<T> *__restrict__ Z, 
     double acc[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
-        const cx<T> zc = orth_at<T, J>(wprev, Z, N, g, p);
-        const cx<T> Wp = apply_at_f<T, DIM>(P, [&](size_t k) { return orth_at<T, J>(wprev, Z, N, g, k); }, zc, q[p], p);
+    // Z_J, A Z_J and the sums at point p from Z_J there and A Z_J
+    auto add = [&](size_t p, cx<T> zc, cx<T> Wp) {
         zJ[p] = zc;
         wout[p] = Wp;
         acc[0] += (double)zc.re * (double)zc.re + (double)zc.im * (double)zc.im;
@@ -362,6 +453,39 @@ __global__ __launch_bounds__(GM_BT) void k_gm_orth_apply(cx<T> *__restrict__ Z, 
             acc[1 + 2 * i] += (double)zi.re * wr + (double)zi.im * wi;
             acc[2 + 2 * i] += (double)zi.re * wi - (double)zi.im * wr;
         }
+    };
+    if constexpr (DIM == 2) {
+        // Z_J of the tile and a point around it through LDS (0 outside the grid),
+        // formed once a point: with each point forming its neighbours' 1023^2 took
+        // 16.6 us (J = 1) and 21.0 (J = 2), now 14.0 and 15.8, 511^2 8.2 and 9.7, now
+        // 7.4 and 8.7 (FP32)
+        constexpr int HX = GM_TX + 2, HY = GM_TY + 2;
+        __shared__ cx<T> zs[HY * HX];
+        const cx<T> zero = {T(0), T(0)};
+        const int t = threadIdx.x, lx = t % GM_TX, ly = t / GM_TX;
+        // the point around the tile that threads below 2 (GM_TX + GM_TY) add
+        const bool ring = t < 2 * (GM_TX + GM_TY);
+        const int k = t < 2 * GM_TX ? t : t - 2 * GM_TX;
+        const int hx = t < 2 * GM_TX ? k % GM_TX : (k < GM_TY ? -1 : GM_TX);
+        const int hy = t < 2 * GM_TX ? (k < GM_TX ? -1 : GM_TY) : k % GM_TY;
+        for_points<DIM>(P, N, [&](size_t p, int ix, int iy, bool own) {
+            const cx<T> zc = own ? orth_at<T, J>(wprev, Z, N, g, p) : zero;
+            cx<T> zh = zero;
+            const int gx = ix - lx + hx, gy = iy - ly + hy;
+            if (ring && gx >= 0 && gx < P.mx && gy >= 0 && gy < P.my)
+                zh = orth_at<T, J>(wprev, Z, N, g, (size_t)gy * P.mx + gx);
+            __syncthreads();   // every thread is past its reads of the tile before
+            cx<T> *c = zs + (ly + 1) * HX + lx + 1;
+            *c = zc;
+            if (ring) zs[(hy + 1) * HX + hx + 1] = zh;
+            __syncthreads();
+            if (own) add(p, zc, apply_point(P, lap_xy(P, zc, c[-1], c[1], c[-HX], c[HX]), zc, q[p]));
+        });
+    } else {
+        for_points<DIM>(P, N, [&](size_t p, int, int, bool) {
+            const cx<T> zc = orth_at<T, J>(wprev, Z, N, g, p);
+            add(p, zc, apply_at_f<T, DIM>(P, [&](size_t k) { return orth_at<T, J>(wprev, Z, N, g, k); }, zc, q[p], p));
+        });
     }
     int slot[NV];
     slot[0] = J;
@@ -372,9 +496,9 @@ __global__ __launch_bounds__(GM_BT) void k_gm_orth_apply(cx<T> *__restrict__ Z, 
 
 // The last Arnoldi vector's partial norm: n_M = |A Z_{M-1} - sum_{i<M} g_i
 // Z_i|^2 (the vector itself is not needed).
-template <typename T, int M>
+template <typename T, int DIM, int M>
 __global__ __launch_bounds__(GM_BT) void k_gm_orth_norm(const cx<T> *__restrict__ Z, const cx<T> *__restrict__ wprev,
-                                                      size_t N, double *__restrict__ S, double *__restrict__ parts,
+                                                        Stencil<T> P, size_t N, double *__restrict__ S, double *__restrict__ parts,
                                                       const int *__restrict__ stop)
 {
     if (stop && *stop) return;
@@ -383,10 +507,11 @@ __global__ __launch_bounds__(GM_BT) void k_gm_orth_norm(const cx<T> *__restrict_
     cx<T> g[M];
     orth_coeffs<T, M>(Sl, g);
     double acc[1] = {0.0};
-    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
+    for_points<DIM>(P, N, [&](size_t p, int, int, bool own) {
+        if (!own) return;
         const cx<T> v = orth_at<T, M>(wprev, Z, N, g, p);
         acc[0] += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
-    }
+    });
     const int slot[1] = {M};
     block_partials<1>(acc, slot, parts);
 }
@@ -427,8 +552,8 @@ __global__ __launch_bounds__(GM_BT) void k_gm_solve_update(cx<T> *__restrict__ u
 }
 
 // Z_{j+1} = W - sum_{i<=j} (d_ij / n_i) Z_i in place, partial |Z_{j+1}|^2.
-template <typename T, int NJ>
-__global__ __launch_bounds__(GM_BT) void k_gm_orth(cx<T> *__restrict__ Z, size_t N, const double *__restrict__ S,
+template <typename T, int DIM, int NJ>
+__global__ __launch_bounds__(GM_BT) void k_gm_orth(cx<T> *__restrict__ Z, Stencil<T> P, size_t N, const double *__restrict__ S,
                                                  double *__restrict__ parts, const int *__restrict__ stop)
 {
     if (stop && *stop) return;
@@ -436,11 +561,12 @@ __global__ __launch_bounds__(GM_BT) void k_gm_orth(cx<T> *__restrict__ Z, size_t
     orth_coeffs<T, NJ>(S, g);
     cx<T> *w = Z + (size_t)NJ * N;
     double acc[1] = {0.0};
-    for (size_t p = (size_t)blockIdx.x * GM_BT + threadIdx.x; p < N; p += (size_t)gridDim.x * GM_BT) {
+    for_points<DIM>(P, N, [&](size_t p, int, int, bool own) {
+        if (!own) return;
         const cx<T> v = orth_at<T, NJ>(w, Z, N, g, p);
         w[p] = v;
         acc[0] += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
-    }
+    });
     const int slot[1] = {NJ};
     block_partials<1>(acc, slot, parts);
 }
@@ -488,6 +614,7 @@ constexpr int GM_BLOCK_THREADS = 1024;
 constexpr int GM_SMALL_THREADS = 256;
 constexpr size_t GM_SMALL_POINTS = 1024;   // = GM_REG_PTS * GM_SMALL_THREADS
 constexpr size_t GM_BLOCK_MAX_POINTS = 4096;
+constexpr size_t GM_RESID_DOTS_POINTS = (size_t)1 << 18;   // k_gm_resid_dots from a guess
 
 template <int NV, int BT>
 __device__ __forceinline__ void block_reduce_bt(const double (&acc)[NV], double *out, double *red)
@@ -805,7 +932,7 @@ void launch_arnoldi_all(cx<T> *Z, size_t N, const cx<T> *q, const Stencil<T> &P,
                        parts, stop);
     hipLaunchKernelGGL((k_gm_reduce<2 * NJ, 0>), dim3(1), dim3(GM_BT), 0, s, parts, nb,
                        NSLOT_D + 2 * (j * GMRES_MAX_M), S + GM_D + 2 * (j * GMRES_MAX_M), S, stop);
-    hipLaunchKernelGGL((k_gm_orth<T, NJ>), dim3(nb), dim3(GM_BT), 0, s, Z, N, S, parts, stop);
+    hipLaunchKernelGGL((k_gm_orth<T, DIM, NJ>), dim3(nb), dim3(GM_BT), 0, s, Z, P, N, S, parts, stop);
     hipLaunchKernelGGL((k_gm_reduce<1, NJ == M ? M : 0>), dim3(1), dim3(GM_BT), 0, s, parts, nb, NJ, S + NJ, S,
                        stop);
     if constexpr (NJ < M) launch_arnoldi_all<T, DIM, NJ + 1, M>(Z, N, q, P, S, parts, nb, s, stop);
@@ -849,14 +976,34 @@ void launch_step_m(const LevelGeom &g, const Stencil<T> &P, const cx<T> *b, cons
                                b, q, u, zero ? 1 : 0, Z, P, N, stop);
         return;
     }
-    const int nb = (int)std::min<size_t>((N + GM_BT - 1) / GM_BT, GM_BLOCKS);
-    hipLaunchKernelGGL((k_gm_resid<T, DIM>), dim3(nb), dim3(GM_BT), 0, s, u, zero ? 1 : 0, b, q, Z, P, N, parts, stop);
+    const size_t runs = DIM == 2 ? (size_t)gm_tiles(P.mx, P.my) : (N + GM_BT - 1) / GM_BT;
+    const int nb = (int)std::min<size_t>(runs, GM_BLOCKS);
+    // The first two passes as one where that costs less than a launch: from a zero
+    // guess the residual is b; else a point forms it five times (2D), up to 2^18
+    // points (FP32, two launches against one: 127^2 6.9 us and 4.8, 255^2 6.9
+    // and 5.3, 511^2 8.7 and 7.6; 1023^2, where the two take 14, is bound by
+    // vector rate instead).
+    cx<T> *w0 = Z + (size_t)M * N;
+    if (fused && zero)
+        hipLaunchKernelGGL((k_gm_resid_dots<T, DIM, true>), dim3(nb), dim3(GM_BT), 0, s, u, b, q, Z, w0, P, N, parts,
+                           stop);
+    bool paired = fused && zero;
+    if constexpr (DIM == 2) {
+        if (fused && !zero && N < GM_RESID_DOTS_POINTS) {
+            hipLaunchKernelGGL((k_gm_resid_dots<T, DIM, false>), dim3(nb), dim3(GM_BT), 0, s, u, b, q, Z, w0, P, N,
+                               parts, stop);
+            paired = true;
+        }
+    }
+    if (!paired)
+        hipLaunchKernelGGL((k_gm_resid<T, DIM>), dim3(nb), dim3(GM_BT), 0, s, u, zero ? 1 : 0, b, q, Z, P, N, parts,
+                           stop);
     if (fused) {
-        hipLaunchKernelGGL((k_gm_apply_dots<T, DIM, 1>), dim3(nb), dim3(GM_BT), 0, s, Z, Z + (size_t)M * N, N, q, P,
-                           parts, stop);
+        if (!paired)
+            hipLaunchKernelGGL((k_gm_apply_dots<T, DIM, 1>), dim3(nb), dim3(GM_BT), 0, s, Z, w0, N, q, P, parts, stop);
         launch_orth_apply_all<T, DIM, 1, M>(Z, N, q, P, S, parts, nb, s, stop);
-        hipLaunchKernelGGL((k_gm_orth_norm<T, M>), dim3(nb), dim3(GM_BT), 0, s, Z, Z + (size_t)(M + ((M - 1) & 1)) * N,
-                           N, S, parts, stop);
+        hipLaunchKernelGGL((k_gm_orth_norm<T, DIM, M>), dim3(nb), dim3(GM_BT), 0, s, Z,
+                           Z + (size_t)(M + ((M - 1) & 1)) * N, P, N, S, parts, stop);
         hipLaunchKernelGGL((k_gm_solve_update<T, M>), dim3(nb), dim3(GM_BT), 0, s, u, Z, N, S, parts, stop);
         return;
     }
