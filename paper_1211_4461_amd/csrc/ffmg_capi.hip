@@ -358,8 +358,8 @@ void vcycle_fused2d(ffmg_handle *h, int l, const cx<T> *b, cx<T> *u, bool zero_g
     cx<T> *t = LP::t(lv), *scratch = LP::r(lv);
     cx<T> *cur = u;
     const int nu1 = nu_pre(h, l), nu2 = nu_post(h, l);
-    if (nu1 == 2 && h->pre_variant != 1) {
-        // two sweeps, residual and full weighting in one pass
+    if ((nu1 == 1 || nu1 == 2) && h->pre_variant != 1) {
+        // the sweeps, residual and full weighting in one pass
         const bool finest = (l == 0);
         int pi = finest ? prof_kernel_begin(h, PROF_PRE) : -1;
         // finest level: the type's default tile height (16 rows FP32, 8 FP64;
@@ -368,7 +368,7 @@ void vcycle_fused2d(ffmg_handle *h, int l, const cx<T> *b, cx<T> *u, bool zero_g
         const int fdef = sizeof(T) == 4 ? 16 : 8;
         const int fh = finest ? (h->pre_variant == 2 ? 24 - fdef : fdef)
                               : (SMOOTH_TH[h->smooth_coarse_variant] >= 16 ? 16 : 8);
-        launch_smooth_rr2d<T>(lv.g, LP::P(lv), zero_guess, u, b, LP::q(lv), t, LP::b(lc), h->stream, finest, stop,
+        launch_smooth_rr2d<T>(lv.g, LP::P(lv), nu1, zero_guess, u, b, LP::q(lv), t, LP::b(lc), h->stream, finest, stop,
                               fh);
         prof_kernel_end(h, PROF_PRE, pi);
         cur = t;

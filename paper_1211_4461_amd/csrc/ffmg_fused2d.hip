@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict2d(const cx<T> *__restric
     resid_restrict2d_body<T>(u, b, q, bc, P, ctiles_x, xcd_tile(blockIdx.x, gridDim.x));
 }
 
-// Pre-smoothing (two sweeps), residual and full weighting in one pass.  The
+// Pre-smoothing (NS = 2 sweeps), residual and full weighting in one pass.  The
 // block owns the fine points [x0, x0 + 64) x [y0, y0 + FH) (written to out:
 // the smoothed u) and the coarse points whose centre lies there, I in
 // [x0/2, x0/2 + 32), J in [y0/2, y0/2 + FH/2) (written to bc).  Their full
@@ -306,7 +306,10 @@ __global__ __launch_bounds__(256) void k_resid_restrict2d(const cx<T> *__restric
 // formed by the same point functions as in k_smooth2d and
 // k_resid_restrict2d, so the pass equals the two launches bit for bit; it
 // skips their re-read of the smoothed u, b and q and one launch.
-template <typename T, bool ZERO, int FH>
+// NS = 1: one sweep, on S2; S1 falls away, U0 is a point smaller and R lies over
+// it (FP32, a V(1, 1) cycle on 255 x 255 and its coarse levels: 7.8 us as two
+// launches from a guess and 7.2 from zero, 5.3 and 3.7 as one).
+template <typename T, bool ZERO, int FH, int NS = 2>
 __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, const cx<T> *__restrict__ b,
                                                  const cx<T> *__restrict__ q, cx<T> *__restrict__ out,
                                                  cx<T> *__restrict__ bc, const Stencil<T> &P, int tiles_x, int tile)
@@ -314,17 +317,18 @@ __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, co
     static_assert(FH % 8 == 0, "fine tile height: a multiple of 8 rows");
     constexpr int RW = FTX + 1, RH = FH + 1;
     constexpr int S2W = FTX + 3, S2H = FH + 3;
-    constexpr int S1W = FTX + 5, S1H = FH + 5;
-    constexpr int UW = FTX + 7, UH = FH + 7;
-    constexpr int A0 = (ZERO ? S2H * S2W : (UH * UW > S2H * S2W ? UH * UW : S2H * S2W));
+    constexpr int S1W = FTX + 1 + 2 * NS, S1H = FH + 1 + 2 * NS;   // sweep 1 (NS = 1: it is S2)
+    constexpr int UW = S1W + 2, UH = S1H + 2;
+    constexpr int AR = NS == 2 ? S2H * S2W : RH * RW;              // what lies over U0
+    constexpr int A0 = (ZERO ? AR : (UH * UW > AR ? UH * UW : AR));
     constexpr int A1 = S1H * S1W > RH * RW ? S1H * S1W : RH * RW;
     // U0 is dead once sweep 1 is done, S1 once sweep 2 is done (barriers)
     __shared__ cx<T> L0[A0];
     __shared__ cx<T> L1[A1];
     cx<T>(&U0)[UH][UW] = *reinterpret_cast<cx<T>(*)[UH][UW]>(&L0[0]);
-    cx<T>(&S2)[S2H][S2W] = *reinterpret_cast<cx<T>(*)[S2H][S2W]>(&L0[0]);
+    cx<T>(&S2)[S2H][S2W] = *reinterpret_cast<cx<T>(*)[S2H][S2W]>(NS == 2 ? &L0[0] : &L1[0]);
     cx<T>(&S1)[S1H][S1W] = *reinterpret_cast<cx<T>(*)[S1H][S1W]>(&L1[0]);
-    cx<T>(&R)[RH][RW] = *reinterpret_cast<cx<T>(*)[RH][RW]>(&L1[0]);
+    cx<T>(&R)[RH][RW] = *reinterpret_cast<cx<T>(*)[RH][RW]>(NS == 2 ? &L1[0] : &L0[0]);
     const int mx = P.mx, my = P.my;
     const int mxc = (mx - 1) / 2, myc = (my - 1) / 2;
     const int x0 = (tile % tiles_x) * FTX, y0 = (tile / tiles_x) * FH;
@@ -342,7 +346,7 @@ __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, co
         for (int k = 0; k < NU; ++k) {
             int i = threadIdx.x + 256 * k;
             int ly = i / UW, lx = i - ly * UW;
-            int gx = x0 + lx - 3, gy = y0 + ly - 3;
+            int gx = x0 + lx - NS - 1, gy = y0 + ly - NS - 1;
             bool in = i < UH * UW && gx >= 0 && gx < mx && gy >= 0 && gy < my;
             ru[k] = ld_masked(u, (size_t)gy * mx + gx, in);
         }
@@ -353,7 +357,7 @@ __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, co
         py[k] = i / S1W;
         px[k] = i - py[k] * S1W;
         act[k] = i < S1H * S1W;
-        int gx = x0 + px[k] - 2, gy = y0 + py[k] - 2;
+        int gx = x0 + px[k] - NS, gy = y0 + py[k] - NS;
         ing[k] = act[k] && gx >= 0 && gx < mx && gy >= 0 && gy < my;
         size_t j = (size_t)gy * mx + gx;
         rb[k] = ld_masked(b, j, ing[k]);
@@ -384,12 +388,14 @@ __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, co
                                     rb[k], rw[k]);
             }
         }
+        if (NS == 1 && ing[k] && sx >= 1 && sx <= FTX && sy >= 1 && sy <= FH)
+            out[(size_t)(y0 + sy - 1) * mx + (x0 + sx - 1)] = v;
         S1[sy][sx] = v;
     }
     __syncthreads();
     // sweep 2 on S2 (over U0's storage); the owned points go to out
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
+    for (int k = 0; k < (NS == 2 ? NP : 0); ++k) {
         const int sx = px[k], sy = py[k];                     // S1 coordinates; S2 is S1 less its rim
         if (!act[k] || sx < 1 || sx > S2W || sy < 1 || sy > S2H) continue;
         cx<T> v = zero;
@@ -401,18 +407,18 @@ __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, co
         }
         S2[sy - 1][sx - 1] = v;
     }
-    __syncthreads();
-    // residual on R (over S1's storage)
+    if (NS == 2) __syncthreads();
+    // residual on R (over S1's storage; NS = 1: over U0's)
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const int sx = px[k], sy = py[k];                     // R is S1 less two rims, low sides
-        if (!act[k] || sx < 2 || sx > RW + 1 || sy < 2 || sy > RH + 1) continue;
-        const int tx = sx - 1, ty = sy - 1;                   // same point in S2
+        const int sx = px[k], sy = py[k];                     // R is S1 less NS rims, low sides
+        if (!act[k] || sx < NS || sx > RW + NS - 1 || sy < NS || sy > RH + NS - 1) continue;
+        const int tx = sx - (NS - 1), ty = sy - (NS - 1);     // same point in S2
         cx<T> r = zero;
         if (ing[k])
             r = resid_point<T>(P, S2[ty][tx], S2[ty][tx - 1], S2[ty][tx + 1], S2[ty - 1][tx], S2[ty + 1][tx], rb[k],
                                rq[k]);
-        R[sy - 2][sx - 2] = r;
+        R[sy - NS][sx - NS] = r;
     }
     __syncthreads();
     // full weighting at the owned coarse points
@@ -433,14 +439,14 @@ __device__ __forceinline__ void smooth_rr2d_body(const cx<T> *__restrict__ u, co
     }
 }
 
-template <typename T, bool ZERO, int TAG, int FH>
+template <typename T, bool ZERO, int TAG, int FH, int NS>
 __global__ __launch_bounds__(256) void k_smooth_rr2d(const cx<T> *__restrict__ u, const cx<T> *__restrict__ b,
                                                      const cx<T> *__restrict__ q, cx<T> *__restrict__ out,
                                                      cx<T> *__restrict__ bc, Stencil<T> P, int tiles_x,
                                                      const int *__restrict__ stop)
 {
     if (stop && *stop) return;
-    smooth_rr2d_body<T, ZERO, FH>(u, b, q, out, bc, P, tiles_x, xcd_tile(blockIdx.x, gridDim.x));
+    smooth_rr2d_body<T, ZERO, FH, NS>(u, b, q, out, bc, P, tiles_x, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // Mixed-precision outer step: u' = u + s d with s = ctl->scale_cur;
@@ -587,14 +593,14 @@ struct SmoothRR {
     static constexpr int FH = sizeof(T) == 4 ? 16 : 8;
 };
 
-template <typename T, int FH>
+template <typename T, int FH, int NS>
 static void launch_smooth_rr2d_fh(const LevelGeom &g, const Stencil<T> &P, bool zero, const cx<T> *u, const cx<T> *b,
                                   const cx<T> *q, cx<T> *out, cx<T> *bc, hipStream_t s, bool finest, const int *stop)
 {
     const int tx = (g.m[0] + FTX - 1) / FTX;
     const int nb = tx * ((g.m[1] + FH - 1) / FH);
 #define FFMG_SRR(Z, TG) \
-    launch_maybe_timed((k_smooth_rr2d<T, Z, TG, FH>), dim3(nb), dim3(256), 0, s, u, b, q, out, bc, P, tx, stop)
+    launch_maybe_timed((k_smooth_rr2d<T, Z, TG, FH, NS>), dim3(nb), dim3(256), 0, s, u, b, q, out, bc, P, tx, stop)
     if (zero) {
         if (finest) FFMG_SRR(true, 1);
         else FFMG_SRR(true, 0);
@@ -606,16 +612,22 @@ static void launch_smooth_rr2d_fh(const LevelGeom &g, const Stencil<T> &P, bool 
 }
 
 template <typename T>
-void launch_smooth_rr2d(const LevelGeom &g, const Stencil<T> &P, bool zero, const cx<T> *u, const cx<T> *b,
-                        const cx<T> *q, cx<T> *out, cx<T> *bc, hipStream_t s, bool finest, const int *stop, int fh)
+void launch_smooth_rr2d(const LevelGeom &g, const Stencil<T> &P, int nsweeps, bool zero, const cx<T> *u,
+                        const cx<T> *b, const cx<T> *q, cx<T> *out, cx<T> *bc, hipStream_t s, bool finest,
+                        const int *stop, int fh)
 {
     if (fh <= 0) fh = SmoothRR<T>::FH;
-    if (fh == 16) launch_smooth_rr2d_fh<T, 16>(g, P, zero, u, b, q, out, bc, s, finest, stop);
-    else launch_smooth_rr2d_fh<T, 8>(g, P, zero, u, b, q, out, bc, s, finest, stop);
+    if (nsweeps == 1) {
+        if (fh == 16) launch_smooth_rr2d_fh<T, 16, 1>(g, P, zero, u, b, q, out, bc, s, finest, stop);
+        else launch_smooth_rr2d_fh<T, 8, 1>(g, P, zero, u, b, q, out, bc, s, finest, stop);
+    } else {
+        if (fh == 16) launch_smooth_rr2d_fh<T, 16, 2>(g, P, zero, u, b, q, out, bc, s, finest, stop);
+        else launch_smooth_rr2d_fh<T, 8, 2>(g, P, zero, u, b, q, out, bc, s, finest, stop);
+    }
 }
-template void launch_smooth_rr2d<double>(const LevelGeom &, const Stencil<double> &, bool, const cd *, const cd *,
-                                         const cd *, cd *, cd *, hipStream_t, bool, const int *, int);
-template void launch_smooth_rr2d<float>(const LevelGeom &, const Stencil<float> &, bool, const cf *, const cf *,
+template void launch_smooth_rr2d<double>(const LevelGeom &, const Stencil<double> &, int, bool, const cd *,
+                                         const cd *, const cd *, cd *, cd *, hipStream_t, bool, const int *, int);
+template void launch_smooth_rr2d<float>(const LevelGeom &, const Stencil<float> &, int, bool, const cf *, const cf *,
                                         const cf *, cf *, cf *, hipStream_t, bool, const int *, int);
 
 void launch_refine2d(const LevelGeom &g, const Stencil<double> &P, const cd *u, const cf *d, const cd *b,
