@@ -474,8 +474,8 @@ ffmg_status mg_profile_durations(ffmg_handle *h, int kernel, double *ms, int64_t
  * (16 rows with the 16-row variant, else 8); one variant each for 3D and
  * tile_config 1.
  * FFMG_TUNE_PRE: the pre-smoothing of a fused 2D level with nu1 = 1 or 2 as
- * one pass of the sweeps, residual and full weighting (variant 0: 16-row tiles
- * on the finest level for FP32 cycles, 8-row for FP64; 2: the other height) or
+ * one pass of the sweeps, residual and full weighting (variant 0: on the finest
+ * level 8-row tiles, 16-row for FP32 cycles from 2^21 points; 2: the other height) or
  * as the smoothing launch followed by the residual + restriction launch (1);
  * one variant for 3D and tile_config 1.
  * FFMG_TUNE_SWEEP3D: the weighted-Jacobi sweeps of a fused 3D level as one
