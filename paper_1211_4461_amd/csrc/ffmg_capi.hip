@@ -712,9 +712,8 @@ void enqueue_step(ffmg_handle *h, const cd *b, cd *ucur, cd *ualt, const int *st
     Level &l0 = h->L[0];
     if (h->opt.precision == FFMG_FP64) {
         vcycle<double>(h, 0, b, ucur, false, stop);
-        launch_stencil<double>(MODE_RNORM, l0.g, l0.P64, ucur, b, l0.q, (cd *)nullptr, h->d_parts, h->stream, false,
-                               stop);
-        launch_ctl_update(h->d_ctl, h->d_parts, stencil_blocks(l0.g), h->stream);
+        launch_rnorm_update(l0.g, l0.P64, ucur, b, l0.q, h->d_parts, h->d_ctl, h->stream, stop,
+                            h->opt.tile_config != TILE_REFERENCE);
         return;
     }
     const int inner = h->opt.inner_cycles > 0 ? h->opt.inner_cycles : DEFAULT_INNER_CYCLES;
@@ -1363,8 +1362,8 @@ static ffmg_status solve_host_controlled(ffmg_handle *h, const void *bv, void *u
     if (h->opt.fmg_cycles > 0) fmg_enqueue(h, b, u, h->opt.fmg_cycles, h->d_scalar);
     // initial residual (cycle 0)
     if (h->opt.precision == FFMG_FP64) {
-        launch_stencil<double>(MODE_RNORM, l0.g, l0.P64, u, b, l0.q, (cd *)nullptr, h->d_parts, h->stream);
-        launch_ctl_update(h->d_ctl, h->d_parts, stencil_blocks(l0.g), h->stream);
+        launch_rnorm_update(l0.g, l0.P64, u, b, l0.q, h->d_parts, h->d_ctl, h->stream, nullptr,
+                            h->opt.tile_config != TILE_REFERENCE);
     } else {
         launch_resid_to_f32_ctl(l0.g, l0.P64, u, b, l0.q, l0.b32, h->d_ctl, h->d_parts, h->stream, nullptr);
         launch_ctl_update(h->d_ctl, h->d_parts, stencil_blocks(l0.g), h->stream);

@@ -128,6 +128,9 @@ void launch_sum(const double *parts, int nparts, double *out, hipStream_t s);
 // partial sums of ||r||^2 (same reduction order as launch_sum).
 void launch_ctl_init(SolveCtl *ctl, const double *bnorm2, double tol, size_t N, int max_cycles, hipStream_t s);
 void launch_ctl_update(SolveCtl *ctl, const double *parts, int nparts, hipStream_t s);
+// the norm of b - A u and the control update (one_launch: as one, where the level is small)
+void launch_rnorm_update(const LevelGeom &g, const Stencil<double> &P, const cd *u, const cd *b, const cd *q,
+                         double *parts, SolveCtl *ctl, hipStream_t s, const int *stop, bool one_launch);
 
 // Setup kernels.
 void launch_make_q(const cd *coef, cd *q, size_t N, double scale, double *bad_parts, int nparts, hipStream_t s);

@@ -15,6 +15,7 @@
 
 #include "ffmg_internal.hpp"
 #include "ffmg_point.hpp"
+#include "ffmg_wave.hpp"
 
 namespace ffmg {
 
@@ -1739,12 +1740,9 @@ __global__ void k_ctl_init(SolveCtl *ctl, const double *__restrict__ bnorm2, dou
     if (!(b2 > 0.0) || !isfinite(b2)) ctl->done = 5;
 }
 
-// One update from the n per-block partial sums of |r_k|^2 (256 threads).
-__device__ __forceinline__ void ctl_update_body(SolveCtl *ctl, const double *__restrict__ parts, int n)
+// One update from |r_k|^2 (one thread).
+__device__ __forceinline__ void ctl_step(SolveCtl *ctl, double s2)
 {
-    if (ctl->done) return;
-    double s2 = sum_parts_256(parts, n);
-    if (threadIdx.x != 0) return;
     SolveCtl c = *ctl;
     c.k += 1;
     c.rk2 = s2;
@@ -1761,6 +1759,93 @@ __device__ __forceinline__ void ctl_update_body(SolveCtl *ctl, const double *__r
     else if (c.k >= c.max_cycles) c.done = 3;
     c.prev2 = s2;
     *ctl = c;
+}
+
+// One update from the n per-block partial sums of |r_k|^2 (256 threads).
+__device__ __forceinline__ void ctl_update_body(SolveCtl *ctl, const double *__restrict__ parts, int n)
+{
+    if (ctl->done) return;
+    double s2 = sum_parts_256(parts, n);
+    if (threadIdx.x == 0) ctl_step(ctl, s2);
+}
+
+// The residual norm of a 2D level of at most RN_TILES tiles and the control update
+// in one workgroup, 256 threads a tile.  The points of a thread, the sums and their
+// order are those of k_stencil2d (MODE_RNORM) and k_ctl_update.  Bound by
+// latency: 63 x 63 5.4 us, as two launches 4.4 and 1.8 us and the gap between
+// them (a 63 x 63 map of 16 cycles 564 -> 543 us).
+constexpr int RN_TILES = 4;
+
+__global__ __launch_bounds__(256 * RN_TILES) void k_rnorm_ctl2d(const cd *__restrict__ u, const cd *__restrict__ b,
+                                                                const cd *__restrict__ q, Stencil<double> P,
+                                                                int tiles_x, int nt, SolveCtl *ctl,
+                                                                const int *__restrict__ stop)
+{
+    if ((stop && *stop) || ctl->done) return;
+    __shared__ double red[4 * RN_TILES];
+    const int slot = threadIdx.x >> 8, t = threadIdx.x & 255;
+    const int mx = P.mx, my = P.my;
+    double acc[1] = {0.0}, sum[1];
+    if (slot < nt) {
+        const int tile = xcd_tile(slot, nt);
+        const int gx = (tile % tiles_x) * 64 + (t & 63), y0 = (tile / tiles_x) * TY2 + (t >> 6);
+        // every load is issued before one is waited for (from clamped points, what
+        // lies outside set to 0 after); the x-neighbours are the neighbouring
+        // lanes, but for the tile's first and last column
+        constexpr int NR = TY2 / 4;
+        const int lane = t & 63, xe = lane == 0 ? gx - 1 : gx + 1;
+        const bool edge = (lane == 0 || lane == 63) && xe >= 0 && xe < mx;
+        cd uc[NR], us[NR], un[NR], ue[NR], bj[NR], qj[NR];
+        const int cx_ = min(gx, mx - 1);
+        auto row = [&](int gy) { return (size_t)min(max(gy, 0), my - 1) * mx; };
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int gy = y0 + 4 * k;
+            uc[k] = u[row(gy) + cx_];
+            us[k] = u[row(gy - 1) + cx_];
+            un[k] = u[row(gy + 1) + cx_];
+            ue[k] = u[row(gy) + (edge ? xe : cx_)];
+            bj[k] = b[row(gy) + cx_];
+            qj[k] = q[row(gy) + cx_];
+        }
+        auto keep = [](bool in, cd v) { return cd{in ? v.re : 0.0, in ? v.im : 0.0}; };
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int gy = y0 + 4 * k;
+            const bool in = gx < mx && gy < my;
+            const cd c = keep(in, uc[k]), s = keep(gy > 0, us[k]), n = keep(gy < my - 1, un[k]), x = keep(edge, ue[k]);
+            cd w = {dpp_mov<DPP_WAVE_SHR1>(c.re), dpp_mov<DPP_WAVE_SHR1>(c.im)};
+            cd e = {dpp_mov<DPP_WAVE_SHL1>(c.re), dpp_mov<DPP_WAVE_SHL1>(c.im)};
+            if (lane == 0) w = x;
+            if (lane == 63) e = x;
+            const cd r = resid_from(P, lap_xy(P, c, w, e, s, n), c, bj[k], qj[k]);
+            if (in) acc[0] += abs2(r);
+        }
+    }
+    wave_sums<1>(acc, sum);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum[0];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double part[RN_TILES];
+#pragma unroll
+    for (int i = 0; i < RN_TILES; ++i)
+        part[i] = i < nt ? (red[4 * i] + red[4 * i + 1]) + (red[4 * i + 2] + red[4 * i + 3]) : 0.0;
+    ctl_step(ctl, (part[0] + part[2]) + (part[1] + part[3]));
+}
+
+// The residual norm |b - A u| of the FP64 iterate and the control update: one
+// launch where the level has at most RN_TILES tiles of the norm's pass.
+void launch_rnorm_update(const LevelGeom &g, const Stencil<double> &P, const cd *u, const cd *b, const cd *q,
+                         double *parts, SolveCtl *ctl, hipStream_t s, const int *stop, bool one_launch)
+{
+    int nb, tx, ty, tz;
+    grid_of(g, nb, tx, ty, tz);
+    if (one_launch && g.dim == 2 && nb <= RN_TILES) {
+        hipLaunchKernelGGL(k_rnorm_ctl2d, dim3(1), dim3(256 * RN_TILES), 0, s, u, b, q, P, tx, nb, ctl, stop);
+        return;
+    }
+    launch_stencil<double>(MODE_RNORM, g, P, u, b, q, (cd *)nullptr, parts, s, false, stop);
+    launch_ctl_update(ctl, parts, nb, s);
 }
 
 __global__ __launch_bounds__(256) void k_ctl_update(SolveCtl *ctl, const double *__restrict__ parts, int n)
