@@ -119,7 +119,7 @@ KERNEL_NAMES = {
         "pre": "k_sweep2_3d<%s, SRC_ZERO2 / SRC_MEM> (finest level: two Jacobi sweeps per pass)"},
     2: {"post": "k_smooth2d<%s, 2, false, true, 1, TH> (finest level: interpolation + two fused Jacobi sweeps)",
         "refine": "k_refine2d (FP64 update + residual; the plane-wave right-hand side formed from q)",
-        "pre": "k_smooth_rr2d<%s, *, 1, *> (finest level: two sweeps + residual + full weighting)"},
+        "pre": "k_smooth_rr2d<%s, *, 1, *, 2> (finest level: two sweeps + residual + full weighting)"},
 }
 # Useful flops of one learned-smoother application per point: 2736 complex
 # multiply-adds (one per complex weight), 8 real flops each.
