@@ -596,13 +596,58 @@ __global__ __launch_bounds__(1024) void k_train_patch(const float2 *__restrict__
     }
 }
 
-// Mean of the per-patch gradients and of the losses: 64 weights a block, every
-// 16th patch a wave, then the waves in order.  (One thread a weight over all
-// patches is a chain of dependent loads: 61 us for 256 patches; this form 5 us.)
+// Adam on the real and imaginary parts of weight k (step >= 1); refreshes the
+// BF16-rounded copy used by the training forward pass.
+struct AdamArgs {
+    float2 *Wm, *Wq, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_update(const AdamArgs &A, int k, float2 g)
+{
+    float2 mk = A.m[k], vk = A.v[k], w = A.Wm[k];
+    mk.x = A.b1 * mk.x + (1.f - A.b1) * g.x;
+    mk.y = A.b1 * mk.y + (1.f - A.b1) * g.y;
+    vk.x = A.b2 * vk.x + (1.f - A.b2) * g.x * g.x;
+    vk.y = A.b2 * vk.y + (1.f - A.b2) * g.y * g.y;
+    w.x -= A.lr * (mk.x / A.c1) / (sqrtf(vk.x / A.c2) + A.eps);
+    w.y -= A.lr * (mk.y / A.c1) / (sqrtf(vk.y / A.c2) + A.eps);
+    A.m[k] = mk;
+    A.v[k] = vk;
+    A.Wm[k] = w;
+    A.Wq[k] = make_float2(bf16_round(w.x), bf16_round(w.y));
+}
+
+// Mean of the per-patch gradients, 64 weights a block (every 16th patch a wave,
+// then the waves in order), where ADAM with the update of those weights; the last
+// block takes the mean of the losses, written to the host's page-locked word.
+// (One thread a weight over all patches is a chain of dependent loads: 61 us for
+// 256 patches.)  5 us for 256 patches; as launches of their own the loss, the
+// update and the copy of the loss took 4.7, 5.2 and 4.1 us more.
+constexpr int NB_GRADS = (NET_NW + 63) / 64;
+
+template <bool ADAM>
 __global__ __launch_bounds__(1024) void k_reduce_grads(const float2 *__restrict__ dW_part, int count,
-                                                       float2 *__restrict__ grad)
+                                                       float2 *__restrict__ grad,
+                                                       const float *__restrict__ loss_part, float *__restrict__ loss,
+                                                       AdamArgs A)
 {
     __shared__ float2 part[16][64];
+    if (blockIdx.x == NB_GRADS) {
+        float *red = &part[0][0].x;
+        if (threadIdx.x < 256) {
+            float s = 0.f;
+            for (int p = threadIdx.x; p < count; p += 256) s += loss_part[p];
+            red[threadIdx.x] = s;
+        }
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = red[0] / (float)count;
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int k = blockIdx.x * 64 + lane, kk = min(k, NET_NW - 1);
     float2 s = make_float2(0.f, 0.f);
@@ -620,44 +665,10 @@ __global__ __launch_bounds__(1024) void k_reduce_grads(const float2 *__restrict_
             s.y += part[w][lane].y;
         }
         const float inv = 1.f / (float)count;
-        grad[k] = make_float2(s.x * inv, s.y * inv);
+        const float2 g = make_float2(s.x * inv, s.y * inv);
+        grad[k] = g;
+        if (ADAM) adam_update(A, k, g);
     }
-}
-
-__global__ __launch_bounds__(256) void k_reduce_loss(const float *__restrict__ part, int count, float *__restrict__ out)
-{
-    __shared__ float red[256];
-    float s = 0.f;
-    for (int p = threadIdx.x; p < count; p += 256) s += part[p];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0] / (float)count;
-}
-
-// Adam on the real and imaginary parts (step >= 1); refreshes the BF16-rounded
-// copy used by the training forward pass.
-__global__ __launch_bounds__(256) void k_adam(float2 *__restrict__ Wm, float2 *__restrict__ Wq,
-                                              const float2 *__restrict__ grad, float2 *__restrict__ m,
-                                              float2 *__restrict__ v, float lr, float b1, float b2, float eps,
-                                              float c1, float c2)
-{
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= NET_NW) return;
-    float2 g = grad[k], mk = m[k], vk = v[k], w = Wm[k];
-    mk.x = b1 * mk.x + (1.f - b1) * g.x;
-    mk.y = b1 * mk.y + (1.f - b1) * g.y;
-    vk.x = b2 * vk.x + (1.f - b2) * g.x * g.x;
-    vk.y = b2 * vk.y + (1.f - b2) * g.y * g.y;
-    w.x -= lr * (mk.x / c1) / (sqrtf(vk.x / c2) + eps);
-    w.y -= lr * (mk.y / c1) / (sqrtf(vk.y / c2) + eps);
-    m[k] = mk;
-    v[k] = vk;
-    Wm[k] = w;
-    Wq[k] = make_float2(bf16_round(w.x), bf16_round(w.y));
 }
 
 __global__ __launch_bounds__(256) void k_round_weights(const float2 *__restrict__ Wm, float2 *__restrict__ Wq)
@@ -685,16 +696,17 @@ void launch_train_patches(const float2 *rt, const float2 *kt, const float2 *et, 
 void launch_reduce_grads(const float2 *dW_part, int count, float2 *grad, const float *loss_part, float *loss,
                          hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce_grads, dim3((NET_NW + 63) / 64), dim3(1024), 0, s, dW_part, count, grad);
-    hipLaunchKernelGGL(k_reduce_loss, dim3(1), dim3(256), 0, s, loss_part, count, loss);
+    hipLaunchKernelGGL(k_reduce_grads<false>, dim3(NB_GRADS + 1), dim3(1024), 0, s, dW_part, count, grad, loss_part,
+                       loss, AdamArgs());
 }
 
-void launch_adam(float2 *Wm, float2 *Wq, const float2 *grad, float2 *m, float2 *v, float lr, float b1, float b2,
-                 float eps, int step, hipStream_t s)
+void launch_reduce_grads_adam(const float2 *dW_part, int count, float2 *grad, const float *loss_part, float *loss,
+                              float2 *Wm, float2 *Wq, float2 *m, float2 *v, float lr, float b1, float b2, float eps,
+                              int step, hipStream_t s)
 {
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(k_adam, dim3((NET_NW + 255) / 256), dim3(256), 0, s, Wm, Wq, grad, m, v, lr, b1, b2, eps,
-                       c1, c2);
+    const AdamArgs A = {Wm, Wq, m, v, lr, b1, b2, eps, 1.f - powf(b1, (float)step), 1.f - powf(b2, (float)step)};
+    hipLaunchKernelGGL(k_reduce_grads<true>, dim3(NB_GRADS + 1), dim3(1024), 0, s, dW_part, count, grad, loss_part,
+                       loss, A);
 }
 
 void launch_round_weights(const float2 *Wm, float2 *Wq, hipStream_t s)
@@ -1174,7 +1186,7 @@ struct ffmg_net {
     hipStream_t stream = nullptr;
     float2 *Wm = nullptr, *Wq = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
     float2 *dW_part = nullptr;
-    float *loss_part = nullptr, *d_loss = nullptr, *h_loss = nullptr;
+    float *loss_part = nullptr, *h_loss = nullptr;   // h_loss: page-locked, written by the device
     int part_cap = 0;
     int step = 0;
     std::string err;
@@ -1221,7 +1233,9 @@ ffmg_status check_finite(ffmg_net *n, const float *w)
     return FFMG_OK;
 }
 
-ffmg_status train_common(ffmg_net *n, const void *rt, const void *kt, const void *et, int count, int border)
+// Losses and gradients of the patches; lr > 0: and the Adam step with that rate.
+ffmg_status train_common(ffmg_net *n, const void *rt, const void *kt, const void *et, int count, int border,
+                         float lr)
 {
     if (!rt || !kt || !et || count < 1) return net_fail(n, FFMG_EINVAL, "null patches or count < 1");
     if (border < 1 || border > 12) return net_fail(n, FFMG_EINVAL, "border must lie in [1, 12]");
@@ -1243,8 +1257,13 @@ ffmg_status train_common(ffmg_net *n, const void *rt, const void *kt, const void
     }
     ffmg::launch_train_patches((const float2 *)rt, (const float2 *)kt, (const float2 *)et, n->Wq, n->dW_part,
                                n->loss_part, count, border, n->stream);
-    ffmg::launch_reduce_grads(n->dW_part, count, n->grad, n->loss_part, n->d_loss, n->stream);
+    if (lr > 0.f)
+        ffmg::launch_reduce_grads_adam(n->dW_part, count, n->grad, n->loss_part, n->h_loss, n->Wm, n->Wq, n->m, n->v,
+                                       lr, 0.9f, 0.999f, 1e-8f, n->step + 1, n->stream);
+    else
+        ffmg::launch_reduce_grads(n->dW_part, count, n->grad, n->loss_part, n->h_loss, n->stream);
     NCHK(n, hipGetLastError());
+    if (lr > 0.f) n->step += 1;
     return FFMG_OK;
 }
 
@@ -1265,7 +1284,6 @@ ffmg_status ml_net_create(const float *w, void *stream, ffmg_net **out)
     if (s == FFMG_OK) s = net_alloc(n, &n->m, bytes);
     if (s == FFMG_OK) s = net_alloc(n, &n->v, bytes);
     if (s == FFMG_OK) s = net_alloc(n, &n->grad, bytes);
-    if (s == FFMG_OK) s = net_alloc(n, &n->d_loss, sizeof(float));
     if (s == FFMG_OK && hipHostMalloc((void **)&n->h_loss, sizeof(float), hipHostMallocDefault) != hipSuccess)
         s = net_fail(n, FFMG_ENOMEM, "hipHostMalloc failed");
     if (s == FFMG_OK) s = ml_net_set_weights(n, w);
@@ -1304,9 +1322,8 @@ ffmg_status ml_loss_grad(ffmg_net *n, const void *rt, const void *kt, const void
                          float *loss, float *grad)
 {
     if (!n) return FFMG_EINVAL;
-    ffmg_status s = train_common(n, rt, kt, et, count, border);
+    ffmg_status s = train_common(n, rt, kt, et, count, border, 0.f);
     if (s != FFMG_OK) return s;
-    if (loss) NCHK(n, hipMemcpyAsync(n->h_loss, n->d_loss, sizeof(float), hipMemcpyDeviceToHost, n->stream));
     if (grad) NCHK(n, hipMemcpyAsync(grad, n->grad, ffmg::NET_NW * sizeof(float2), hipMemcpyDeviceToHost, n->stream));
     NCHK(n, hipStreamSynchronize(n->stream));
     if (loss) *loss = *n->h_loss;
@@ -1318,13 +1335,9 @@ ffmg_status ml_train_step(ffmg_net *n, const void *rt, const void *kt, const voi
 {
     if (!n) return FFMG_EINVAL;
     if (!(lr > 0.f) || !isfinite(lr)) return net_fail(n, FFMG_EINVAL, "lr must be positive");
-    ffmg_status s = train_common(n, rt, kt, et, count, border);
+    ffmg_status s = train_common(n, rt, kt, et, count, border, lr);
     if (s != FFMG_OK) return s;
-    n->step += 1;
-    ffmg::launch_adam(n->Wm, n->Wq, n->grad, n->m, n->v, lr, 0.9f, 0.999f, 1e-8f, n->step, n->stream);
-    NCHK(n, hipGetLastError());
     if (loss) {
-        NCHK(n, hipMemcpyAsync(n->h_loss, n->d_loss, sizeof(float), hipMemcpyDeviceToHost, n->stream));
         NCHK(n, hipStreamSynchronize(n->stream));
         *loss = *n->h_loss;
     }

@@ -21,8 +21,9 @@ void launch_train_patches(const float2 *rt, const float2 *kt, const float2 *et, 
                           float *loss_part, int count, int border, hipStream_t s);
 void launch_reduce_grads(const float2 *dW_part, int count, float2 *grad, const float *loss_part, float *loss,
                          hipStream_t s);
-void launch_adam(float2 *Wm, float2 *Wq, const float2 *grad, float2 *m, float2 *v, float lr, float b1, float b2,
-                 float eps, int step, hipStream_t s);
+void launch_reduce_grads_adam(const float2 *dW_part, int count, float2 *grad, const float *loss_part, float *loss,
+                              float2 *Wm, float2 *Wq, float2 *m, float2 *v, float lr, float b1, float b2, float eps,
+                              int step, hipStream_t s);
 void launch_round_weights(const float2 *Wm, float2 *Wq, hipStream_t s);
 
 // inference: u += h^2 N(r, kappa h^2)  (= s h^2 N(r / s, kappa h^2), N being linear in r)
