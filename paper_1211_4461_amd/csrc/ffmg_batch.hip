@@ -64,9 +64,12 @@ struct Batch {
     RefineJob *d_refA = nullptr, *d_refB = nullptr;
     int *d_ref_tile_job = nullptr;
     FinishJob *d_finish = nullptr;
-    int *d_ndone = nullptr;
-    int *h_ndone = nullptr;               // pinned
-    SolveCtl *h_ctls = nullptr;           // pinned
+    int *h_ndone = nullptr;               // pinned, written by the device
+    SolveCtl *h_ctls = nullptr;           // pinned, written by the device
+    // the tables written per call (init, refA, refB, fin, xfin), in one block on
+    // the device and its pinned copy
+    char *d_up = nullptr, *h_up = nullptr;
+    size_t up_bytes = 0;
     std::vector<InitJob> init;
     std::vector<RefineJob> refA, refB;
     std::vector<FinishJob> fin;
@@ -87,6 +90,7 @@ struct Batch {
         for (void *p : allocs) (void)hipFree(p);
         if (h_ndone) (void)hipHostFree(h_ndone);
         if (h_ctls) (void)hipHostFree(h_ctls);
+        if (h_up) (void)hipHostFree(h_up);
         if (stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -94,6 +98,14 @@ struct Batch {
 void batch_destroy(Batch *b) { delete b; }
 
 namespace {
+
+// The control blocks of all instances into the host's page-locked array (a copy
+// each took 10 us, 24 of them a batch of 4 ms).
+__global__ __launch_bounds__(64) void k_gather_ctl(const CtlJob *__restrict__ jobs, int n, SolveCtl *__restrict__ out)
+{
+    const int i = blockIdx.x * 64 + threadIdx.x;
+    if (i < n) out[i] = *jobs[i].ctl;
+}
 
 #define BCHK(x)                                                                                                     \
     do {                                                                                                            \
@@ -582,12 +594,20 @@ ffmg_status build_batch(ffmg_handle *const *hs, int count, Batch **out)
     B.refA.resize(count);
     B.refB.resize(count);
     B.fin.resize(count);
-    BCHK(B.alloc((void **)&B.d_init, count * sizeof(InitJob)));
-    BCHK(B.alloc((void **)&B.d_refA, count * sizeof(RefineJob)));
-    BCHK(B.alloc((void **)&B.d_refB, count * sizeof(RefineJob)));
-    BCHK(B.alloc((void **)&B.d_finish, count * sizeof(FinishJob)));
-    BCHK(B.alloc((void **)&B.d_ndone, sizeof(int)));
-    BCHK(B.alloc((void **)&B.d_xfin, count * sizeof(XferJob)));
+    {
+        size_t at[6] = {0};
+        const size_t bytes[5] = {count * sizeof(InitJob), count * sizeof(RefineJob), count * sizeof(RefineJob),
+                                 count * sizeof(FinishJob), count * sizeof(XferJob)};
+        for (int k = 0; k < 5; ++k) at[k + 1] = at[k] + (bytes[k] + 255) / 256 * 256;
+        B.up_bytes = at[5];
+        BCHK(B.alloc((void **)&B.d_up, B.up_bytes));
+        BCHK(hipHostMalloc((void **)&B.h_up, B.up_bytes, hipHostMallocDefault));
+        B.d_init = (InitJob *)(B.d_up + at[0]);
+        B.d_refA = (RefineJob *)(B.d_up + at[1]);
+        B.d_refB = (RefineJob *)(B.d_up + at[2]);
+        B.d_finish = (FinishJob *)(B.d_up + at[3]);
+        B.d_xfin = (XferJob *)(B.d_up + at[4]);
+    }
     B.xfin.resize(count);
     for (int i = 0; i < count; ++i) {
         B.xfin[i] = xfer_job(B.inst[i], 0, B.inst[i].u32[1], nullptr, true);
@@ -608,7 +628,7 @@ ffmg_status build_batch(ffmg_handle *const *hs, int count, Batch **out)
         launch_refine2d_batch(step == 0 ? B.d_refA : B.d_refB, B.d_ref_tile_job, B.ref_ntiles, B.stream);
         launch_ctl_update_batch(B.d_ctl, count, B.stream);
     }
-    launch_count_done(B.d_ctl, count, B.d_ndone, B.stream);
+    launch_count_done(B.d_ctl, count, B.h_ndone, B.stream);
     hipError_t ce = hipStreamEndCapture(B.stream, &B.graph);
     if (ce != hipSuccess) {
         (void)hipGetLastError();
@@ -721,12 +741,17 @@ ffmg_status mg_solve_batched(ffmg_handle *const *hs, int count, const double *et
     // order after the caller's stream (the RHS and u of the caller's work)
     BCHK(hipEventRecord(ein, h0->stream));
     BCHK(hipStreamWaitEvent(B.stream, ein, 0));
-    BCHK(hipMemcpyAsync(B.d_init, B.init.data(), count * sizeof(InitJob), hipMemcpyHostToDevice, B.stream));
-    BCHK(hipMemcpyAsync(B.d_refA, B.refA.data(), count * sizeof(RefineJob), hipMemcpyHostToDevice, B.stream));
-    BCHK(hipMemcpyAsync(B.d_refB, B.refB.data(), count * sizeof(RefineJob), hipMemcpyHostToDevice, B.stream));
-    BCHK(hipMemcpyAsync(B.d_finish, B.fin.data(), count * sizeof(FinishJob), hipMemcpyHostToDevice, B.stream));
-    if (B.fmg > 0)
-        BCHK(hipMemcpyAsync(B.d_xfin, B.xfin.data(), count * sizeof(XferJob), hipMemcpyHostToDevice, B.stream));
+    // one upload (five of a few KB each from pageable memory held the host for
+    // 10 us apiece); the pinned copy is free: every call ends with a wait
+    auto put = [&](const void *dev, const void *src, size_t bytes) {
+        memcpy(B.h_up + ((const char *)dev - B.d_up), src, bytes);
+    };
+    put(B.d_init, B.init.data(), count * sizeof(InitJob));
+    put(B.d_refA, B.refA.data(), count * sizeof(RefineJob));
+    put(B.d_refB, B.refB.data(), count * sizeof(RefineJob));
+    put(B.d_finish, B.fin.data(), count * sizeof(FinishJob));
+    put(B.d_xfin, B.xfin.data(), count * sizeof(XferJob));
+    BCHK(hipMemcpyAsync(B.d_up, B.h_up, B.up_bytes, hipMemcpyHostToDevice, B.stream));
     BCHK(hipEventRecord(e0, B.stream));
     launch_init_batch(B.d_init, count, B.max_nb_norm, B.max_m, B.fmg == 0, B.stream);
     if (B.fmg > 0) BCHK(hipGraphLaunch(B.fmg_exec, B.stream));
@@ -742,15 +767,14 @@ ffmg_status mg_solve_batched(ffmg_handle *const *hs, int count, const double *et
         int nb = std::min(batch, max_replays - replays);
         for (int r = 0; r < nb; ++r) BCHK(hipGraphLaunch(B.exec, B.stream));
         replays += nb;
-        BCHK(hipMemcpyAsync(B.h_ndone, B.d_ndone, sizeof(int), hipMemcpyDeviceToHost, B.stream));
         BCHK(hipStreamSynchronize(B.stream));
         if (*B.h_ndone >= count || replays >= max_replays) break;
         batch = 1;
     }
     launch_finish_batch(B.d_finish, count, B.stream);
     BCHK(hipEventRecord(e1, B.stream));
-    for (int i = 0; i < count; ++i)
-        BCHK(hipMemcpyAsync(B.h_ctls + i, B.inst[i].ctl, sizeof(SolveCtl), hipMemcpyDeviceToHost, B.stream));
+    hipLaunchKernelGGL(k_gather_ctl, dim3((count + 63) / 64), dim3(64), 0, B.stream, B.d_ctl, count, B.h_ctls);
+    BCHK(hipGetLastError());
     BCHK(hipStreamSynchronize(B.stream));
     // the caller's stream continues after the batch
     BCHK(hipEventRecord(ein, B.stream));
