@@ -15,14 +15,21 @@
 // each other (two chains that run side by side), and O(n^2 B) products, against
 // n dependent pivot steps and O(n^3) for elimination on the whole matrix.  The
 // blocks are inverted with partial pivoting; pivots are not exchanged between
-// slices, so the result is checked (max |A X - I|), and a matrix on which it
+// slices, so a chain whose leading slices are close to singular by themselves
+// loses digits that the whole matrix has.  The result is therefore held to
+// rounding, max |A X - I| <= CB_ROUND eps ||A|| max |X|, and a matrix on which it
 // fails is inverted by the pivoted elimination of ffmg_stencil.hip instead.
+// Measured in units of eps ||A|| max |X|: at most 3.1 over random contrasts of
+// size 0 to 50 on grids from 3 x 3 to 31 x 31 and 7 x 7 x 15, 1.9 on the 31 x 31
+// ionisation operators; with a first slice singular up to a relative shift of
+// 1e-3, 1e-5, 1e-7 on 7 x 15 points 13, 1053, 109054 (elimination: 1).
 //
 // The two chains are bound by latency (B nb dependent pivot steps of 0.6 us for
 // B = 31, 0.8 us for B = 49: a 64-lane arg-max, one reciprocal, one barrier).
 // Measured, all kernels of the inverse: 31 x 31 grid 740 us (blocked
 // elimination: 7100 us), 7 x 7 x 7 390 us (1350 us), 7 x 7 47 us (193 us).
 #include <algorithm>
+#include <cmath>
 
 #include "ffmg_internal.hpp"
 
@@ -33,7 +40,8 @@ namespace {
 constexpr int CB_WAVES = 8;                     // waves that share a block's columns
 constexpr int CB_MAX = CB_WAVES * 7;             // largest block: seven columns per wave
 constexpr int CB_COLS = 8;                      // columns of G a workgroup carries along the chain
-constexpr double CB_TOL = 1e-9;                 // accepted max |A X - I|
+constexpr double CB_ROUND = 8.0;                // accepted max |A X - I| over eps ||A|| max |X|
+constexpr double CB_TOL = 1e-9;                 // and in any case
 
 // The coarsest grid as nb slices of B = n0 n1 points; point (i0, i1) of slice
 // i has the flat index i0 s0 + i1 s1 + i so.
@@ -190,12 +198,21 @@ __device__ __forceinline__ int cb_invert(cd (&m)[NS], int B, CbShared &sh)
     return kown;
 }
 
+// The largest magnitudes the check goes by, as FP32 bits: of the inverse's
+// entries (the larger of |re| and |im|) and of the operator's diagonal.
+struct CbScale {
+    unsigned x, diag;
+};
+
+__device__ __forceinline__ float cb_abs(cd v) { return fmaxf(fabsf((float)v.re), fabsf((float)v.im)); }
+
 // The two chains: block 0 the S_i from the first slice, block 1 the T_i from
 // the last; c S_i^{-1} and c T_i^{-1} go to chain[dir][i] (row-major B x B).
 template <int NS>
 __global__ __launch_bounds__(64 * CB_WAVES) void k_coarse_chain(CoarseShape C, const cd *__restrict__ q,
-                                                                cd *__restrict__ chain)
+                                                                cd *__restrict__ chain, CbScale *__restrict__ scale)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *scale = CbScale{0u, 0u};   // (the later launches add to it)
     __shared__ CbShared sh;
     __shared__ cd X[NS * CB_WAVES * NS * CB_WAVES];
     const int dir = blockIdx.x, B = C.B;   // B is odd: rows of B values fall on different banks
@@ -235,7 +252,8 @@ __global__ __launch_bounds__(64 * CB_WAVES) void k_coarse_chain(CoarseShape C, c
 // The diagonal blocks G_jj of the inverse, one workgroup each.
 template <int NS>
 __global__ __launch_bounds__(64 * CB_WAVES) void k_coarse_diag(CoarseShape C, const cd *__restrict__ q,
-                                                               const cd *__restrict__ chain, cd *__restrict__ G)
+                                                               const cd *__restrict__ chain, cd *__restrict__ G,
+                                                               CbScale *__restrict__ scale)
 {
     __shared__ CbShared sh;
     const int jb = blockIdx.x, B = C.B;
@@ -243,6 +261,10 @@ __global__ __launch_bounds__(64 * CB_WAVES) void k_coarse_diag(CoarseShape C, co
     const size_t BB = (size_t)B * B;
     cd m[NS];
     const cd qr = lane < B ? q[cb_index(C, lane, jb)] : cd{0.0, 0.0};
+    if (wave == 0) {
+        const unsigned d = wave_max(lane < B ? __float_as_uint(cb_abs(cb_entry(C, lane, lane, qr))) : 0u);
+        if (lane == 0) atomicMax(&scale->diag, d);
+    }
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         const int col = j * CB_WAVES + wave;
@@ -267,7 +289,8 @@ __global__ __launch_bounds__(64 * CB_WAVES) void k_coarse_diag(CoarseShape C, co
 // the next slice's factor is loaded into registers during the current product
 // and stored to the other of two LDS buffers after it.
 __global__ __launch_bounds__(256) void k_coarse_cols(CoarseShape C, const cd *__restrict__ chain,
-                                                     const cd *__restrict__ G, cd *__restrict__ aug, int ngroups)
+                                                     const cd *__restrict__ G, cd *__restrict__ aug, int ngroups,
+                                                     CbScale *__restrict__ scale)
 {
     constexpr int NL = (CB_MAX * CB_MAX + 255) / 256;
     __shared__ cd L[2][CB_MAX * CB_MAX];
@@ -298,10 +321,12 @@ __global__ __launch_bounds__(256) void k_coarse_cols(CoarseShape C, const cd *__
     const bool any = i >= 0 && i < C.nb;
     if (any) load(i);
     int gcol[2];
+    float big = 0.f;        // the largest entry this thread forms (rows and columns beyond B repeat others or are 0)
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int c = wave * 2 + k, col = c0 + c;
         const cd v = (lane < B && col < B) ? G[(size_t)jb * BB + lane * B + col] : zero;
+        big = fmaxf(big, cb_abs(v));
         g[0][lane][c] = v;
         gcol[k] = col < B ? cb_index(C, col, jb) : -1;
         if (dir == 0 && lane < B && gcol[k] >= 0) aug[(size_t)cb_index(C, lane, jb) * 2 * n + n + gcol[k]] = v;
@@ -319,6 +344,7 @@ __global__ __launch_bounds__(256) void k_coarse_cols(CoarseShape C, const cd *__
             a0 = cb_add(a0, x, g[buf][k][wave * 2]);
             a1 = cb_add(a1, x, g[buf][k][wave * 2 + 1]);
         }
+        big = fmaxf(big, fmaxf(cb_abs(a0), cb_abs(a1)));
         g[buf ^ 1][lane][wave * 2] = a0;
         g[buf ^ 1][lane][wave * 2 + 1] = a1;
         if (lane < B) {
@@ -328,11 +354,15 @@ __global__ __launch_bounds__(256) void k_coarse_cols(CoarseShape C, const cd *__
         }
         if (more) stage(buf ^ 1);
     }
+    const unsigned m = wave_max(__float_as_uint(big));
+    if (lane == 0) atomicMax(&scale->x, m);
 }
 
-// info[0] = -1 if an entry of A X - I is not below CB_TOL (a NaN is not).
+// info[0] = -1 if an entry of A X - I is not below its bound (a NaN is not);
+// offdiag: the sum of the magnitudes of a row's other entries.
 __global__ __launch_bounds__(256) void k_coarse_check(const cd *__restrict__ q, const cd *__restrict__ aug,
-                                                      Stencil<double> P, int *__restrict__ info)
+                                                      Stencil<double> P, double offdiag,
+                                                      const CbScale *__restrict__ scale, int *__restrict__ info)
 {
     const int mx = P.mx, my = P.my, mz = P.mz, n = mx * my * mz;
     const int i = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
@@ -349,7 +379,9 @@ __global__ __launch_bounds__(256) void k_coarse_check(const cd *__restrict__ q, 
     if (iz > 0) r = r - P.c[2] * X[(i - mx * my) * W];
     if (iz + 1 < mz) r = r - P.c[2] * X[(i + mx * my) * W];
     if (i == j) r.re -= 1.0;
-    if (!(fabs(r.re) < CB_TOL && fabs(r.im) < CB_TOL)) info[0] = -1;
+    const double norm = (double)__uint_as_float(scale->diag) + offdiag;
+    const double tol = fmin(CB_ROUND * 0x1p-52 * norm * (double)__uint_as_float(scale->x), CB_TOL);
+    if (!(fabs(r.re) < tol && fabs(r.im) < tol)) info[0] = -1;
 }
 
 CoarseShape coarse_shape(const LevelGeom &g, const Stencil<double> &P)
@@ -383,7 +415,7 @@ size_t coarse_inverse_ws(const LevelGeom &g)
 {
     const int mo = std::max(g.m[0], std::max(g.m[1], g.m[2]));
     const size_t n = g.N(), B = n / mo;
-    return B <= CB_MAX ? 3 * n * B : 0;
+    return B <= CB_MAX ? 3 * n * B + 1 : 0;
 }
 
 void launch_coarse_inverse(const LevelGeom &g, const Stencil<double> &P, const cd *q, cd *aug, cd *ws, int *info,
@@ -392,11 +424,16 @@ void launch_coarse_inverse(const LevelGeom &g, const Stencil<double> &P, const c
     const CoarseShape C = coarse_shape(g, P);
     const int n = C.B * C.nb, groups = (C.B + CB_COLS - 1) / CB_COLS;
     cd *chain = ws, *G = ws + 2 * (size_t)n * C.B;
+    CbScale *scale = reinterpret_cast<CbScale *>(ws + 3 * (size_t)n * C.B);
+    double offdiag = 0.0;
+    for (int k = 0; k < 3; ++k)
+        if (g.m[k] > 1) offdiag += 2.0 * std::hypot(P.c[k].re, P.c[k].im);
     launch_gj_init(info, s);
 #define CB_LAUNCH(NS)                                                                                          \
     do {                                                                                                       \
-        hipLaunchKernelGGL(k_coarse_chain<NS>, dim3(2), dim3(64 * CB_WAVES), 0, s, C, q, chain);               \
-        hipLaunchKernelGGL(k_coarse_diag<NS>, dim3(C.nb), dim3(64 * CB_WAVES), 0, s, C, q, (const cd *)chain, G); \
+        hipLaunchKernelGGL(k_coarse_chain<NS>, dim3(2), dim3(64 * CB_WAVES), 0, s, C, q, chain, scale);        \
+        hipLaunchKernelGGL(k_coarse_diag<NS>, dim3(C.nb), dim3(64 * CB_WAVES), 0, s, C, q, (const cd *)chain, G, \
+                           scale);                                                                             \
     } while (0)
     if (C.B <= CB_WAVES) CB_LAUNCH(1);
     else if (C.B <= 2 * CB_WAVES) CB_LAUNCH(2);
@@ -404,8 +441,9 @@ void launch_coarse_inverse(const LevelGeom &g, const Stencil<double> &P, const c
     else CB_LAUNCH(7);
 #undef CB_LAUNCH
     hipLaunchKernelGGL(k_coarse_cols, dim3(C.nb * groups, 2), dim3(256), 0, s, C, (const cd *)chain, (const cd *)G,
-                       aug, groups);
-    hipLaunchKernelGGL(k_coarse_check, dim3((n + 255) / 256, n), dim3(256), 0, s, q, (const cd *)aug, P, info);
+                       aug, groups, scale);
+    hipLaunchKernelGGL(k_coarse_check, dim3((n + 255) / 256, n), dim3(256), 0, s, q, (const cd *)aug, P, offdiag,
+                       (const CbScale *)scale, info);
 }
 
 }  // namespace ffmg

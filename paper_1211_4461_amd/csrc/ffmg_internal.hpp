@@ -179,7 +179,7 @@ void launch_gauss_jordan(cd *aug, int n, int *info, hipStream_t s, cd *ws);
 void launch_gj_init(int *info, hipStream_t s);
 // The coarsest operator's inverse by its block structure, into the right half
 // of aug (n x 2n; the left half is not written); info[0] = -1 where it is not
-// an inverse to 1e-9 (then the elimination above has to run), else 0.
+// an inverse to rounding (then the elimination above has to run), else 0.
 size_t coarse_inverse_ws(const LevelGeom &g);
 void launch_coarse_inverse(const LevelGeom &g, const Stencil<double> &P, const cd *q, cd *aug, cd *ws, int *info,
                            hipStream_t s);
