@@ -461,7 +461,9 @@ ffmg_status mg_profile_durations(ffmg_handle *h, int kernel, double *ms, int64_t
  * shapes; the best one depends on the device, the grid and the number of
  * directions.  FFMG_TUNE_FF_GEMM: the split-BF16 far-field GEMM (row tiles x
  * column tiles per wave, or a block tile staged in LDS and shared by its four
- * waves); with ff_precision FP64 it has one variant.
+ * waves; the last variant, the default, chooses among the others by the number
+ * of tiles of each of the map's contractions); with ff_precision FP64 it has one
+ * variant.
  * FFMG_TUNE_TAIL: the largest level (4096, 1024 or 256 interior points for
  * variants 0, 1, 2; in FP64 cycles 1024 at most; the finest level too where it
  * is that small) run inside the one-workgroup LDS tail of the fused 2D cycle;

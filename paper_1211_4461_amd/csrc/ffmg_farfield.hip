@@ -851,9 +851,9 @@ struct BfVariant {
 };
 static const BfVariant BF_VARIANTS[] = {{2, 1, false}, {2, 2, false}, {4, 1, false}, {4, 2, false}, {2, 4, false},
                                         {4, 4, false}, {8, 4, true},  {4, 8, true},  {8, 8, true}};
-constexpr int BF_NVARIANTS = (int)(sizeof(BF_VARIANTS) / sizeof(BF_VARIANTS[0]));
-constexpr int BF_DEFAULT_VARIANT = 3;     // the one mg_tune_get names while none is set
-constexpr int BF_AUTO_VARIANT = -1;       // chosen per launch by bf_variant_for
+// The variant after those: one of them chosen per launch by bf_variant_for (the
+// default).
+constexpr int BF_AUTO_VARIANT = (int)(sizeof(BF_VARIANTS) / sizeof(BF_VARIANTS[0]));
 constexpr int BF_RT_PAD = 8;
 constexpr long BF_COL_PAD = 4 * 4 * 16;   // 4 waves x CT <= 4 tiles x 16 columns (LDS blocks: <= 8 x 16)
 
@@ -863,7 +863,7 @@ struct GemmLaunchB {
     long ldP = 0;
 };
 
-// The variant for a contraction nothing was tuned for, by its tiles of 16 x 16:
+// The variant for a contraction by its tiles of 16 x 16:
 // the smallest wave tiles while they do not fill the chip (latency), then larger
 // ones, then, with three parts and enough rows, the blocks staged in LDS (with
 // two parts they move too little per product to pay).  All compute the same
@@ -991,9 +991,9 @@ struct FarFieldPlan {
 
 FarFieldPlan *ff_plan_create() { return new FarFieldPlan(); }
 void ff_plan_destroy(FarFieldPlan *p) { delete p; }
-int ff_plan_variants() { return BF_NVARIANTS; }
-int ff_plan_default_variant() { return BF_DEFAULT_VARIANT; }
-void ff_plan_set_variant(FarFieldPlan *p, int v) { p->variant = (v >= 0 && v < BF_NVARIANTS) ? v : BF_AUTO_VARIANT; }
+int ff_plan_variants() { return BF_AUTO_VARIANT + 1; }
+int ff_plan_default_variant() { return BF_AUTO_VARIANT; }
+void ff_plan_set_variant(FarFieldPlan *p, int v) { p->variant = (v >= 0 && v < BF_AUTO_VARIANT) ? v : BF_AUTO_VARIANT; }
 int ff_plan_variant(const FarFieldPlan *p) { return p->variant; }
 uint64_t ff_plan_generation(const FarFieldPlan *p) { return p->gen; }
 
