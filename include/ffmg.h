@@ -447,7 +447,9 @@ ffmg_status mg_residual_norm(ffmg_handle *h, const void *b, const void *u, doubl
  * residual + restriction (3D), 7 and 8 the finest-level pass of two
  * pre-smoothing sweeps, the residual and its full weighting (3D,
  * FFMG_TUNE_SWEEP3D variant 4; 7 from a guess, 8 from a zero guess, whose
- * launches are then not counted under 0 and 6).  mask = 0 disables.  mg_profile_read
+ * launches are then not counted under 0 and 6).  A finest level small enough for
+ * the one-workgroup tail (FFMG_TUNE_TAIL) runs as launches of its own while kernel
+ * 0 or 2 is enabled (the iterates are the same bits).  mask = 0 disables.  mg_profile_read
  * synchronises, returns the summed duration (ms) and launch count of one
  * kernel, and clears its record.  mg_profile_durations does the same but
  * writes each launch's duration (ms, in launch order) into ms[0 .. cap - 1]

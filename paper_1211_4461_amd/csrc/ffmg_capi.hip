@@ -526,7 +526,7 @@ void plan_tail_levels(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int 
 // coarsest level of more than 256 unknowns stays with the grid-wide kernels:
 // one workgroup takes longer to read its inverse than the launches it saves.
 template <typename T>
-void plan_tail(ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level = 0)
+void plan_tail(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level = 0)
 {
     tp = TailParams<T>{};
     lds = 0;
@@ -540,6 +540,16 @@ void plan_tail(ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level = 0
         max_nt = tail_count<T>(h);
     }
     plan_tail_levels<T>(h, tp, lds, min_level, max_nt);
+}
+
+// The tails of both precisions.  While the finest level's smoothing is profiled
+// that level stays out of them, so that its launches are there to be timed (the
+// iterates are the same bits).
+void plan_tails(ffmg_handle *h)
+{
+    const int min_level = (h->profile_mask & (1 << PROF_PRE | 1 << PROF_POST)) ? 1 : 0;
+    plan_tail<double>(h, h->tail64, h->tail_lds[0], min_level);
+    if (h->opt.precision == FFMG_FP32_IR) plan_tail<float>(h, h->tail32, h->tail_lds[1], min_level);
 }
 
 // The learned smoother: weight fragments, kappa h^2 on the finest level, and
@@ -697,8 +707,7 @@ ffmg_status setup_impl(ffmg_handle *h)
         TRY(read_info());
     }
     if (info != 0) return fail(h, FFMG_EINVAL, "coarsest operator is singular (zero pivot in column %d)", info - 1);
-    plan_tail<double>(h, h->tail64, h->tail_lds[0]);
-    if (ir) plan_tail<float>(h, h->tail32, h->tail_lds[1]);
+    plan_tails(h);
     if (h->opt.smoother == FFMG_SMOOTH_LEARNED) TRY(setup_learned(h));
     return FFMG_OK;
 }
@@ -1096,6 +1105,7 @@ ffmg_status mg_profile_enable(ffmg_handle *h, int enable)
 {
     if (!h) return FFMG_EINVAL;
     h->profile_mask = enable & ((1 << PROF_N) - 1);
+    plan_tails(h);
     return FFMG_OK;
 }
 
@@ -1715,8 +1725,7 @@ void set_tail_variant(ffmg_handle *h, int v)
 {
     if (v == h->tail_variant) return;
     h->tail_variant = v;
-    plan_tail<double>(h, h->tail64, h->tail_lds[0]);
-    if (h->opt.precision == FFMG_FP32_IR) plan_tail<float>(h, h->tail32, h->tail_lds[1]);
+    plan_tails(h);
     h->serial = next_handle_serial();
 }
 }  // namespace
