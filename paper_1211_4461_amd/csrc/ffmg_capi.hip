@@ -481,13 +481,13 @@ int tail_count(const ffmg_handle *h)
 
 // The tail of at most max_nt levels, from level min_level on at the earliest:
 // the longest run of levels ending at the coarsest that fit the kernel and its
-// LDS and hold at most TAIL_POINTS[tail_variant] points each.
+// LDS and hold at most TAIL_POINTS[variant] points each.
 template <typename T>
-void plan_tail_levels(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level, int max_nt)
+void plan_tail_levels(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level, int max_nt, int variant)
 {
     tp = TailParams<T>{};
     lds = 0;
-    const size_t max_points = (size_t)TAIL_POINTS[h->tail_variant];
+    const size_t max_points = (size_t)TAIL_POINTS[variant];
     const int nl = (int)h->L.size();
     size_t later = 0;       // elements of the levels below, none of them the first
     int top = nl;
@@ -526,7 +526,7 @@ void plan_tail_levels(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int 
 // coarsest level of more than 256 unknowns stays with the grid-wide kernels:
 // one workgroup takes longer to read its inverse than the launches it saves.
 template <typename T>
-void plan_tail(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level = 0)
+void plan_tail(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_level, int variant)
 {
     tp = TailParams<T>{};
     lds = 0;
@@ -539,7 +539,7 @@ void plan_tail(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_lev
         min_level = std::max(min_level, 1);
         max_nt = tail_count<T>(h);
     }
-    plan_tail_levels<T>(h, tp, lds, min_level, max_nt);
+    plan_tail_levels<T>(h, tp, lds, min_level, max_nt, variant);
 }
 
 // The tails of both precisions.  While the finest level's smoothing is profiled
@@ -548,8 +548,8 @@ void plan_tail(const ffmg_handle *h, TailParams<T> &tp, size_t &lds, int min_lev
 void plan_tails(ffmg_handle *h)
 {
     const int min_level = (h->profile_mask & (1 << PROF_PRE | 1 << PROF_POST)) ? 1 : 0;
-    plan_tail<double>(h, h->tail64, h->tail_lds[0], min_level);
-    if (h->opt.precision == FFMG_FP32_IR) plan_tail<float>(h, h->tail32, h->tail_lds[1], min_level);
+    plan_tail<double>(h, h->tail64, h->tail_lds[0], min_level, h->tail_variant);
+    if (h->opt.precision == FFMG_FP32_IR) plan_tail<float>(h, h->tail32, h->tail_lds[1], min_level, h->tail_variant);
 }
 
 // The learned smoother: weight fragments, kappa h^2 on the finest level, and
@@ -773,7 +773,7 @@ int tail_count32(const ffmg_handle *h) { return tail_count<float>(h); }
 
 void plan_tail32(const ffmg_handle *h, TailParams<float> &tp, size_t &lds, int max_nt)
 {
-    plan_tail_levels<float>(h, tp, lds, 1, max_nt);
+    plan_tail_levels<float>(h, tp, lds, 1, max_nt, h->tail_variant);
 }
 
 // One learned smoothing step on level l: r = b - A u (FP64), then
@@ -949,7 +949,7 @@ void fmg_start(ffmg_handle *h, const cd *b, cd *u, int k, const double *bnorm2, 
     }
     TailParams<T> tp = LP::tail(h);
     size_t tail_lds = LP::tail_lds(h);
-    if (tp.nt == last + 1) plan_tail<T>(h, tp, tail_lds, 1);   // no cycle on the finest level
+    if (tp.nt == last + 1) plan_tail<T>(h, tp, tail_lds, 1, h->tail_variant);   // no cycle on the finest level
     const bool tail_fmg = tp.nt >= 2;
     const int top = tail_fmg ? last + 1 - tp.nt : last;        // right-hand sides injected down to here
     launch_inject_rhs<T>(l0.g, b, LP::b(h->L[1]), bnorm2, h->stream, l0.q, h->pw_f);
@@ -1728,6 +1728,16 @@ void set_tail_variant(ffmg_handle *h, int v)
     plan_tails(h);
     h->serial = next_handle_serial();
 }
+
+// Whether the handle has an FP64 tail at its largest (variant 0), whichever
+// variant is set and whatever is profiled.
+bool has_tail(const ffmg_handle *h)
+{
+    TailParams<double> tp;
+    size_t lds;
+    plan_tail<double>(h, tp, lds, 0, 0);
+    return tp.nt > 0;
+}
 }  // namespace
 
 extern "C" {
@@ -1739,7 +1749,7 @@ int mg_tune_variants(const ffmg_handle *h, int tunable)
     case FFMG_TUNE_FF_GEMM: return (h->opt.ff_precision == FFMG_FF_FP64) ? 1 : ff_plan_variants();
     case FFMG_TUNE_TAIL:
         return (h->prob.dim == 2 && h->opt.tile_config == TILE_FUSED && h->opt.smoother != FFMG_SMOOTH_LEARNED &&
-                h->tail64.nt > 0)
+                has_tail(h))
                    ? TAIL_VARIANTS
                    : 1;
     case FFMG_TUNE_SMOOTH:
