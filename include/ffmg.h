@@ -479,10 +479,9 @@ ffmg_status mg_profile_durations(ffmg_handle *h, int kernel, double *ms, int64_t
  * tile_config 1.
  * FFMG_TUNE_PRE: the pre-smoothing of a fused 2D level with nu1 = 1 or 2 as
  * one pass of the sweeps, residual and full weighting (variant 0: on the finest
- * level 8-row tiles, 16-row for FP32 cycles from 2^21 points; 2: 8-row there for
- * FP32 cycles, 16-row for FP64) or
- * as the smoothing launch followed by the residual + restriction launch (1);
- * one variant for 3D and tile_config 1.
+ * level 8-row tiles, 16-row for FP32 cycles from 2^21 points; 2: the other of the
+ * two heights there) or as the smoothing launch followed by the residual +
+ * restriction launch (1); one variant for 3D and tile_config 1.
  * FFMG_TUNE_SWEEP3D: the weighted-Jacobi sweeps of a fused 3D level as one
  * z-marching pass per pair of sweeps (the first sweep's planes held in LDS,
  * the interpolation of the coarse correction formed inside the first pass)

@@ -14,6 +14,7 @@
 
 #include "ffmg_handle.hpp"
 #include "ffmg_learned.hpp"
+#include "ffmg_tiles.hpp"
 
 using namespace ffmg;
 
@@ -362,15 +363,8 @@ void vcycle_fused2d(ffmg_handle *h, int l, const cx<T> *b, cx<T> *u, bool zero_g
         // the sweeps, residual and full weighting in one pass
         const bool finest = (l == 0);
         int pi = finest ? prof_kernel_begin(h, PROF_PRE) : -1;
-        // finest level: 8 rows, in FP32 from 2^21 points 16 (variant 0), or the
-        // type's other height (variant 2: 8 rows FP32, 16 FP64); coarse levels:
-        // 16 rows with the 16-row smoothing tile, else 8.  FP32, two sweeps from
-        // a guess, 8 rows and 16: 255^2 5.6 us and 7.0, 511^2 6.3 and 7.6, 1023^2
-        // 12.2 and 12.1, 2047^2 31.6 and 30.3; from zero 5.0 and 6.0, 5.7 and 6.6,
-        // 10.5 and 11.2, 28.8 and 27.2.
-        const int other = sizeof(T) == 4 ? 8 : 16;
-        const int fdef = sizeof(T) == 4 && lv.g.N() >= (size_t)1 << 21 ? 16 : 8;
-        const int fh = finest ? (h->pre_variant == 2 ? other : fdef)
+        // coarse levels: 16 rows with the 16-row smoothing tile, else 8
+        const int fh = finest ? presmooth_rows(sizeof(T) == 4, lv.g.N(), h->pre_variant)
                               : (SMOOTH_TH[h->smooth_coarse_variant] >= 16 ? 16 : 8);
         launch_smooth_rr2d<T>(lv.g, LP::P(lv), nu1, zero_guess, u, b, LP::q(lv), t, LP::b(lc), h->stream, finest, stop,
                               fh);
