@@ -3,9 +3,9 @@
 The library exposes tunable kernel families (``mg_tune_variants``); every
 variant of a family computes the same bits with a different tile shape, and
 which one is fastest depends on the device and on the problem's shapes.  This
-module keys a choice by (device architecture, tunable and its number of
-variants, dimension, interior extents, number of directions, precision, the
-solve options that change the timed work), runs the library's own timing
+module keys a choice by (device architecture, tunable, its number of variants
+and the version of their meaning, dimension, interior extents, number of
+directions, precision, the solve options that change the timed work), runs the library's own timing
 sweep (``mg_tune_farfield``, ``mg_tune_solve``) on a cache miss, and stores
 the winner.
 
@@ -51,14 +51,19 @@ KEY_OPTIONS = ("nu1", "nu2", "nu_coarse", "inner_cycles", "fmg_cycles", "smoothe
                "ff_precision")
 
 
+# Raised whenever a variant number of some tunable comes to mean another kernel
+# (its count unchanged), so that choices timed on the former kernels are not applied.
+VARIANTS_VERSION = 2
+
+
 def key(arch: str, tunable: int, dim: int, shape, n_dirs: int, precision: int, n_variants: int = 0,
         options: Optional[dict] = None) -> str:
-    """Cache key: device, tunable and its variant count (a family that gains
-    a variant is tuned again), grid, directions, precision and the solve
-    options that affect timing."""
+    """Cache key: device, tunable, its variant count (a family that gains a
+    variant is tuned again) and the version of the variants, grid, directions,
+    precision and the solve options that affect timing."""
     ext = "x".join(str(int(m)) for m in shape)
     opts = ",".join(f"{k}={int((options or {}).get(k, 0))}" for k in KEY_OPTIONS)
-    return (f"{arch}|tunable={int(tunable)}|nv={int(n_variants)}|d={int(dim)}|m={ext}|M={int(n_dirs)}"
+    return (f"{arch}|tunable={int(tunable)}|nv={int(n_variants)}|v={VARIANTS_VERSION}|d={int(dim)}|m={ext}|M={int(n_dirs)}"
             f"|prec={int(precision)}|{opts}")
 
 
