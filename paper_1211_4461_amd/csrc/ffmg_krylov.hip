@@ -259,6 +259,13 @@ __device__ __forceinline__ void gm_solve_in(const double *n, const double *d, do
     }
 }
 
+// The small problem's matrix in LDS (as doubles: a shared variable has no
+// constructor), aligned as the complex values it is read as.
+template <int M>
+struct alignas(alignof(cd)) GmMatrix {
+    double v[2 * (M + 1) * M];
+};
+
 template <int M>
 __device__ __forceinline__ void gm_solve_small(const double *n, const double *d, double *c)
 {
@@ -266,8 +273,10 @@ __device__ __forceinline__ void gm_solve_small(const double *n, const double *d,
         cd H[M + 1][M];
         gm_solve_in<M>(n, d, c, H);
     } else {
-        __shared__ double Hs[2 * (M + 1) * M];
-        gm_solve_in<M>(n, d, c, reinterpret_cast<cd(&)[M + 1][M]>(Hs));
+        static_assert(alignof(GmMatrix<M>) >= alignof(cd) && sizeof(GmMatrix<M>) == sizeof(cd[M + 1][M]),
+                      "GmMatrix is read as cd[M + 1][M]");
+        __shared__ GmMatrix<M> Hs;
+        gm_solve_in<M>(n, d, c, reinterpret_cast<cd(&)[M + 1][M]>(Hs.v));
     }
 }
 
