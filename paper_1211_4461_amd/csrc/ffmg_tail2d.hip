@@ -440,11 +440,12 @@ struct TailLoads {
     cx<T> q[TAIL_MAX_LEVELS];
     CoarseInverse<TAIL_NT<KS>> ci;
 
-    __device__ __forceinline__ void load(const TailParams<T> &tp, const cd *ainv)
+    // cycles: whether V-cycles follow (the coarsest solve alone needs no q)
+    __device__ __forceinline__ void load(const TailParams<T> &tp, const cd *ainv, bool cycles = true)
     {
 #pragma unroll
         for (int i = FIRST; i < TAIL_MAX_LEVELS; ++i)
-            if (i + 1 < tp.nt) q[i] = load_point(tp.lv[i].q, tp.lv[i]);
+            if (cycles && i + 1 < tp.nt) q[i] = load_point(tp.lv[i].q, tp.lv[i]);
         if (ainv) ci.load(tp.aug, tp.nc);
     }
     // (the coarsest level's whole array: its solve writes the interior only)
@@ -457,11 +458,11 @@ struct TailLoads {
             for (int j = threadIdx.x; j < n; j += blockDim.x) v.A[j - lead] = cx<T>{T(0), T(0)};
         }
     }
-    __device__ __forceinline__ void store(const TailParams<T> &tp, cx<T> *lds, cd *ainv)
+    __device__ __forceinline__ void store(const TailParams<T> &tp, cx<T> *lds, cd *ainv, bool cycles = true)
     {
 #pragma unroll
         for (int i = FIRST; i < TAIL_MAX_LEVELS; ++i)
-            if (i + 1 < tp.nt) {
+            if (cycles && i + 1 < tp.nt) {
                 const TailView<T> v(lds, tp.lv[i]);
                 if ((int)threadIdx.x < v.slots) v.q[threadIdx.x] = q[i];
             }
@@ -544,13 +545,14 @@ __device__ __forceinline__ void tail2d_fmg_body(const TailParams<T> &tp, const c
     cd *ainv = inverse_at(tp, lds);
     {
         TailLoads<T, KS> ld;
-        ld.load(tp, ainv);
+        ld.load(tp, ainv, k > 0);
         ld.clear(tp, lds);
-        ld.store(tp, lds, ainv);
+        ld.store(tp, lds, ainv, k > 0);
     }
-    // point (x, y) of level i is point (2^i (x + 1) - 1, 2^i (y + 1) - 1) of level 0
+    // point (x, y) of level i is point (2^i (x + 1) - 1, 2^i (y + 1) - 1) of level
+    // 0; without cycles only the coarsest level's right-hand side is read
 #pragma unroll 1
-    for (int i = first; i < nt; ++i) {
+    for (int i = k > 0 ? first : nt - 1; i < nt; ++i) {
         const TailView<T> v(lds, tp.lv[i]);
         const int x = tid & ((1 << v.lp) - 1), y = tid >> v.lp;
         const bool in = x < v.mx && y < v.my;
@@ -572,6 +574,7 @@ __device__ __forceinline__ void tail2d_fmg_body(const TailParams<T> &tp, const c
             if constexpr (KS > 1) {
 #pragma unroll
                 for (int r = 0; r < KS; ++r) {
+                    if (k == 0) break;
                     const size_t j = (size_t)(top.strip * KS + r) * L0.mx + top.x;
                     top.b[r] = ld_masked(b_top, j, top.in(r));
                     top.q[r] = ld_masked(L0.q, j, top.in(r));
