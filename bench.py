@@ -489,7 +489,7 @@ def run_ionization(ff, torch, W, lanes=4):
                      "max_rel_dev_from_printed_points_E_gt_-0.7": round(max(dev), 4)}
     out["speedup_vs_plain"] = round(out["plain_fp64"]["ms_per_energy"] / out["mixed"]["ms_per_energy"], 3)
     out["note"] = ("cross sections: [single, double, total] per energy, half the outgoing flux per kind of channel; "
-                   "the setup phase is dominated by the blocked Gauss-Jordan inverse of the 31^2 coarsest level")
+                   "the setup phase is dominated by the inverse of the 31^2 coarsest level from its slices")
     return out
 
 

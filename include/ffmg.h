@@ -485,12 +485,12 @@ ffmg_status mg_profile_durations(ffmg_handle *h, int kernel, double *ms, int64_t
  * FFMG_TUNE_SWEEP3D: the weighted-Jacobi sweeps of a fused 3D level as one
  * z-marching pass per pair of sweeps (the first sweep's planes held in LDS,
  * the interpolation of the coarse correction formed inside the first pass)
- * with tiles chosen by type and number of points (variant 0), 64-point-wide
- * tiles of 16 rows in FP32 and 8 in FP64 (variant 2), 32-point-wide tiles of
- * 16 and 8 rows for the pass that interpolates the coarse correction and the
- * variant-0 tiles for the others (variant 3), variant 3 with the two FP32
+ * with tiles of 64 x 8 points in FP32 and by the number of points in FP64
+ * (variant 0), of 64 x 16 in FP32 and 64 x 8 in FP64 (variant 2), those of variant
+ * 0 but by the number of points in FP32 and 32 x 8 in FP64 for the pass that
+ * interpolates the coarse correction (variant 3), variant 3 with the two FP32
  * pre-smoothing sweeps, the residual and its full weighting in one pass
- * (variant 4, the default of FFMG_FP32_IR handles; FP64 levels as variant 3),
+ * (variant 4, the default of FFMG_FP32_IR handles; FP64 levels as variant 0),
  * or one pass per sweep (variant 1); one variant for 2D and tile_config 1.
  * FFMG_TUNE_BATCH (set on the first handle of a batch, 2D FFMG_FP32_IR fused
  * handles): the tile heights of mg_solve_batched's smoothing and one-pass

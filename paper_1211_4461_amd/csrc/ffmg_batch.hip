@@ -101,7 +101,8 @@ namespace {
 
 // The control blocks of all instances into the host's page-locked array.  With a
 // copy each, and the call's five tables copied one by one, a batch of 24 instances
-// on three grids took 3495 us, now 3414.
+// on three grids took 3254 to 3315 us, now 3180 to 3211 (medians of 60 calls in
+// eight processes of each form in turn).
 __global__ __launch_bounds__(64) void k_gather_ctl(const CtlJob *__restrict__ jobs, int n, SolveCtl *__restrict__ out)
 {
     const int i = blockIdx.x * 64 + threadIdx.x;
