@@ -32,6 +32,7 @@
 #include <cmath>
 
 #include "ffmg_internal.hpp"
+#include "ffmg_wave.hpp"
 
 namespace ffmg {
 
@@ -89,15 +90,7 @@ __device__ __forceinline__ unsigned wave_max(unsigned v)
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-__device__ __forceinline__ double readlane_d(double v, int lane)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(b & 0xffffffff), lane);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
-}
-
-__device__ __forceinline__ cd readlane_cd(cd v, int lane) { return cd{readlane_d(v.re, lane), readlane_d(v.im, lane)}; }
+__device__ __forceinline__ cd readlane_cd(cd v, int lane) { return cd{lane_value(v.re, lane), lane_value(v.im, lane)}; }
 
 // 1 / a: the hardware reciprocal with two Newton steps (a zero gives NaN).
 __device__ __forceinline__ cd cb_recip(cd a)

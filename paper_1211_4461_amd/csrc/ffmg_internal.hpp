@@ -145,7 +145,9 @@ constexpr int GMRES_MAX_M = 8;
 constexpr int GM_D = 16;
 constexpr int GM_C = GM_D + 2 * GMRES_MAX_M * GMRES_MAX_M;
 constexpr int GM_S = GM_C + 2 * GMRES_MAX_M;
-constexpr int GM_PARTS = (GMRES_MAX_M + 1 + 2 * GMRES_MAX_M * GMRES_MAX_M) * 1024;
+// Most blocks of a grid-wide pass, each with a partial sum per value.
+constexpr int GM_BLOCKS = 512;
+constexpr int GM_PARTS = (GMRES_MAX_M + 1 + 2 * GMRES_MAX_M * GMRES_MAX_M) * GM_BLOCKS;
 // One GMRES(m) smoothing step in place on a level (zero: u is 0 on entry);
 // Z: m + 2 vectors of the level, S: GM_S doubles, parts: GM_PARTS doubles;
 // fused: m + 3 launches, else the reference 4 m + 3.

@@ -38,11 +38,11 @@ namespace ffmg {
 
 namespace {
 
-// Grid-stride blocks (and partial sums per value) and their threads.  Every
+// Threads of the grid-wide passes' blocks (GM_BLOCKS at most).  Every
 // block of a pass adds up all blocks' partial sums of the pass before, so few
 // large blocks: with 1024 of 256 threads a pass read 57 MB of partial sums
 // (511 x 511, FP32, m = 3: the four passes that do, 33 us then, 25 us now).
-constexpr int GM_BLOCKS = 512, GM_BT = 512;
+constexpr int GM_BT = 512;
 // partial-sum slots: n_i at slot i (i <= m), d_ij (re, im) at NSLOT_D + 2 (j GMRES_MAX_M + i)
 constexpr int NSLOT_D = GMRES_MAX_M + 1;
 

@@ -1051,12 +1051,14 @@ static void launch_sweep2_3d_tile(const LevelGeom &g, const Stencil<T> &P, const
 //   FP64: 32 x 16 (1.5 slots a column, 512 blocks at least) against 64 x 4 (3
 //   slots, 1024 blocks), interpolating and plain pass: 127^3 33 and 28 us
 //   against 50 and 32, 511^3 2.04 and 1.94 ms against 2.60 and 2.00.
-//   FP32: 32 x 16 where the pass interpolates (it also stages coarse planes),
-//   else 64 x 8.
-// Small levels are latency bound: up to 2^17 points small tiles (12 x 12, one
-// column a thread: 31^3 interpolating 7.3 us against 9.1 and 15^3 6.2 against
-// 9.3 with 64 x 4; FP64), up to 2^20 the large tile with a column and a half a
-// thread (63^3 10.6 us against 20.2).
+//   FP32: 32 x 16 where the pass interpolates (it also stages coarse planes;
+//   variants 3 and 4), else 64 x 8 at every size.
+// Variant 2 is 64 x 16 (FP32) and 64 x 8 (FP64), variant 3 in FP64 32 x 8 where
+// the pass interpolates; variant 4 in FP64 is variant 0.  Small levels, which are
+// latency bound, take other tiles where none of these is fixed: up to 2^17 points
+// 12 x 12 (one column a thread: 31^3 interpolating 7.3 us against 9.1 and 15^3 6.2
+// against 9.3 with 64 x 4; FP64), up to 2^20 the large tile with a column and a
+// half a thread (63^3 10.6 us against 20.2).
 template <typename T>
 void launch_sweep2_3d(const LevelGeom &g, const Stencil<T> &P, const cx<T> *u, const cx<T> *ec, const cx<T> *b,
                       const cx<T> *q, cx<T> *out, hipStream_t s, bool finest, const int *stop, bool zero, int shape)
@@ -1064,12 +1066,12 @@ void launch_sweep2_3d(const LevelGeom &g, const Stencil<T> &P, const cx<T> *u, c
     constexpr bool F64 = sizeof(T) == 8;
     constexpr size_t SMALL = (size_t)1 << 17, MEDIUM = (size_t)1 << 20;
     const size_t N = g.N();
-    const bool narrow = ec && !zero && (shape == 3 || shape == 4);
+    const bool prol = ec && !zero;
     if (shape == 2) {
         launch_sweep2_3d_tile<T, F64 ? 8 : 16, 64>(g, P, u, ec, b, q, out, s, finest, stop, zero);
-    } else if (F64 && shape == 3 && narrow) {
+    } else if (F64 && prol && shape == 3) {
         launch_sweep2_3d_tile<T, F64 ? 8 : 16, 32>(g, P, u, ec, b, q, out, s, finest, stop, zero);
-    } else if (F64 || narrow) {
+    } else if (F64 || (prol && (shape == 3 || shape == 4))) {
         if (N < SMALL)
             launch_sweep2_3d_tile<T, 12, 12>(g, P, u, ec, b, q, out, s, finest, stop, zero, 256);
         else if (N < MEDIUM)
