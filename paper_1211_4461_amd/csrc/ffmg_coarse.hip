@@ -19,10 +19,11 @@
 // loses digits that the whole matrix has.  The result is therefore held to
 // rounding, max |A X - I| <= CB_ROUND eps ||A|| max |X|, and a matrix on which it
 // fails is inverted by the pivoted elimination of ffmg_stencil.hip instead.
-// Measured in units of eps ||A|| max |X|: at most 3.1 over random contrasts of
-// size 0 to 50 on grids from 3 x 3 to 31 x 31 and 7 x 7 x 15, 1.9 on the 31 x 31
-// ionisation operators; with a first slice singular up to a relative shift of
-// 1e-3, 1e-5, 1e-7 on 7 x 15 points 13, 1053, 109054 (elimination: 1).
+// Measured in units of eps ||A|| max |X| over random operators (boxes, wavenumbers
+// and contrasts over two decades): 7 x 7 at most 2.9 of 200, 15 x 15 3.2 of 100, 31 x 31
+// 3.0 of 12, 7 x 7 x 7 median 2.7 and at most 6.4 of 200; the 31 x 31 ionisation
+// operators 1.9.  With a first slice singular up to a relative shift of 1e-3, 1e-5,
+// 1e-7 on 7 x 15 points 13, 1053, 109054 (elimination: 1).
 //
 // The two chains are bound by latency (B nb dependent pivot steps of 0.6 us for
 // B = 31, 0.8 us for B = 49: a 64-lane arg-max, one reciprocal, one barrier).
